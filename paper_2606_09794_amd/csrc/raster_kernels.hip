@@ -51,6 +51,8 @@
 //             and quaternion.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "../../include/nasg.h"
 #include "nasg_device.hpp"
 #include "raster.hpp"
@@ -58,11 +60,19 @@
 namespace nasg {
 
 constexpr double kNear = 0.2;
-constexpr float kClamp = 0.99f;
+constexpr double kClamp = 0.99;
 constexpr double kSupport = 9.0;
 constexpr int kBinParts = 8;  // most tile classes of the binning pass
 constexpr int kBinLdsTiles = 8192;      // class tiles one LDS-counting block holds
 constexpr int kBinPrimsPerThread = 32;  // primitives per thread of an LDS-counting block
+
+// A primitive reaches a pixel with rho >= e^{-9/2} = 0.0111, so an opacity
+// above 0.99 / 0.0111 = 89.2 is clamped on its whole support: any larger one
+// (or a NaN, whose alpha is the clamp too) acts as kSigmaMax.
+constexpr float kSigmaMax = 128.f;
+__device__ inline double opacity(float sigma) {
+  return static_cast<double>(fminf(sigma, kSigmaMax));
+}
 
 __global__ void raster_begin(RasterArgs a) {
   const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -185,14 +195,21 @@ template <bool GEOM>
 __global__ void raster_finish_grads(RasterArgs a) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= a.n) return;
+  // the render kernel's sums are in units of the opacity (see there)
   const double* acc = a.grad_acc + kAccStride * i;
+  const double sg = opacity(a.opac[i]);
   if (a.grad_colors != nullptr) {
-    a.grad_colors[3 * i + 0] = static_cast<float>(acc[0]);
-    a.grad_colors[3 * i + 1] = static_cast<float>(acc[1]);
-    a.grad_colors[3 * i + 2] = static_cast<float>(acc[2]);
+    a.grad_colors[3 * i + 0] = static_cast<float>(sg * acc[0]);
+    a.grad_colors[3 * i + 1] = static_cast<float>(sg * acc[1]);
+    a.grad_colors[3 * i + 2] = static_cast<float>(sg * acc[2]);
   }
   if (a.grad_opac != nullptr) a.grad_opac[i] = static_cast<float>(acc[3]);
-  if constexpr (GEOM) geometry_chain(a, i, acc + 4, a.grad_means, a.grad_scales, a.grad_rots);
+  if constexpr (GEOM) {
+    // dL/dq = -sigma s / 2 per pixel, q = a dx^2 + 2 b dx dy + c dy^2
+    const double g2[5] = {sg * acc[4], sg * acc[5], -0.5 * sg * acc[6], -sg * acc[7],
+                          -0.5 * sg * acc[8]};
+    geometry_chain(a, i, g2, a.grad_means, a.grad_scales, a.grad_rots);
+  }
 }
 
 __global__ void raster_project(RasterArgs a) {
@@ -610,13 +627,13 @@ __global__ __launch_bounds__(256) void raster_sort_network(RasterArgs a) {
   if (threadIdx.x == 0) a.cursor[tile] = ~c;
 }
 
+// A staged tile entry: pixel-space mean, conic (q = a dx^2 + 2 b dx dy + c dy^2),
+// colour, opacity and the largest rho below the alpha clamp. Every field is
+// FP64 so that the pixel loops convert nothing.
 struct StageEntry {
-  double u, v, a, b2, c;  // pixel-space mean and conic, b2 = 2 b
-  double c0, c1, c2;      // colour
-  float sigma;
-  uint32_t mask;          // row bands (rows 4 b .. 4 b + 3 of the tile) the q <= 9 box meets
-  int32_t idx;
-  int32_t pad;
+  double u, v, a, b, c;
+  double sigma, rmax;     // alpha = sigma min(rho, rmax)
+  double c0, c1, c2;
 };
 
 // Totals of several per-lane values over the 64 lanes of a wavefront (every
@@ -677,114 +694,109 @@ __device__ inline float lane_sums4(const float (&x)[4]) {
 __device__ inline bool lane_writes4(int lane) { return (lane & 0xF) == 0; }
 __device__ inline int lane_slot4(int lane) { return 2 * ((lane >> 4) & 1) + ((lane >> 5) & 1); }
 
-// Transmittance as t * 2^E (E a multiple of kRenorm). t is renormalised every
-// kRenormEvery entries of a wavefront's list and at the end of each chunk, so
-// at most kRenormEvery layers (each multiplying t by at least 0.01 going
-// forward, or dividing it by at least 0.01 going back) pass between checks:
-// t stays within [2^-500 1e-64, 1] in the forward and below 2^300 1e64 in the
-// backward, normal doubles, and a pixel behind thousands of layers keeps an
-// exact transmittance for the backward's recovery by division.
+// Transmittance as t * 2^E (E a multiple of kRenorm). t is renormalised after
+// every 64 staged entries, so at most 64 layers (each multiplying t by at
+// least 0.01 going forward, or dividing it by at least 0.01 going back) pass
+// between checks: t stays within [2^-500 1e-128, 1] in the forward and below
+// 2^300 1e128 in the backward, normal doubles, and a pixel behind thousands of
+// layers keeps an exact transmittance for the backward's recovery by division.
 constexpr int kRenorm = 500;
-constexpr int kRenormEvery = 32;
 // rho = exp(-q/2) = 2^(q * (-log2(e) / 2)); the constant is exact in float
 // (half of the float log2 e), so this is the float exponential of -q/2
 constexpr float kNegHalfLog2e = -0.72134752044448170368f;
-
-// Minimum over the rectangle [x0, x1] x [y0, y1] of the positive definite
-// q = a dx^2 + b2 dx dy + c dy^2 (dx = x - u, dy = y - v): zero if (u, v) is
-// inside; otherwise on the boundary, where each edge is a 1D quadratic
-// minimised at its vertex clamped to the edge.
-__device__ inline double quad_min_rect(double a, double b2, double c, double u, double v,
-                                       double x0, double x1, double y0, double y1) {
-  if (u >= x0 && u <= x1 && v >= y0 && v <= y1) return 0.0;
-  const double hb = 0.5 * b2, ia = rcp64(a), ic = rcp64(c);
-  double best = INFINITY;
-#pragma unroll
-  for (int side = 0; side < 2; ++side) {
-    const double dx = (side ? x1 : x0) - u;  // vertical edge
-    const double dy = fmin(fmax(-hb * dx * ic, y0 - v), y1 - v);
-    best = fmin(best, a * dx * dx + b2 * dx * dy + c * dy * dy);
-    const double ey = (side ? y1 : y0) - v;  // horizontal edge
-    const double ex = fmin(fmax(-hb * ey * ia, x0 - u), x1 - u);
-    best = fmin(best, a * ex * ex + b2 * ex * ey + c * ey * ey);
-  }
-  return best;
-}
-
-// EXACT adds the exact band test to the box test; it pays in the backward,
-// whose per-entry work is large, not in the forward, where its staging cost
-// outweighs the entries it removes (measured).
-template <bool EXACT>
-__device__ inline void stage_entry(const RasterArgs& a, const uint64_t* list, int e, double x0,
-                                   double y0, StageEntry* slot) {
-  const int32_t idx = static_cast<int32_t>(static_cast<uint32_t>(list[e]));
-  const RenderRec r = a.rec[idx];
+__device__ inline RenderRec stage_entry(const RasterArgs& a, const uint64_t* list, int e,
+                                        StageEntry* slot, int32_t* idx) {
+  *idx = static_cast<int32_t>(static_cast<uint32_t>(list[e]));
+  const RenderRec r = a.rec[*idx];
   StageEntry s;
   s.u = r.u;
   s.v = r.v;
   s.a = r.a;
-  s.b2 = r.b2;
+  s.b = 0.5 * r.b2;
   s.c = r.c;
+  s.sigma = opacity(r.sigma);
+  s.rmax = s.sigma >= kClamp ? kClamp / s.sigma : 2.0;   // rho <= 1: no clamp below
   s.c0 = r.c0;
   s.c1 = r.c1;
   s.c2 = r.c2;
-  s.sigma = r.sigma;
-  s.idx = idx;
-  s.pad = 0;
-  // a band's bit is set when the ellipse q <= 9 can reach one of its pixel
-  // centres: the box test and, with EXACT, the minimum of q over the band's
-  // rectangle of pixel centres (with a relative margin far above rounding)
-  uint32_t mask = 0;
-  if (r.u + r.ex >= x0 + 0.5 && r.u - r.ex <= x0 + 15.5) {
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const double ylo = y0 + 4 * b + 0.5, yhi = ylo + 3.0;
-      if (r.v + r.ey >= ylo && r.v - r.ey <= yhi &&
-          (!EXACT || quad_min_rect(r.a, r.b2, r.c, r.u, r.v, x0 + 0.5, x0 + 15.5, ylo, yhi) <=
-                         kSupport * (1.0 + 1e-9)))
-        mask |= 1u << b;
-    }
-  }
-  s.mask = mask;
   *slot = s;
+  return r;
 }
 
-// Each wavefront lists, in order, the staged entries whose band mask meets
-// `bits`; returns the list length (uniform).
-__device__ inline int wave_compact(const StageEntry* stage, int lim, uint32_t bits,
-                                   int16_t* wl) {
-  const int lane = static_cast<int>(threadIdx.x) & 63;
-  int n = 0;
-  for (int g = 0; g < lim; g += 64) {
-    const int k = g + lane;
-    const bool want = k < lim && (stage[k].mask & bits) != 0;
-    const uint64_t bal = __ballot(want);
-    const int below = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(bal >> 32),
-                                                 __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(bal), 0));
-    if (want) wl[n + below] = static_cast<int16_t>(k);
-    n += __popcll(bal);
+// Where the ellipse q <= 9 of a record reaches, for culling an entry against
+// the rectangles of pixel centres that a wavefront works on. On a horizontal
+// line dy the ellipse spans dx = -(b/a) dy -+ (3/sqrt a) sqrt(1 - (dy/ey)^2),
+// ey its vertical half-extent; over a band of lines the right end is largest
+// at the line nearest to the right extreme point (dy = -(b/c) ex), the left
+// end at the line nearest to its mirror image. FP32, kept conservative: the
+// record's half-extents are rounded outward by 1e-5 and 0.01 pixel (which
+// bounds the loss from the extreme point's rounding by 0.01 pixel), bands are
+// widened by the rounding of their coordinates and spans by 0.02 pixel and
+// 2e-6 of the sizes that enter. A NaN culls nothing. About 30 instructions a
+// band, against some 70 for the minimum of q over the band's rectangle.
+struct Reach {
+  float u, v, ex, ey;   // centre relative to the tile's corner, half-extents
+  float iey, slope, w;  // 1/ey, -b/a, 3/sqrt a
+  float dyr, mx, my;    // dy of the right extreme point, margins
+};
+
+__device__ inline Reach reach_of(const RenderRec& r, double x0, double y0) {
+  Reach e;
+  e.u = static_cast<float>(r.u - x0);
+  e.v = static_cast<float>(r.v - y0);
+  e.ex = r.ex;
+  e.ey = r.ey;
+  e.iey = __builtin_amdgcn_rcpf(r.ey);
+  const double hb = -0.5 * r.b2;
+  e.slope = static_cast<float>(hb * __builtin_amdgcn_rcp(r.a));
+  e.w = 3.f * static_cast<float>(__builtin_amdgcn_rsq(r.a));
+  const float d = static_cast<float>(hb * __builtin_amdgcn_rcp(r.c)) * r.ex;
+  e.dyr = fminf(fmaxf(d, -r.ey), r.ey);
+  e.mx = fmaf(2e-6f, r.ex + fabsf(e.u), 0.02f);
+  e.my = fmaf(4e-7f, fabsf(e.v), 1e-5f);
+  return e;
+}
+
+// Bit k is set when the ellipse may reach a pixel centre of column k of the
+// band of rows [row, row + ROWS) (tile-relative), columns COLS pixels wide.
+template <int ROWS, int COLS>
+__device__ inline uint32_t reach_band(const Reach& e, int row) {
+  const float yl = (static_cast<float>(row) + 0.5f) - e.v - e.my;
+  const float yh = (static_cast<float>(row + ROWS) - 0.5f) - e.v + e.my;
+  const float dr = fminf(fmaxf(e.dyr, yl), yh), dl = fminf(fmaxf(-e.dyr, yl), yh);
+  const float sr = dr * e.iey, sl = dl * e.iey;
+  const float xr = e.u + e.mx + fmaf(e.slope, dr, e.w * __builtin_amdgcn_sqrtf(fmaxf(fmaf(-sr, sr, 1.f), 0.f)));
+  const float xl = e.u - e.mx + fmaf(e.slope, dl, -e.w * __builtin_amdgcn_sqrtf(fmaxf(fmaf(-sl, sl, 1.f), 0.f)));
+  uint32_t bits = 0;
+#pragma unroll
+  for (int k = 0; k < kTile / COLS; ++k) {
+    const float lo = COLS * k + 0.5f, hi = COLS * k + (COLS - 0.5f);
+    if (!(xr < lo) && !(xl > hi)) bits |= 1u << k;
   }
-  return n;
+  return yl > e.ey || yh < -e.ey ? 0u : bits;
 }
 
 // Thread layout of the render kernels: a block of 256 / RPL threads per
-// 16 x 16 tile; lane l of wavefront w owns column l & 15 and the RPL rows
-// 4 RPL w + (l >> 4) + 4 j, j < RPL (row band RPL w + j), so an entry's dx
-// terms are shared by a lane's RPL pixels.
-// Rows per lane, measured on MI355X at 3 M primitives and 1920 x 1080: the
-// forward is fastest at one pixel per thread (occupancy hides the LDS and
-// FP64 latencies), the backward at four (one wavefront per tile: the four
-// per-entry wavefront sums and atomics are shared by four pixels per lane).
-constexpr int kFwdRows = 1;
-constexpr int kBwdRows = 4;
-
+// 16 x 16 tile, each lane RPL pixels. RPL = 1: wavefront w owns the 8 x 8
+// quadrant (w & 1, w >> 1). RPL = 4: one wavefront owns the tile, lane l the
+// pixels of column l & 15 in rows (l >> 4) + 4 j (row band j), so that an
+// entry's dx terms, its wavefront totals and its atomics are shared by four
+// pixels. An entry that cannot reach a quadrant or band skips it for the whole
+// wavefront: of the pixels so evaluated, at 3 M primitives and 1920 x 1080 the
+// ellipse covers 0.61 in 8 x 8 quadrants and 0.55 in 16 x 4 bands (0.44 with
+// the bounding box alone).
 template <int RPL>
 struct TileMap {
+  static_assert(RPL == 1 || RPL == 4, "rows per lane");
   int px, py0;     // the lane's column and first row
   int wave;
   double x0, y0;   // the tile's corner
   bool in_x;
   int height;
+  __device__ bool in(int j) const { return in_x && py0 + 4 * j < height; }
+  __device__ int64_t pixel(int j, int width) const {
+    return static_cast<int64_t>(py0 + 4 * j) * width + px;
+  }
 };
 
 template <int RPL>
@@ -792,9 +804,9 @@ __device__ inline TileMap<RPL> tile_map(const RasterArgs& a, int64_t tile) {
   TileMap<RPL> m;
   const int tx = static_cast<int>(tile % a.tiles_x), ty = static_cast<int>(tile / a.tiles_x);
   const int lane = static_cast<int>(threadIdx.x) & 63;
-  m.wave = static_cast<int>(threadIdx.x) >> 6;
-  m.px = tx * kTile + (lane & 15);
-  m.py0 = ty * kTile + 4 * RPL * m.wave + (lane >> 4);
+  m.wave = RPL == 4 ? 0 : __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  m.px = tx * kTile + (RPL == 4 ? lane & 15 : 8 * (m.wave & 1) + (lane & 7));
+  m.py0 = ty * kTile + (RPL == 4 ? lane >> 4 : 8 * (m.wave >> 1) + (lane >> 3));
   m.x0 = tx * kTile;
   m.y0 = ty * kTile;
   m.in_x = m.px < a.width;
@@ -802,80 +814,112 @@ __device__ inline TileMap<RPL> tile_map(const RasterArgs& a, int64_t tile) {
   return m;
 }
 
+// The units of the tile that an entry may reach: bit j is row band j (BANDS)
+// or quadrant j (column half j & 1, row half j >> 1). kSlowBit: the entry's
+// alpha can reach the clamp.
+constexpr uint32_t kSlowBit = 16;
+
+template <bool BANDS>
+__device__ inline uint32_t unit_mask(const RenderRec& r, double x0, double y0) {
+  const Reach e = reach_of(r, x0, y0);
+  uint32_t mask = 0;
+  if constexpr (BANDS) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) mask |= reach_band<4, 16>(e, 4 * j) << j;
+  } else {
+    mask = reach_band<8, 8>(e, 0) | (reach_band<8, 8>(e, 8) << 2);
+  }
+  return mask != 0 && opacity(r.sigma) >= kClamp ? mask | kSlowBit : mask;
+}
+
+// The part of a unit mask that concerns wavefront w.
 template <int RPL>
-__global__ __launch_bounds__(256 / RPL) void raster_render_fwd(RasterArgs a) {
-  constexpr int kBlock = 256 / RPL;
+__device__ inline uint32_t wave_units(uint32_t mask, int w) {
+  return RPL == 4 ? mask & ~kSlowBit : (mask >> w) & 1u;
+}
+
+// Keeps a value in vector registers from here on: an entry's fields are read
+// from LDS once, not again in every pixel's branch.
+__device__ __forceinline__ void keep(double& x) { asm("" : "+v"(x)); }
+
+// One pixel per thread. Each wavefront walks, in order, the staged entries
+// that reach its quadrant, picked 64 at a time from a ballot by scalar bit
+// scans (no list in LDS). Per entry: eight FP64 instructions for q and the
+// support test, then rho in FP32, alpha, three colour sums and the
+// transmittance in FP64. While no entry can reach the clamp and every pixel
+// has E = 0 the clamp and the scale factor 2^E are left out (fast). Bound by
+// the entries' reads from LDS (72 B per wavefront and entry) and by VALU
+// issue, in about equal parts: 2.10 -> 1.55 ms at 3 M primitives and
+// 1920 x 1080, 233 -> 174 us at 500 k and 1280 x 720 against 16 x 4 bands
+// culled by bounding box with a compacted list in LDS. Two pixels per lane
+// (half the LDS reads, half the waves) took 1.51 ms and 184 us, and twice the
+// time on a few tiles.
+__global__ __launch_bounds__(256) void raster_render_fwd(RasterArgs a) {
+  constexpr int kBlock = 256;
   __shared__ StageEntry stage[kBlock];
-  __shared__ int16_t wlist[kBlock / 64][kBlock];
+  __shared__ uint32_t smask[kBlock];
   const int64_t tile = blockIdx.x;
-  const TileMap<RPL> m = tile_map<RPL>(a, tile);
-  const double cxp = m.px + 0.5;
+  const TileMap<1> m = tile_map<1>(a, tile);
+  const double cxp = m.px + 0.5, cyp = m.py0 + 0.5;
   const int cnt = __builtin_amdgcn_readfirstlane(min(a.cursor[tile], a.cap));
   const uint64_t* list = a.lists + tile * a.cap;
-  const uint32_t bits = ((1u << RPL) - 1u) << (RPL * m.wave);
-  int16_t* wl = wlist[m.wave];
+  const int lane = static_cast<int>(threadIdx.x) & 63;
+  const bool in = m.in(0);
 
-  double C[RPL][3], t[RPL], pw[RPL];
-  int E[RPL];
-  bool in[RPL];
-#pragma unroll
-  for (int j = 0; j < RPL; ++j) {
-    C[j][0] = C[j][1] = C[j][2] = 0.0;
-    t[j] = 1.0;  // T = t * pw, pw = 2^E
-    pw[j] = 1.0;
-    E[j] = 0;
-    in[j] = m.in_x && m.py0 + 4 * j < m.height;
-  }
-  auto renorm = [&]() {
-#pragma unroll
-    for (int j = 0; j < RPL; ++j) {
-      if (t[j] < 0x1p-500) {
-        t[j] *= 0x1p500;
-        E[j] -= kRenorm;
-        pw[j] = ldexp(1.0, E[j]);
+  double C0 = 0.0, C1 = 0.0, C2 = 0.0;
+  double t = 1.0, pw = 1.0;   // T = t * pw, pw = 2^E
+  int E = 0;
+  auto walk = [&](auto fast, uint64_t bal, const StageEntry* st) {
+    constexpr bool kFast = decltype(fast)::value;
+    while (bal != 0) {
+      const StageEntry& s = st[__builtin_ctzll(bal)];
+      bal &= bal - 1;
+      const double dx = cxp - s.u, dy = cyp - s.v;
+      const double q = fma(dy, fma(s.c, dy, s.b * (dx + dx)), s.a * dx * dx);
+      if (in && q <= kSupport) {
+        double rho = static_cast<double>(
+            __builtin_amdgcn_exp2f(static_cast<float>(q) * kNegHalfLog2e));
+        if constexpr (!kFast) rho = fmin(rho, s.rmax);
+        const double al = s.sigma * rho;
+        double w = al * t;
+        if constexpr (!kFast) w *= pw;
+        C0 = fma(w, s.c0, C0);
+        C1 = fma(w, s.c1, C1);
+        C2 = fma(w, s.c2, C2);
+        t = fma(-al, t, t);
       }
     }
   };
   for (int base = 0; base < cnt; base += kBlock) {
     __syncthreads();
     const int e = base + static_cast<int>(threadIdx.x);
-    if (e < cnt) stage_entry<false>(a, list, e, m.x0, m.y0, &stage[threadIdx.x]);
-    __syncthreads();
-    const int nl = wave_compact(stage, min(kBlock, cnt - base), bits, wl);
-    __syncthreads();
-    for (int i = 0; i < nl; ++i) {
-      const StageEntry& s = stage[wl[i]];
-      const double dx = cxp - s.u;
-      const double A = s.a * dx * dx, B = s.b2 * dx;
-#pragma unroll
-      for (int j = 0; j < RPL; ++j) {
-        if (RPL > 1 && ((s.mask >> (RPL * m.wave + j)) & 1u) == 0) continue;  // uniform
-        const double dy = (m.py0 + 4 * j + 0.5) - s.v;
-        const double q = fma(dy, fma(s.c, dy, B), A);
-        if (in[j] && q <= kSupport) {
-          const float rho = __builtin_amdgcn_exp2f(static_cast<float>(q) * kNegHalfLog2e);
-          const float al = fminf(s.sigma * rho, kClamp);
-          const double ald = static_cast<double>(al);
-          const double w = ald * t[j] * pw[j];
-          C[j][0] = fma(w, s.c0, C[j][0]);
-          C[j][1] = fma(w, s.c1, C[j][1]);
-          C[j][2] = fma(w, s.c2, C[j][2]);
-          t[j] *= 1.0 - ald;
-        }
-      }
-      if ((i & (kRenormEvery - 1)) == kRenormEvery - 1) renorm();
+    uint32_t mask = 0;
+    if (e < cnt) {
+      int32_t idx;
+      const RenderRec r = stage_entry(a, list, e, &stage[threadIdx.x], &idx);
+      mask = unit_mask<false>(r, m.x0, m.y0);
     }
-    renorm();
+    smask[threadIdx.x] = mask;
+    __syncthreads();
+    for (int g = 0; g < kBlock && base + g < cnt; g += 64) {
+      const uint32_t um = smask[g + lane];
+      const uint64_t bal = __ballot(wave_units<1>(um, m.wave) != 0);
+      if (__any((um & kSlowBit) != 0 || E != 0)) walk(std::false_type{}, bal, stage + g);
+      else walk(std::true_type{}, bal, stage + g);
+      if (t < 0x1p-500) {
+        t *= 0x1p500;
+        E -= kRenorm;
+        pw = ldexp(1.0, E);
+      }
+    }
   }
-#pragma unroll
-  for (int j = 0; j < RPL; ++j) {
-    if (!in[j]) continue;
-    const int64_t pix = static_cast<int64_t>(m.py0 + 4 * j) * a.width + m.px;
-    a.image_out[3 * pix] = static_cast<float>(C[j][0]);
-    a.image_out[3 * pix + 1] = static_cast<float>(C[j][1]);
-    a.image_out[3 * pix + 2] = static_cast<float>(C[j][2]);
-    a.pix_state[2 * pix] = t[j];
-    a.pix_state[2 * pix + 1] = static_cast<double>(E[j]);
+  if (in) {
+    const int64_t pix = m.pixel(0, a.width);
+    a.image_out[3 * pix] = static_cast<float>(C0);
+    a.image_out[3 * pix + 1] = static_cast<float>(C1);
+    a.image_out[3 * pix + 2] = static_cast<float>(C2);
+    a.pix_state[2 * pix] = t;
+    a.pix_state[2 * pix + 1] = static_cast<double>(E);
   }
 }
 
@@ -885,11 +929,30 @@ __global__ __launch_bounds__(256 / RPL) void raster_render_fwd(RasterArgs a) {
 // alpha_i) R_{i+1}, so dC/dalpha_i = T_i (c_i - R_{i+1}): no difference of
 // large sums, whatever the depth. T_i is recovered from the forward's final
 // transmittance, T_i = T_{i+1} / (1 - alpha_i).
+//
+// Only the upstream gradient's product with R enters: P = g . R obeys the same
+// recursion as a scalar per pixel, P_i = g.c_i - (1 - alpha_i) (g.c_i -
+// P_{i+1}), and dL/dalpha_i = T_i (g.c_i - P_{i+1}). All sums are taken in
+// units of the opacity (alpha = sigma rho): with s = T rho dL/dalpha / T,
+// the entry's sums are T rho g (colour / sigma), s (dL/dsigma) and the moments
+// s (a dx + b dy), s (b dx + c dy), s dx^2, s dx dy, s dy^2, which the finish
+// kernel scales by sigma and the constant factors once per primitive. At the
+// clamp rho is rmax and s is 0.
+// Rows per lane of the backward by the number of tiles (1024 SIMDs): with three
+// tiles per SIMD or more, four rows per lane share the per-entry work (3.84 ms
+// against 5.23 at 8160 tiles and 3 M primitives, 496 against 552 us at 3600
+// tiles); below, one row per lane and four wavefronts per tile fill the chip
+// (148 against 158 us at 2553 tiles, 101 against 178 at 920, 19 against 50 at
+// 117).
+constexpr int64_t kBwdRowsTiles = 3072;
+
 template <int RPL, bool GEOM>
-__global__ __launch_bounds__(256 / RPL) void raster_render_bwd(RasterArgs a) {
+__global__ __launch_bounds__(256 / RPL) __attribute__((amdgpu_waves_per_eu(RPL == 4 ? 4 : 6)))
+void raster_render_bwd(RasterArgs a) {
   constexpr int kBlock = 256 / RPL;
   __shared__ StageEntry stage[kBlock];
-  __shared__ int16_t wlist[kBlock / 64][kBlock];
+  __shared__ int32_t sidx[kBlock];
+  __shared__ uint32_t smask[kBlock];
   {
     const RasterStamp st = *a.stamp;  // same for every thread: a uniform exit
     if (st.magic != kStampMagic || st.cap != a.cap || st.tiles_x != a.tiles_x ||
@@ -900,26 +963,23 @@ __global__ __launch_bounds__(256 / RPL) void raster_render_bwd(RasterArgs a) {
   }
   const int64_t tile = blockIdx.x;
   const TileMap<RPL> m = tile_map<RPL>(a, tile);
-  const double cxp = m.px + 0.5;
+  const double cxp = m.px + 0.5, cyp = m.py0 + 0.5;
   const int cnt = __builtin_amdgcn_readfirstlane(min(a.cursor[tile], a.cap));
   const uint64_t* list = a.lists + tile * a.cap;
-  const uint32_t bits = ((1u << RPL) - 1u) << (RPL * m.wave);
-  int16_t* wl = wlist[m.wave];
 
-  double t[RPL], pw[RPL], R[RPL][3];
-  float g[RPL][3];
+  double t[RPL], pw[RPL], P[RPL], g[RPL][3];
   int E[RPL];
   bool in[RPL];
 #pragma unroll
   for (int j = 0; j < RPL; ++j) {
-    in[j] = m.in_x && m.py0 + 4 * j < m.height;
-    R[j][0] = R[j][1] = R[j][2] = 0.0;
+    in[j] = m.in(j);
+    P[j] = 0.0;
     t[j] = 1.0;
     pw[j] = 1.0;
     E[j] = 0;
-    g[j][0] = g[j][1] = g[j][2] = 0.f;
+    g[j][0] = g[j][1] = g[j][2] = 0.0;
     if (in[j]) {
-      const int64_t pix = static_cast<int64_t>(m.py0 + 4 * j) * a.width + m.px;
+      const int64_t pix = m.pixel(j, a.width);
       t[j] = a.pix_state[2 * pix];
       E[j] = static_cast<int>(a.pix_state[2 * pix + 1]);
       pw[j] = ldexp(1.0, E[j]);
@@ -928,97 +988,107 @@ __global__ __launch_bounds__(256 / RPL) void raster_render_bwd(RasterArgs a) {
       g[j][2] = a.grad_image[3 * pix + 2];
     }
   }
-  auto renorm = [&]() {
-#pragma unroll
-    for (int j = 0; j < RPL; ++j) {
-      if (t[j] > 0x1p300 && E[j] < 0) {
-        t[j] *= 0x1p-500;
-        E[j] += kRenorm;
-        pw[j] = ldexp(1.0, E[j]);
-      }
-    }
-  };
   const int lane = static_cast<int>(threadIdx.x & 63);
   const bool writer = GEOM ? lane_writes9(lane) : lane_writes4(lane);
   const int slot = GEOM ? lane_slot9(lane) : lane_slot4(lane);
+  auto entry = [&](auto fast, int k, uint32_t bits) {
+    constexpr bool kFast = decltype(fast)::value;
+    StageEntry s = stage[k];
+    keep(s.v);
+    keep(s.c);
+    keep(s.sigma);
+    keep(s.c0);
+    keep(s.c1);
+    keep(s.c2);
+    const double dx = cxp - s.u;
+    const double A = s.a * dx * dx, B = s.b * (dx + dx);
+    double gc0 = 0.0, gc1 = 0.0, gc2 = 0.0;
+    // a lane's pixels share dx: it sums s, s dy and s dy^2 over them
+    double q0 = 0.0, q1 = 0.0, q2 = 0.0;
+#pragma unroll
+    for (int j = 0; j < RPL; ++j) {
+      if (RPL > 1 && ((bits >> j) & 1u) == 0) continue;  // uniform
+      const double dy = (cyp + 4.0 * j) - s.v;
+      const double q = fma(dy, fma(s.c, dy, B), A);
+      if (in[j] && q <= kSupport) {
+        const double rho = static_cast<double>(
+            __builtin_amdgcn_exp2f(static_cast<float>(q) * kNegHalfLog2e));
+        const double rc = kFast ? rho : fmin(rho, s.rmax);
+        const double om = fma(-s.sigma, rc, 1.0);
+        t[j] *= rcp64(om);  // now T_i = t * pw
+        const double w = rc * (kFast ? t[j] : t[j] * pw[j]);
+        gc0 = fma(w, g[j][0], gc0);
+        gc1 = fma(w, g[j][1], gc1);
+        gc2 = fma(w, g[j][2], gc2);
+        const double gc = fma(g[j][0], s.c0, fma(g[j][1], s.c1, g[j][2] * s.c2));
+        const double d = gc - P[j];
+        P[j] = fma(-om, d, gc);
+        const double sm = kFast || rho < s.rmax ? d * w : 0.0;
+        q0 += sm;
+        if constexpr (GEOM) {
+          const double sy = sm * dy;
+          q1 += sy;
+          q2 = fma(sy, dy, q2);
+        }
+      }
+    }
+    // the entry's totals over the wavefront, one per writing lane
+    float tot;
+    if constexpr (GEOM) {
+      const double qx = dx * q0;
+      const float v[9] = {static_cast<float>(gc0), static_cast<float>(gc1),
+                          static_cast<float>(gc2), static_cast<float>(q0),
+                          static_cast<float>(fma(s.a, qx, s.b * q1)),
+                          static_cast<float>(fma(s.b, qx, s.c * q1)),
+                          static_cast<float>(dx * qx), static_cast<float>(dx * q1),
+                          static_cast<float>(q2)};
+      tot = lane_sums9(v, lane);
+    } else {
+      const float v[4] = {static_cast<float>(gc0), static_cast<float>(gc1),
+                          static_cast<float>(gc2), static_cast<float>(q0)};
+      tot = lane_sums4(v);
+    }
+    if (writer && tot != 0.f)
+      unsafeAtomicAdd(a.grad_acc + kAccStride * static_cast<int64_t>(sidx[k]) + slot,
+                      static_cast<double>(tot));
+  };
   for (int end = cnt; end > 0; end -= kBlock) {
     const int base = max(0, end - kBlock);
     __syncthreads();
     const int e = base + static_cast<int>(threadIdx.x);
-    if (e < end) stage_entry<true>(a, list, e, m.x0, m.y0, &stage[threadIdx.x]);
+    uint32_t mask = 0;
+    if (e < end) {
+      const RenderRec r = stage_entry(a, list, e, &stage[threadIdx.x], &sidx[threadIdx.x]);
+      mask = unit_mask<RPL == 4>(r, m.x0, m.y0);
+    }
+    smask[threadIdx.x] = mask;
     __syncthreads();
-    const int nl = wave_compact(stage, end - base, bits, wl);
-    __syncthreads();
-    for (int i = nl - 1; i >= 0; --i) {
-      const StageEntry& s = stage[wl[i]];
-      const double dx = cxp - s.u;
-      const double A = s.a * dx * dx, B = s.b2 * dx;
-      double gc0 = 0.0, gc1 = 0.0, gc2 = 0.0;
-      float gop = 0.f;
-      // geometry: a lane's pixels share dx, so it sums dL/dq, dL/dq dy and
-      // dL/dq dy^2 over them and forms dL/d(u, v, a, b, c) once per entry
-      double q0 = 0.0, q1 = 0.0, q2 = 0.0;
-      const double nhs = -0.5 * static_cast<double>(s.sigma);  // dalpha/dq = -sigma rho / 2
+    for (int g0 = (end - base - 1) & ~63; g0 >= 0; g0 -= 64) {
+      const uint32_t um = smask[g0 + lane];
+      const uint32_t mine = wave_units<RPL>(um, m.wave);
+      bool scaled = (um & kSlowBit) != 0;
+#pragma unroll
+      for (int j = 0; j < RPL; ++j) scaled = scaled || E[j] != 0;
+      const bool slow = __any(scaled);
+      auto walk = [&](auto fast) {
+        uint64_t bal = __ballot(mine != 0);
+        while (bal != 0) {
+          const int k = 63 - __builtin_clzll(bal);
+          bal &= ~(1ull << k);
+          entry(fast, g0 + k, RPL == 1 ? 1u : __builtin_amdgcn_readlane(mine, k));
+        }
+      };
+      if (slow) walk(std::false_type{});
+      else walk(std::true_type{});
 #pragma unroll
       for (int j = 0; j < RPL; ++j) {
-        if (RPL > 1 && ((s.mask >> (RPL * m.wave + j)) & 1u) == 0) continue;  // uniform
-        const double dy = (m.py0 + 4 * j + 0.5) - s.v;
-        const double q = fma(dy, fma(s.c, dy, B), A);
-        if (in[j] && q <= kSupport) {
-          const float rho = __builtin_amdgcn_exp2f(static_cast<float>(q) * kNegHalfLog2e);
-          const float raw = s.sigma * rho;
-          const float al = fminf(raw, kClamp);
-          const double ald = static_cast<double>(al);
-          const double om = 1.0 - ald;
-          t[j] *= rcp64(om);  // now T_i = t * pw
-          const double T = t[j] * pw[j];
-          const double w = ald * T;
-          gc0 = fma(w, g[j][0], gc0);
-          gc1 = fma(w, g[j][1], gc1);
-          gc2 = fma(w, g[j][2], gc2);
-          // c - R_{i+1} serves both dC/dalpha and R_i = R_{i+1} + alpha (c - R_{i+1})
-          const double d0 = s.c0 - R[j][0], d1 = s.c1 - R[j][1], d2 = s.c2 - R[j][2];
-          if (raw < kClamp) {
-            const double da = fma(g[j][0], d0, fma(g[j][1], d1, g[j][2] * d2));
-            const double gs = da * (T * rho);  // dL/dsigma of this pixel
-            gop += static_cast<float>(gs);
-            if constexpr (GEOM) {
-              const double dq = nhs * gs;  // dL/dq of this pixel
-              const double dqy = dq * dy;
-              q0 += dq;
-              q1 += dqy;
-              q2 = fma(dqy, dy, q2);
-            }
-          }
-          R[j][0] = fma(ald, d0, R[j][0]);
-          R[j][1] = fma(ald, d1, R[j][1]);
-          R[j][2] = fma(ald, d2, R[j][2]);
+        if (t[j] > 0x1p300 && E[j] < 0) {
+          t[j] *= 0x1p-500;
+          E[j] += kRenorm;
+          pw[j] = ldexp(1.0, E[j]);
         }
       }
-      // the entry's totals over the wavefront, one per writing lane
-      float tot;
-      if constexpr (GEOM) {
-        // q = a dx^2 + b2 dx dy + c dy^2, dx = px - u, dy = py - v
-        const double dq0 = dx * q0;
-        const float v[9] = {static_cast<float>(gc0), static_cast<float>(gc1),
-                            static_cast<float>(gc2), gop,
-                            static_cast<float>(-(2.0 * s.a * dq0 + s.b2 * q1)),  // dL/du
-                            static_cast<float>(-(s.b2 * dq0 + 2.0 * s.c * q1)),  // dL/dv
-                            static_cast<float>(dx * dq0),                        // dL/da
-                            static_cast<float>(2.0 * dx * q1),                   // dL/db
-                            static_cast<float>(q2)};                             // dL/dc
-        tot = lane_sums9(v, lane);
-      } else {
-        const float v[4] = {static_cast<float>(gc0), static_cast<float>(gc1),
-                            static_cast<float>(gc2), gop};
-        tot = lane_sums4(v);
-      }
-      if (writer && tot != 0.f)
-        unsafeAtomicAdd(a.grad_acc + kAccStride * static_cast<int64_t>(s.idx) + slot,
-                        static_cast<double>(tot));
-      if ((i & (kRenormEvery - 1)) == 0) renorm();
     }
-    renorm();
   }
 }
 
@@ -1027,6 +1097,12 @@ __global__ void raster_copy_flag(const int32_t* src, int32_t* dst) { *dst = *src
 hipError_t launch_copy_flag(const int32_t* src, int32_t* dst, hipStream_t s) {
   hipLaunchKernelGGL(raster_copy_flag, dim3(1), dim3(1), 0, s, src, dst);
   return hipGetLastError();
+}
+
+template <int RPL, bool GEOM>
+static void launch_bwd(const RasterArgs& a, int64_t n_tiles, hipStream_t s) {
+  hipLaunchKernelGGL((raster_render_bwd<RPL, GEOM>), dim3(static_cast<unsigned>(n_tiles)),
+                     dim3(256 / RPL), 0, s, a);
 }
 
 hipError_t launch_raster(const RasterArgs& a, bool bwd, hipStream_t s) {
@@ -1050,19 +1126,20 @@ hipError_t launch_raster(const RasterArgs& a, bool bwd, hipStream_t s) {
     hipLaunchKernelGGL(raster_sort, dim3(static_cast<unsigned>(n_tiles)), dim3(256), 0, s, a);
     hipLaunchKernelGGL(raster_sort_network, dim3(static_cast<unsigned>(n_tiles)), dim3(256), 0, s,
                        a);
-    hipLaunchKernelGGL(raster_render_fwd<kFwdRows>, dim3(static_cast<unsigned>(n_tiles)),
-                       dim3(256 / kFwdRows), 0, s, a);
+    hipLaunchKernelGGL(raster_render_fwd, dim3(static_cast<unsigned>(n_tiles)), dim3(256), 0, s,
+                       a);
   } else {
     if (a.n == 0) return hipGetLastError();
     const bool geom = a.grad_means != nullptr || a.grad_scales != nullptr || a.grad_rots != nullptr;
     hipLaunchKernelGGL(raster_zero_acc, dim3(gn), dim3(256), 0, s, a.grad_acc, a.n, a.stale);
+    if (n_tiles >= kBwdRowsTiles) {
+      geom ? launch_bwd<4, true>(a, n_tiles, s) : launch_bwd<4, false>(a, n_tiles, s);
+    } else {
+      geom ? launch_bwd<1, true>(a, n_tiles, s) : launch_bwd<1, false>(a, n_tiles, s);
+    }
     if (geom) {
-      hipLaunchKernelGGL((raster_render_bwd<kBwdRows, true>), dim3(static_cast<unsigned>(n_tiles)),
-                         dim3(256 / kBwdRows), 0, s, a);
       hipLaunchKernelGGL(raster_finish_grads<true>, dim3(gn), dim3(256), 0, s, a);
     } else {
-      hipLaunchKernelGGL((raster_render_bwd<kBwdRows, false>), dim3(static_cast<unsigned>(n_tiles)),
-                         dim3(256 / kBwdRows), 0, s, a);
       hipLaunchKernelGGL(raster_finish_grads<false>, dim3(gn), dim3(256), 0, s, a);
     }
   }

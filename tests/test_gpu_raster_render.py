@@ -1,0 +1,78 @@
+"""The compositing render kernels at the sizes where their branches change:
+both lane layouts of the backward (few tiles: four wavefronts a tile; many:
+one), culling of needle-shaped and sub-pixel ellipses against quadrants and
+row bands, opacities on both sides of the alpha clamp, and stacks deep enough
+that the transmittance leaves the range in which its scale factor is skipped.
+Against the FP64 oracle at the compositing bar (scaled error <= 1e-5)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2606_09794_amd as P
+import workloads as W
+from gpu_util import compare
+from oracle import raster_ref as RR
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-5
+WIN = (70, 45)          # the window that holds every primitive
+
+
+def _scene(kind):
+    w, h = WIN
+    rng = np.random.default_rng(sum(map(ord, kind)))
+    if kind == "needles":       # 3 sigma from a hundredth of a pixel to the whole window
+        sc = W.draw_splat_scene(60, 500, w, h, scale=(2e-4, 1.0))
+        sc.scales[:, 2] = sc.scales[:, 0]
+    elif kind == "opacities":
+        sc = W.draw_splat_scene(61, 300, w, h, scale=(0.05, 0.4))
+        sc.opac[:] = rng.choice([0.0, 1e-30, 1e-6, 0.3, 0.98, 0.99, 0.995, 1.0, 3.0, 127.0, 500.0],
+                                sc.n).astype(np.float32)
+    else:                       # "deep": over 200 clamped layers, T below 2^-500
+        sc = W.draw_splat_scene(62, 500, w, h, scale=(1.0, 3.0), depth=(3.0, 6.0), behind=0.0,
+                                opac=(0.9, 1.0))
+    return sc
+
+
+@pytest.mark.parametrize("canvas", [WIN, (896, 896)], ids=["few-tiles", "many-tiles"])
+@pytest.mark.parametrize("kind", ["needles", "opacities", "deep"])
+def test_render_branches(kind, canvas):
+    w, h = WIN
+    sc = _scene(kind)
+    x0, y0 = ((canvas[0] - w) // 2 // 16 * 16, (canvas[1] - h) // 2 // 16 * 16)
+    cam = P.Camera(sc.cam["R"], sc.cam["t"], sc.cam["fx"], sc.cam["fy"], sc.cam["cx"] + x0,
+                   sc.cam["cy"] + y0, *canvas)
+    d = [torch.from_numpy(np.ascontiguousarray(x)).cuda()
+         for x in (sc.means, sc.scales, sc.rots, sc.opac, sc.colors)]
+    g = torch.zeros((canvas[1], canvas[0], 3), device="cuda")
+    g[y0:y0 + h, x0:x0 + w] = torch.from_numpy(sc.grad_image).cuda()
+    img, ws = P.raster_fwd(*d, cam, 1024)
+    out = P.raster_bwd(*d, cam, ws, g, 1024, geometry=True)
+    two = P.raster_bwd(*d, cam, ws, g, 1024)
+    torch.cuda.synchronize()
+    ref, scale = RR.render(sc.means, sc.scales, sc.rots, sc.opac, sc.colors, sc.cam,
+                           grad_image=sc.grad_image, geometry=True)
+    compare(img[y0:y0 + h, x0:x0 + w].cpu().numpy(), ref["image"], scale["image"], "image", TOL)
+    for name, v in zip(("colors", "opac", "means", "scales", "rots"), out):
+        compare(v.cpu().numpy(), ref[name], scale[name], f"grad {name}", TOL)
+    for name, v in zip(("colors", "opac"), two):
+        compare(v.cpu().numpy(), ref[name], scale[name], f"grad {name} alone", TOL)
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_unbounded_opacity_composites_at_the_clamp(value):
+    """An infinite opacity, or a NaN (which the clamp's minimum drops), acts as
+    any opacity that is clamped on its whole support."""
+    sc = _scene("opacities")
+    res = []
+    for v in (value, 500.0):
+        op = np.where(sc.opac == 500.0, np.float32(v), sc.opac)
+        d = [torch.from_numpy(np.ascontiguousarray(x)).cuda()
+             for x in (sc.means, sc.scales, sc.rots, op, sc.colors)]
+        cam = P.Camera(sc.cam["R"], sc.cam["t"], sc.cam["fx"], sc.cam["fy"], sc.cam["cx"],
+                       sc.cam["cy"], *WIN)
+        img, ws = P.raster_fwd(*d, cam, 1024)
+        res.append((img, *P.raster_bwd(*d, cam, ws, torch.from_numpy(sc.grad_image).cuda(), 1024)))
+    assert torch.equal(res[0][0], res[1][0])
+    for x, y in zip(res[0][1:], res[1][1:]):
+        assert torch.allclose(x, y, rtol=1e-6, atol=1e-9)
