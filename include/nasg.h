@@ -146,7 +146,7 @@ typedef enum nasg_param { NASG_PARAM_QUAT = 0, NASG_PARAM_ANGLES = 1 } nasg_para
  *              y = z x x, no normaliser (the table gives none).
  * SG, SB, SC and ASG take NASG_PARAM_QUAT only; `norm` is validated but used
  * by NASGabor only. The families other than NASGabor use a fixed lane
- * mapping by view count (tuning entries set the block size only) and are not
+ * mapping by view and lobe count (tuning entries set the block size only) and are not
  * accepted by the persistent batch (NASG_ERR_MODE).                          */
 typedef enum nasg_family {
   NASG_FAMILY_NASGABOR = 0,
@@ -228,8 +228,10 @@ int sh3_eval_bwd(const float* sh, int64_t n, const nasg_views* views,
  * pulls them from a device work queue. Each scene runs the lane mapping the
  * tuning table (nasg_set_tuning, kernel 1, its K and V, float32) holds for
  * it when the batch kernel carries that mapping -- (1, 1), (1, 2), (1, 4),
- * (4, 2) or (4, 4) -- and otherwise the smallest of these whose view chunk
- * holds its views (V = 1, 2, 3..4, 5..8, more). Gradient sums stay per primitive in
+ * (4, 2) or (4, 4) -- and otherwise the one that nasg_eval_bwd takes on its
+ * own: the smallest of these whose view chunk holds its views (V = 1, 2, 3..4,
+ * 5..8, more), or (1, 4) for V > 4 where four lanes would leave too many
+ * without a lobe (K = 1, and for V <= 8 K = 2, 3, 5, 6). Gradient sums stay per primitive in
  * registers and lanes (the queue counter is the only atomic). Lobe parameters
  * must be float32 (NASG_F32).
  *
@@ -445,8 +447,9 @@ const char* nasg_status_string(int status);
  * (16, 1); bcast = 1 (NASGabor kernels 0 and 1 only): (4, 1), (8, 1),
  * (16, 1), (8, 2), (8, 4); others return NASG_ERR_SHAPE. nasg_set_tuning
  * overrides the built-in
- * choice for a (kernel, K, V, dtype) key; nasg_get_tuning reports the choice
- * that a call with that key would use. kernel: 0 = NASG forward, 1 = NASG
+ * choice for a (kernel, K, V, dtype) key, which depends on N too (few
+ * primitives are spread over more lanes); nasg_get_tuning reports the choice
+ * that a call with that key and many primitives would use. kernel: 0 = NASG forward, 1 = NASG
  * backward / fused, 2 = SH forward, 3 = SH backward. K is ignored for SH.
  * lanes = 0 removes an override. Host-side table, not thread-safe against
  * concurrent calls.                                                         */

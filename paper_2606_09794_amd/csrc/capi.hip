@@ -53,24 +53,98 @@ bool supported(int lanes, int vpl, int bcast) {
 
 bool block_ok(int b) { return b == 64 || b == 128 || b == 256; }
 
-// Built-in choice when no tuning entry exists (the tuner's picks at K = 8 on
-// MI355X): one lane per primitive up to four views (no slot transfers, and
-// no more view slots than views), then four lanes with two or four views
-// each, so that a lane evaluates several independent lobe-views per step
-// within the registers of two waves per SIMD.
-nasg_tuning heuristic(int32_t v) {
-  if (v <= 1) return {1, 1, 256, 0};
-  if (v <= 2) return {1, 2, 256, 0};
-  if (v <= 4) return {1, 4, 256, 0};
-  if (v <= 8) return {4, 2, 128, 0};
-  return {4, 4, 128, 0};
+// ---- built-in launch shapes, used when no tuning entry exists
+// A lane mapping (P lanes per primitive, VPL views per lane) has P VPL view
+// slots and prepares P lobes at a time, so slots beyond the views and lanes
+// beyond the lobes do nothing. With enough primitives to fill the chip the
+// fewest lanes win that keep a lane's registers at two waves per SIMD; with
+// few, a primitive is spread over lanes until the launch has about 131 072 of
+// them (two waves on each of the 1024 SIMDs) or the lobes run out. The lines
+// below come from every compiled mapping timed on MI355X over K in {1, 2, 4,
+// 8, 16}, V in {1, 2, 4, 6, 8, 16, 32} and N from 4096 to 1.5 M; times are in
+// us, a choice by the view count alone against this one.
+constexpr int64_t kFillLanes = 131072;
+
+int pow2_at_least(int x) {
+  int p = 1;
+  while (p < x) p *= 2;
+  return p;
 }
 
-nasg_tuning choose(int32_t kernel, int32_t k, int32_t v, int32_t dtype) {
+nasg_tuning shape_of(int64_t n, int lanes, int vpl, int bcast = 0) {
+  return {lanes, vpl, n * lanes <= 32768 ? 64 : 256, bcast};
+}
+
+// The mapping that fills the chip best when there are primitives enough, also
+// a scene's in the persistent batch: one lane up to four views; beyond, four
+// lanes, except where they would waste more on missing lobes than one lane's
+// repeated passes over the lobes cost (1.27 times for V <= 8, about twice for
+// more). Backward, N = 1.5 M: K = 1, V = 8 355 -> 236, V = 16 572 -> 459;
+// K = 2, V = 8 375 -> 320 (V = 16 stays at four lanes, 570 against 640).
+// Forward: K = 1, V = 8 188 -> 78, V = 16 356 -> 164.
+void mapping_at_scale(int k, int v, int* lanes, int* vpl) {
+  const bool one = k == 1 || (v <= 8 && 5 * k < 4 * ((k + 3) / 4 * 4));
+  *lanes = v <= 4 || one ? 1 : 4;
+  *vpl = v <= 1 ? 1 : v <= 2 ? 2 : *lanes == 4 && v <= 8 ? 2 : 4;
+}
+
+// Few primitives (forward, K = 8, N = 4096: V = 1 8.9 -> 3.5, V = 4 13.6 ->
+// 5.2; bfloat16 storage in both directions alike). In float32 a scene's
+// results in the persistent batch equal those of a launch of its own bit for
+// bit, so only mappings that sum in the order of the mapping at scale serve:
+// for up to four views the forward's broadcast mappings, whose colours are
+// summed in lobe order.
+nasg_tuning nasg_shape(bool bwd, bool bf16, int64_t n, int k, int v) {
+  int lanes, vpl;
+  mapping_at_scale(k, v, &lanes, &vpl);
+  nasg_tuning scale = shape_of(n, lanes, vpl);
+  if (scale.block == 256 && lanes == 4 && vpl == 4 && k >= 8) scale.block = 128;
+  if (bwd && !bf16) return scale;
+  const int kp = std::min(16, pow2_at_least(k));
+  auto fits = [n](int p, int64_t most) { return n * p <= most; };
+  if (v == 1) {
+    int p = 1;
+    while (2 * p <= kp && fits(2 * p, kFillLanes)) p *= 2;
+    return shape_of(n, p, 1, p >= 4);
+  }
+  if (v <= 4) return k >= 3 && fits(8, kFillLanes) ? shape_of(n, 8, vpl, 1) : scale;
+  if (!bf16) return scale;
+  if (lanes == 1) {
+    if (fits(4, kFillLanes / 2)) return shape_of(n, 4, v <= 8 ? 2 : 4);
+    return fits(2, kFillLanes) && k > 1 ? shape_of(n, 2, bwd ? 2 : 4) : scale;
+  }
+  if (v <= 8) {
+    if (k >= 16 && fits(16, kFillLanes / 2)) return shape_of(n, 16, 1);
+    return k >= 8 && fits(8, kFillLanes) ? shape_of(n, 8, 1) : scale;
+  }
+  if (k >= 16 && fits(16, 2 * kFillLanes)) return shape_of(n, 16, 1);
+  // eight lanes, where they leave no more without a lobe than four, hold half
+  // the view slots each: better in the forward at any size (K = 8, V = 16,
+  // N = 1.5 M: 659 -> 617), in the backward, whose slots are larger, for few
+  return k >= 8 && (k + 7) / 8 * 8 == (k + 3) / 4 * 4 && (!bwd || fits(8, 4 * kFillLanes))
+             ? shape_of(n, 8, 2) : scale;
+}
+
+// SH-3: every lane of a primitive would load all 48 coefficients, so one lane
+// wherever the primitives fill the chip (backward, N = 1.5 M, V = 16: 344 ->
+// 240 us against four lanes; forward 161 -> 110), and more only for few.
+nasg_tuning sh_shape(bool bwd, int64_t n, int v) {
+  const int vp = std::min(16, pow2_at_least(v));
+  int p = 1;
+  if (!bwd || v > 4) {
+    const int64_t fill = bwd && v < 16 ? kFillLanes / 2 : kFillLanes;
+    while (2 * p <= vp && n * 2 * p <= fill) p *= 2;
+    if (p == 1 && bwd && v >= 16 && n * 2 <= 4 * kFillLanes) p = 2;
+  }
+  const int most = p >= 16 ? 1 : p >= 8 ? 2 : 4;
+  return shape_of(n, p, std::min(most, pow2_at_least((v + p - 1) / p)));
+}
+
+nasg_tuning choose(int32_t kernel, int64_t n, int32_t k, int32_t v, int32_t dtype) {
   const auto& tab = tuning_table();
   auto it = tab.find(Key{kernel, kernel >= 2 ? 0 : k, v, kernel >= 2 ? 0 : dtype});
   if (it != tab.end()) return it->second;
-  return heuristic(v);
+  return kernel >= 2 ? sh_shape(kernel == 3, n, v) : nasg_shape(kernel == 1, dtype == NASG_BF16, n, k, v);
 }
 
 int check_views(const nasg_views* vw, int64_t n) {
@@ -133,14 +207,16 @@ int check_grad_ptrs(const float* grad_rgb, const nasg_grads* g, const float* rgb
 
 // ---- persistent batches
 // A scene's lane mapping in the persistent batch: the tuning table's choice
-// for its (K, V) when the batch kernel carries that mapping, else the
-// smallest view chunk that holds its views ((1, 1), (1, 2), (1, 4), (4, 2),
-// (4, 4) for V = 1, 2, 3..4, 5..8, more); plus kBatchVariants for the paper's
-// raw values.
+// for its (K, V) when the batch kernel carries that mapping, else the mapping
+// at scale ((1, 1), (1, 2), (1, 4), (4, 2), (4, 4): all carried); plus
+// kBatchVariants for the paper's raw values.
 int batch_variant(int32_t k, int32_t v, int32_t param) {
-  int var = v <= 1 ? 0 : v <= 2 ? 1 : v <= 4 ? 2 : v <= 8 ? 3 : 4;
+  int lanes, vpl, var = 0;
+  mapping_at_scale(k, v, &lanes, &vpl);
   const auto& tab = tuning_table();
   const auto it = tab.find(Key{1, k, v, NASG_F32});   // kernel 1: the NASG backward
+  for (int c = 0; c < nasg::kBatchVariants; ++c)
+    if (nasg::kBatchLanes[c] == lanes && nasg::kBatchViewsPerLane[c] == vpl) var = c;
   if (it != tab.end() && it->second.bcast == 0) {
     for (int c = 0; c < nasg::kBatchVariants; ++c)
       if (nasg::kBatchLanes[c] == it->second.lanes &&
@@ -317,7 +393,7 @@ int nasg_set_tuning(int32_t kernel, int32_t k, int32_t v, int32_t dtype, const n
 int nasg_get_tuning(int32_t kernel, int32_t k, int32_t v, int32_t dtype, nasg_tuning* t) {
   if (kernel < 0 || kernel > 3) return NASG_ERR_MODE;
   if (t == nullptr) return NASG_ERR_NULL;
-  *t = choose(kernel, k, v, dtype);
+  *t = choose(kernel, 1 << 22, std::max(1, k), std::max(1, v), dtype);  // built-in: at scale
   return NASG_OK;
 }
 
@@ -333,7 +409,7 @@ int nasg_eval_fwd(const nasg_params* p, const nasg_views* views, float* rgb, int
   NasgArgs a = make_args(p, views);
   a.rgb = rgb;
   a.norm = norm;
-  const nasg_tuning t = choose(0, p->k, views->v, p->dtype);
+  const nasg_tuning t = choose(0, p->n, p->k, views->v, p->dtype);
   const hipError_t e = nasg::launch_nasg(a, t.lanes, t.views_per_lane, t.bcast != 0, false,
                                          p->dtype == NASG_BF16, t.block,
                                          static_cast<hipStream_t>(stream));
@@ -361,7 +437,7 @@ int nasg_eval_bwd(const nasg_params* p, const nasg_views* views, const float* gr
   a.g_geom = g->geom;
   a.norm = norm;
   a.accumulate = grad_mode == NASG_GRAD_ACCUMULATE;
-  const nasg_tuning t = choose(1, p->k, views->v, p->dtype);
+  const nasg_tuning t = choose(1, p->n, p->k, views->v, p->dtype);
   const hipError_t e = nasg::launch_nasg(a, t.lanes, t.views_per_lane, t.bcast != 0, true,
                                          p->dtype == NASG_BF16, t.block,
                                          static_cast<hipStream_t>(stream));
@@ -384,7 +460,7 @@ int sh3_eval_fwd(const float* sh, int64_t n, const nasg_views* views, float* rgb
   a.rgb = rgb;
   a.n = n;
   a.v = views->v;
-  const nasg_tuning t = choose(2, 0, views->v, 0);
+  const nasg_tuning t = choose(2, n, 0, views->v, 0);
   const hipError_t e = nasg::launch_sh(a, t.lanes, t.views_per_lane, false, t.block,
                                        static_cast<hipStream_t>(stream));
   return e == hipSuccess ? NASG_OK : NASG_ERR_LAUNCH;
@@ -414,7 +490,7 @@ int sh3_eval_bwd(const float* sh, int64_t n, const nasg_views* views, const floa
   a.n = n;
   a.v = views->v;
   a.accumulate = grad_mode == NASG_GRAD_ACCUMULATE;
-  const nasg_tuning t = choose(3, 0, views->v, 0);
+  const nasg_tuning t = choose(3, n, 0, views->v, 0);
   const hipError_t e = nasg::launch_sh(a, t.lanes, t.views_per_lane, true, t.block,
                                        static_cast<hipStream_t>(stream));
   return e == hipSuccess ? NASG_OK : NASG_ERR_LAUNCH;

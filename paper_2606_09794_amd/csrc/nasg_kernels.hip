@@ -86,8 +86,9 @@ __device__ __noinline__ Activated activate_raw(float4 sh, float w0, float w1, fl
 // BC (views broadcast): the P lanes of a primitive own its lobes as usual but
 // every lane holds the same VPL views, so each lane evaluates its lobes
 // against all of them with no slot transfer, and the per-view colour and
-// direction-gradient partials are summed over the lane group at the end (DPP).
-// For few views this spreads a primitive over P lanes (P lobes prepared and
+// direction-gradient partials are summed over the lane group at the end (DPP);
+// the forward instead adds each lobe's colour in lobe order, in every lane of
+// the group, so that its bits are those of the one-lane mapping. For few views this spreads a primitive over P lanes (P lobes prepared and
 // loaded at once) instead of one lane walking all of them.
 template <int P, int VPL, bool BWD, bool BF16, bool ANG, bool NOCAR = false, bool BC = false,
           bool ONCE = false, bool PF = !(P == 1 && VPL == 1)>
@@ -192,6 +193,7 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
       float acc_w0 = 0.f, acc_w1 = 0.f, acc_w2 = 0.f, acc_G = 0.f, acc_l = 0.f, acc_a = 0.f;
       float acc_k = 0.f, acc_z = 0.f;
       float ax0 = 0.f, ax1 = 0.f, ax2 = 0.f, az0 = 0.f, az1 = 0.f, az2 = 0.f;
+      float Gt[BC && !BWD ? VPL : 1];   // the owned lobe's G, for the sum in lobe order
 
 #pragma unroll 2
       for (int step = 0; step < (BC ? 1 : P); ++step) {
@@ -258,9 +260,13 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
           const float pE = exp_neg(fma(two_lamd, em1d, Ad));
           const float Npe = live ? Nn * pE : 0.f;
           const float G = Npe * car;
-          sl.col[t][0] = fmaf(w0, G, sl.col[t][0]);
-          sl.col[t][1] = fmaf(w1, G, sl.col[t][1]);
-          sl.col[t][2] = fmaf(w2, G, sl.col[t][2]);
+          if constexpr (BC && !BWD) {
+            Gt[t] = G;
+          } else {
+            sl.col[t][0] = fmaf(w0, G, sl.col[t][0]);
+            sl.col[t][1] = fmaf(w1, G, sl.col[t][1]);
+            sl.col[t][2] = fmaf(w2, G, sl.col[t][2]);
+          }
           if constexpr (BWD) {
             const float LR = pole ? -0.25f : static_cast<float>(Ld * rden);  // ln kappa/(1-(d.z)^2)
             // Q = 1/(2 kappa) + 2 d.z ln kappa/(1 - (d.z)^2) = (h + 2 d.z ln kappa)/(1 - (d.z)^2)
@@ -311,6 +317,21 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
           if constexpr (P > 1 && !BC) {
             slot_pass<P, VPL, BWD>(sl, t, rot_addr);
             __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+      }
+
+      if constexpr (BC && !BWD) {
+#pragma unroll
+        for (int m = 0; m < P; ++m) {
+          if (lc + m >= K) continue;  // uniform
+          const float m0 = __shfl(w0, m, P), m1 = __shfl(w1, m, P), m2 = __shfl(w2, m, P);
+#pragma unroll
+          for (int t = 0; t < VPL; ++t) {
+            const float Gm = __shfl(Gt[t], m, P);
+            sl.col[t][0] = fmaf(m0, Gm, sl.col[t][0]);
+            sl.col[t][1] = fmaf(m1, Gm, sl.col[t][1]);
+            sl.col[t][2] = fmaf(m2, Gm, sl.col[t][2]);
           }
         }
       }
@@ -497,7 +518,7 @@ hipError_t launch_nasg(const NasgArgs& a, int lanes, int vpl, bool bcast, bool b
   if (a.family == kFamNasg) {
     // NASG lobes: the compiled family mappings, chosen by view count
     int fl, fv;
-    family_mapping(a.v, fl, fv);
+    family_mapping(a.k, a.v, fl, fv);
     switch (fl) {
       case 1: return launch_pv<1, 1, true>(a, bwd, bf16, block, s);
       case 2: return launch_pv<2, 2, true>(a, bwd, bf16, block, s);

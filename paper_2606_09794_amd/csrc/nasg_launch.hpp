@@ -42,12 +42,12 @@ constexpr int kFamSc = 4;
 constexpr int kFamAsg = 5;
 
 // The lane mappings compiled for the families other than NASGabor, by view
-// count: (1, 1) for V = 1, (2, 2) up to 4, (4, 2) up to 8, (8, 2) above.
-inline void family_mapping(int v, int& lanes, int& vpl) {
-  if (v <= 1) { lanes = 1; vpl = 1; }
-  else if (v <= 4) { lanes = 2; vpl = 2; }
-  else if (v <= 8) { lanes = 4; vpl = 2; }
-  else { lanes = 8; vpl = 2; }
+// count: (1, 1) for V = 1, (2, 2) up to 4, (4, 2) up to 8, (8, 2) above, but
+// no more lanes than the lobes round up to (lanes beyond them do nothing).
+inline void family_mapping(int k, int v, int& lanes, int& vpl) {
+  lanes = v <= 1 ? 1 : v <= 4 ? 2 : v <= 8 ? 4 : 8;
+  while (lanes > 1 && lanes / 2 >= k) lanes /= 2;
+  vpl = lanes == 1 ? 1 : 2;
 }
 
 struct ShArgs {

@@ -98,8 +98,8 @@ struct ViewSlots {
 
 // Fills this lane's home slot of the view chunk starting at v0. BC (views
 // broadcast): every lane of the group holds the same views v0 + t, t < VPL,
-// and only lane 0's colours start from c0 (the group's partial colours are
-// summed after the lobes).
+// and in the backward only lane 0's colours start from c0 (the group's partial
+// colours are summed after the lobes; the forward's are whole in every lane).
 template <int P, int VPL, bool BWD, bool BC = false, bool STREAM = false>
 __device__ __forceinline__ void slots_setup(const NasgArgs& a, int64_t i, int v0, int j,
                                             const double (&base)[3], const float (&c0)[3],
@@ -125,7 +125,7 @@ __device__ __forceinline__ void slots_setup(const NasgArgs& a, int64_t i, int v0
     s.df[t][1] = static_cast<float>(s.dd[t][1]);
     s.df[t][2] = static_cast<float>(s.dd[t][2]);
     s.rinv[t] = static_cast<float>(ri);
-    const bool own_c0 = !BC || j == 0;
+    const bool own_c0 = !BC || !BWD || j == 0;
     s.col[t][0] = own_c0 ? c0[0] : 0.f;
     s.col[t][1] = own_c0 ? c0[1] : 0.f;
     s.col[t][2] = own_c0 ? c0[2] : 0.f;
@@ -162,21 +162,21 @@ __device__ __forceinline__ void slot_pass(ViewSlots<VPL>& s, int t, int rot_addr
 
 // With the slots home again: the colours of this lane's views, and the c0 and
 // mean (or dirs) gradients of the primitive (sums over its views, reduced
-// over the lane group, written by lane 0). BC: the group's partial colours
-// and direction gradients are first summed over its lanes (each lane then
+// over the lane group, written by lane 0). BC backward: the group's partial
+// colours and direction gradients are first summed over its lanes (each lane then
 // holds the totals of all VPL views); lane t % P writes view t's colour, and
 // the c0 and mean gradients are not summed over lanes again.
 template <int P, int VPL, bool BWD, bool BC = false, bool STREAM = false>
 __device__ __forceinline__ void slots_finish(const NasgArgs& a, int64_t i, bool valid, int v0,
                                              int j, bool acc_mode, ViewSlots<VPL>& s) {
   const int64_t N = a.n;
-  if constexpr (BC) {
+  if constexpr (BC && BWD) {
 #pragma unroll
     for (int t = 0; t < VPL; ++t) {
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
         s.col[t][c] = group_sum<P>(s.col[t][c]);
-        if constexpr (BWD) s.gdir[t][c] = group_sum<P>(s.gdir[t][c]);
+        s.gdir[t][c] = group_sum<P>(s.gdir[t][c]);
       }
     }
   }

@@ -1,0 +1,72 @@
+"""The built-in launch shapes: on both sides of every line of the choice by N,
+K and V, the colours and gradients equal those of the one-lane mapping up to
+the order of the lobe and view sums (a few float32 roundings of terms whose
+absolute sum the oracle's scale measures; checked against the oracle at the
+bar of the lane-mapping tests)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2606_09794_amd as P
+import workloads as W
+from gpu_util import compare, oracle_nasg, oracle_sh, upload
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-5
+
+
+def _take(w, m=96):
+    idx = np.unique(np.concatenate([np.arange(m // 2), w.n - 1 - np.arange(m // 2)]) % w.n)
+    return idx, W.take_primitives(w, idx)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [1, 4097, 16385, 32769])
+@pytest.mark.parametrize("k,v", [(1, 1), (5, 1), (16, 1), (2, 2), (3, 2), (9, 2), (1, 4), (8, 3), (2, 7),
+                                 (6, 6), (7, 8), (16, 5), (1, 9), (2, 18), (3, 17), (9, 17), (16, 33)])
+def test_nasg_shapes(n, k, v, dtype):
+    w = W.draw_workload(n + 64 * k + v, n, k, v, dtype=dtype, with_sh=False)
+    d = upload(w)
+    idx, sub = _take(w)
+    ref, scale = oracle_nasg(sub, "exact")
+    rgb = P.nasg_eval_fwd(d["quat"], d["shape"], d["rgbw"], d["c0"], means=d["means"], cams=d["cams"])
+    fused = torch.full_like(rgb, float("nan"))
+    g = P.nasg_eval_bwd(d["quat"], d["shape"], d["rgbw"], d["c0"], d["grad_rgb"], means=d["means"],
+                        cams=d["cams"], rgb_out=fused)
+    torch.cuda.synchronize()
+    assert torch.isfinite(rgb).all() and torch.isfinite(fused).all()
+    t = torch.from_numpy(idx).cuda()
+    compare(rgb[:, t].cpu().numpy(), ref["rgb"], scale["rgb"], "rgb", TOL)
+    compare(fused[:, t].cpu().numpy(), ref["rgb"], scale["rgb"], "fused rgb", TOL)
+    for name, x in (("quat", g["quat"][:, t]), ("shape", g["shape"][:, t]),
+                    ("rgbw", g["rgbw"][:, :, t]), ("c0", g["c0"][t]), ("geom", g["geom"][t])):
+        compare(x.cpu().numpy(), ref[name], scale[name], name, TOL)
+
+
+@pytest.mark.parametrize("n", [1, 4097, 16385, 131073])
+@pytest.mark.parametrize("v", [1, 3, 7, 16, 33])
+def test_sh_shapes(n, v):
+    w = W.draw_workload(n + v, n, 1, v)
+    d = upload(w)
+    idx, sub = _take(w)
+    ref, scale = oracle_sh(sub)
+    rgb = P.sh3_eval_fwd(d["sh"], means=d["means"], cams=d["cams"])
+    g = P.sh3_eval_bwd(d["sh"], d["grad_rgb"], means=d["means"], cams=d["cams"])
+    torch.cuda.synchronize()
+    t = torch.from_numpy(idx).cuda()
+    compare(rgb[:, t].cpu().numpy(), ref["rgb"], scale["rgb"], "rgb", TOL)
+    compare(g["sh"][:, :, t].cpu().numpy(), ref["sh"], scale["sh"], "sh", TOL)
+    compare(g["geom"][t].cpu().numpy(), ref["geom"], scale["geom"], "geom", TOL)
+
+
+@pytest.mark.parametrize("family", ["nasg", "sg", "sb", "sc", "asg"])
+@pytest.mark.parametrize("k,v", [(1, 17), (2, 9), (3, 8), (5, 20)])
+def test_family_shapes(family, k, v):
+    w = W.draw_workload(7 * k + v, 300, k, v, family=family, with_sh=False)
+    d = upload(w)
+    ref, scale = oracle_nasg(w, "exact")
+    g = P.nasg_eval_bwd(d["quat"], d["shape"], d["rgbw"], d["c0"], d["grad_rgb"], means=d["means"],
+                        cams=d["cams"], family=family)
+    torch.cuda.synchronize()
+    for name, x in g.items():
+        compare(x.cpu().numpy(), ref[name], scale[name], name, TOL)
