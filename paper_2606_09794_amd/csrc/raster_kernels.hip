@@ -15,7 +15,8 @@
 // Pipeline (all on the caller's stream, nothing allocated, no host sync):
 //   project : per primitive, FP64 pixel mean, inverse 2D covariance, depth and
 //             the 16 x 16-pixel tiles its ellipse's bounding box touches, kept
-//             with the colour and opacity in a 64-byte render record;
+//             with the colour and opacity in a 64-byte render record; the same
+//             launch clears the tile cursors;
 //   bin     : each primitive's 64-bit depth key (float depth bits, index)
 //             goes to the lists of those tiles (a cursor per tile, fixed
 //             capacity per tile; entries beyond it are dropped and flagged);
@@ -23,12 +24,11 @@
 //             atomic per touched tile;
 //   sort    : per tile, the list is sorted by (depth, primitive index), which
 //             fixes the compositing order: a bucket sort on the depth bits in
-//             LDS, or a bitonic network on the 64-bit keys for small tiles
-//             and for tiles whose depths crowd into few buckets;
-//   render  : one block per tile, each lane one or more pixels of one column
-//             (they share the entry's dx terms), front to back over the list
-//             in chunks staged through LDS; an entry's q <= 9 box decides per
-//             row band whether a wavefront looks at it at all. The support
+//             LDS, a count of the smaller keys for short lists, or a bitonic
+//             network on the 64-bit keys where depths crowd into few buckets;
+//   render  : one block per tile, front to back over the list in chunks staged
+//             through LDS; where the entry's q <= 9 ellipse reaches decides
+//             which wavefronts look at it at all. The support
 //             test and the quadratic form are FP64 (so both sides of a
 //             parity check take the same support decisions), rho = exp(-q/2)
 //             is FP32, and the transmittance (with an explicit power-of-two
@@ -36,21 +36,22 @@
 //             termination a pixel may composite thousands of layers;
 //   backward: back to front over the same list, with dC/dc_i = alpha_i T_i
 //             and dC/dalpha_i = T_i (c_i - R_{i+1}), R the colour seen from
-//             the next layer on in units of its transmittance, built by a
-//             convex-combination recursion (no cancellation at any depth),
-//             and T_i recovered from the forward's final transmittance. Per
-//             primitive, a lane sums its pixels' terms, the wavefront
-//             totals them over its lanes by halving exchanges, and the lanes
-//             holding the totals add them to FP64 per-primitive accumulators
-//             with one atomic instruction. With
-//             geometry gradients the same pass also sums dL/d(u, v, a, b, c)
-//             (dL/dq = -sigma rho / 2 times the pixel's dL/dalpha);
+//             the next layer on in units of its transmittance, built (as its
+//             product with the upstream gradient) by a convex-combination
+//             recursion (no cancellation at any depth), and T_i recovered from
+//             the forward's final transmittance. Per primitive, a lane sums
+//             its pixels' terms, the wavefront totals them over its lanes by
+//             halving exchanges, and the lanes holding the totals add them to
+//             FP64 per-primitive accumulators with one atomic instruction. With
+//             geometry gradients the same pass also sums the moments that
+//             dL/d(u, v, a, b, c) are made of;
 //   finish  : per primitive, the accumulators rounded to the float32
 //             outputs and, with geometry gradients, the FP64 chain from
 //             dL/d(u, v, a, b, c) through the projection to the mean, scales
 //             and quaternion.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "../../include/nasg.h"
@@ -64,7 +65,7 @@ constexpr double kClamp = 0.99;
 constexpr double kSupport = 9.0;
 constexpr int kBinParts = 8;  // most tile classes of the binning pass
 constexpr int kBinLdsTiles = 8192;      // class tiles one LDS-counting block holds
-constexpr int kBinPrimsPerThread = 32;  // primitives per thread of an LDS-counting block
+constexpr int kBinThreads = 1024;       // of an LDS-counting block
 
 // A primitive reaches a pixel with rho >= e^{-9/2} = 0.0111, so an opacity
 // above 0.99 / 0.0111 = 89.2 is clamped on its whole support: any larger one
@@ -74,8 +75,9 @@ __device__ inline double opacity(float sigma) {
   return static_cast<double>(fminf(sigma, kSigmaMax));
 }
 
-__global__ void raster_begin(RasterArgs a) {
-  const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+// Every thread of the grid (which covers the tiles and the primitives): the
+// tile cursors, the overflow flag and the forward's stamp.
+__device__ inline void begin_frame(const RasterArgs& a, int64_t t) {
   if (t < static_cast<int64_t>(a.tiles_x) * a.tiles_y) a.cursor[t] = 0;
   if (t == 0) {
     *a.overflow = 0;
@@ -214,6 +216,7 @@ __global__ void raster_finish_grads(RasterArgs a) {
 
 __global__ void raster_project(RasterArgs a) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  begin_frame(a, i);
   if (i >= a.n) return;
   RenderRec rec{};
   BinRec bin{};
@@ -321,27 +324,27 @@ __device__ inline void for_class_tiles(const BinRec& r, int64_t tiles_x, int par
 // range in its list with one device atomic on the tile's cursor, then places
 // the keys in those ranges with LDS atomics: one device atomic per (block,
 // tile) instead of one per entry.
-__global__ __launch_bounds__(256) void raster_bin_lds(RasterArgs a, int pshift) {
-  __shared__ int cnt[kBinLdsTiles];
+__global__ __launch_bounds__(kBinThreads) void raster_bin_lds(RasterArgs a, int pshift, int chunk) {
+  extern __shared__ int cnt[];
   const int parts = 1 << pshift;
   const int part = static_cast<int>(blockIdx.x & (parts - 1));
-  const int64_t first = static_cast<int64_t>(blockIdx.x >> pshift) * (256 * kBinPrimsPerThread);
-  const int64_t last = min(first + 256 * kBinPrimsPerThread, a.n);
+  const int64_t first = static_cast<int64_t>(blockIdx.x >> pshift) * chunk;
+  const int64_t last = min(first + chunk, a.n);
   const int64_t n_tiles = static_cast<int64_t>(a.tiles_x) * a.tiles_y;
   const int n_local = static_cast<int>((n_tiles - part + parts - 1) >> pshift);
-  for (int m = threadIdx.x; m < n_local; m += 256) cnt[m] = 0;
+  for (int m = threadIdx.x; m < n_local; m += kBinThreads) cnt[m] = 0;
   __syncthreads();
-  for (int64_t i = first + threadIdx.x; i < last; i += 256) {
+  for (int64_t i = first + threadIdx.x; i < last; i += kBinThreads) {
     const BinRec r = a.bins[i];
     for_class_tiles(r, a.tiles_x, part, parts, [&](int64_t t) { atomicAdd(&cnt[t >> pshift], 1); });
   }
   __syncthreads();
-  for (int m = threadIdx.x; m < n_local; m += 256) {
+  for (int m = threadIdx.x; m < n_local; m += kBinThreads) {
     const int c = cnt[m];
     if (c > 0) cnt[m] = atomicAdd(a.cursor + (static_cast<int64_t>(m) << pshift) + part, c);
   }
   __syncthreads();
-  for (int64_t i = first + threadIdx.x; i < last; i += 256) {
+  for (int64_t i = first + threadIdx.x; i < last; i += kBinThreads) {
     const BinRec r = a.bins[i];
     const uint64_t key = depth_key(r.z, i);
     for_class_tiles(r, a.tiles_x, part, parts, [&](int64_t t) {
@@ -456,10 +459,11 @@ __device__ void bitonic_keys(uint64_t (&v)[EPT], uint64_t* lds) {
 // Runs of equal float depth (in index order on entry): a stable insertion
 // sort by FP64 depth, done by the thread that owns the run's first entry;
 // then the sorted keys go back to the tile's list.
+template <int T>
 __device__ void order_runs_and_store(const RasterArgs& a, uint64_t* list, int cnt,
                                      uint64_t* lds) {
   const int t = static_cast<int>(threadIdx.x);
-  for (int e = t; e < cnt; e += 256) {
+  for (int e = t; e < cnt; e += T) {
     const uint32_t hi = static_cast<uint32_t>(lds[e] >> 32);
     const bool start = e == 0 || static_cast<uint32_t>(lds[e - 1] >> 32) != hi;
     if (!start || e + 1 >= cnt || static_cast<uint32_t>(lds[e + 1] >> 32) != hi) continue;
@@ -477,7 +481,7 @@ __device__ void order_runs_and_store(const RasterArgs& a, uint64_t* list, int cn
     }
   }
   __syncthreads();
-  for (int e = t; e < cnt; e += 256) list[e] = lds[e];
+  for (int e = t; e < cnt; e += T) list[e] = lds[e];
 }
 
 template <int EPT>
@@ -494,7 +498,7 @@ __device__ void sort_tile(const RasterArgs& a, uint64_t* list, int cnt, uint64_t
 #pragma unroll
   for (int r = 0; r < EPT; ++r) lds[t * EPT + r] = v[r];
   __syncthreads();
-  order_runs_and_store(a, list, cnt, lds);
+  order_runs_and_store<256>(a, list, cnt, lds);
 }
 
 // Bucket sort of one tile's keys (257 .. 4096 of them) on the float depth
@@ -502,41 +506,47 @@ __device__ void sort_tile(const RasterArgs& a, uint64_t* list, int cnt, uint64_t
 // shift that fits the tile's span of bits into kSortBuckets buckets, is
 // monotone in the key, so sorting each bucket by the full key (depth bits,
 // then index) sorts the list. An LDS histogram, a block scan of it and a
-// scatter place the keys; the owner of 16 consecutive buckets then sorts
-// each of them by insertion. Returns false, having changed nothing, when a
+// scatter place the keys; the owner of eight consecutive buckets then sorts
+// each of them by insertion. 512 threads a block: 49 KB of LDS allow three
+// blocks per CU, whose 24 wavefronts hide the LDS latency that 12 (256 threads)
+// leave bare (3 M primitives at 1920 x 1080: 275 -> 190 us; 1024 threads 193,
+// and 98 against 77 us for 500 k primitives). Returns false, having changed nothing, when a
 // bucket holds more than kSortBucketRun keys: the bitonic network takes
 // that tile instead.
 constexpr int kSortBuckets = 4096;
 constexpr int kSortBucketRun = 32;
+constexpr int kSortThreads = 512;
 
 __device__ bool bucket_sort_tile(const RasterArgs& a, uint64_t* list, int cnt, uint64_t* out,
                                  int* bucket, uint32_t* red) {
-  constexpr int BPT = kSortBuckets / 256;  // buckets owned by each thread
+  constexpr int BPT = kSortBuckets / kSortThreads, kWaves = kSortThreads / 64;  // buckets owned by each thread
   const int t = static_cast<int>(threadIdx.x), lane = t & 63, wave = t >> 6;
   // the keys' high words (float depth bits) are read from the list where
   // only they are needed, which keeps the keys out of registers
   const uint32_t* hw = reinterpret_cast<const uint32_t*>(list) + 1;
   uint32_t lo = 0xffffffffu, hi = 0u;
-  for (int e = t; e < cnt; e += 256) {
+  for (int e = t; e < cnt; e += kSortThreads) {
     const uint32_t h = hw[2 * e];
     lo = min(lo, h);
     hi = max(hi, h);
   }
-  for (int k = t; k < kSortBuckets; k += 256) bucket[k] = 0;
+  for (int k = t; k < kSortBuckets; k += kSortThreads) bucket[k] = 0;
   for (int o = 32; o >= 1; o >>= 1) {
     lo = min(lo, static_cast<uint32_t>(__shfl_xor(static_cast<int>(lo), o, 64)));
     hi = max(hi, static_cast<uint32_t>(__shfl_xor(static_cast<int>(hi), o, 64)));
   }
   if (lane == 0) {
     red[wave] = lo;
-    red[4 + wave] = hi;
+    red[kWaves + wave] = hi;
   }
   __syncthreads();
-  lo = min(min(red[0], red[1]), min(red[2], red[3]));
-  hi = max(max(red[4], red[5]), max(red[6], red[7]));
+  for (int w = 0; w < kWaves; ++w) {
+    lo = min(lo, red[w]);
+    hi = max(hi, red[kWaves + w]);
+  }
   const uint32_t span = hi - lo;
   const int shift = span == 0 ? 0 : max(0, 32 - __clz(static_cast<int>(span)) - 12);
-  for (int e = t; e < cnt; e += 256) atomicAdd(&bucket[(hw[2 * e] - lo) >> shift], 1);
+  for (int e = t; e < cnt; e += kSortThreads) atomicAdd(&bucket[(hw[2 * e] - lo) >> shift], 1);
   __syncthreads();
   int c[BPT];
   int sum = 0, cmax = 0;
@@ -563,7 +573,7 @@ __device__ bool bucket_sort_tile(const RasterArgs& a, uint64_t* list, int cnt, u
     run += c[k];
   }
   __syncthreads();
-  for (int e = t; e < cnt; e += 256) {
+  for (int e = t; e < cnt; e += kSortThreads) {
     const uint64_t key = list[e];
     out[atomicAdd(&bucket[(static_cast<uint32_t>(key >> 32) - lo) >> shift], 1)] = key;
   }
@@ -583,20 +593,42 @@ __device__ bool bucket_sort_tile(const RasterArgs& a, uint64_t* list, int cnt, u
     }
   }
   __syncthreads();
-  order_runs_and_store(a, list, cnt, out);
+  order_runs_and_store<kSortThreads>(a, list, cnt, out);
   return true;
 }
 
-__global__ __launch_bounds__(256) void raster_sort(RasterArgs a) {
+// Lists of at most kRankSort keys: each thread counts the keys below its own
+// (they are distinct), which is its place: no barrier per step, and a list of
+// a few keys costs a few steps (1540 tiles of about 4 keys: 18 -> 4 us against
+// the bitonic network over 256).
+constexpr int kRankSort = 256;
+
+__device__ void rank_sort_tile(const RasterArgs& a, uint64_t* list, int cnt, uint64_t* out,
+                               uint64_t* in) {
+  const int t = static_cast<int>(threadIdx.x);
+  if (t < cnt) in[t] = list[t];
+  __syncthreads();
+  if (t < cnt) {
+    const uint64_t key = in[t];
+    int rank = 0;
+#pragma unroll 4
+    for (int k = 0; k < cnt; ++k) rank += in[k] < key ? 1 : 0;
+    out[rank] = key;
+  }
+  __syncthreads();
+  order_runs_and_store<kSortThreads>(a, list, cnt, out);
+}
+
+__global__ __launch_bounds__(kSortThreads) void raster_sort(RasterArgs a) {
   __shared__ uint64_t lds[256 * 16];
-  __shared__ int bucket[kSortBuckets];
-  __shared__ uint32_t red[8];
+  __shared__ alignas(8) int bucket[kSortBuckets];
+  __shared__ uint32_t red[2 * kSortThreads / 64];
   const int64_t tile = blockIdx.x;
   const int cnt = min(a.cursor[tile], a.cap);
   if (cnt <= 1) return;
   uint64_t* list = a.lists + tile * a.cap;
-  if (cnt <= 256) {
-    sort_tile<1>(a, list, cnt, lds);
+  if (cnt <= kRankSort) {
+    rank_sort_tile(a, list, cnt, lds, reinterpret_cast<uint64_t*>(bucket));
   } else if (!bucket_sort_tile(a, list, cnt, lds, bucket, red)) {
     // left to raster_sort_network, which this mark (the tile's count, bit
     // inverted) tells to take the tile and restore the count; every thread
@@ -1105,25 +1137,36 @@ static void launch_bwd(const RasterArgs& a, int64_t n_tiles, hipStream_t s) {
                      dim3(256 / RPL), 0, s, a);
 }
 
+// Primitives per LDS-counting block: 1024 threads hide the latency of the
+// record loads and LDS atomics that a block of 256 left bare (3 M primitives
+// at 1920 x 1080: 366 -> 259 us, with four per thread; eight 278, two blocks
+// per CU are then all that fit); fewer primitives take smaller chunks, so that
+// at least 128 blocks share them (500 k at 1280 x 720: 171 -> 36 us, with one
+// per thread 45, whose blocks send more device atomics; 12 k: 48 -> 5 us).
+static int64_t bin_chunk(int64_t n) {
+  return kBinThreads * std::min<int64_t>(4, std::max<int64_t>(1, n / (kBinThreads * 128)));
+}
+
 hipError_t launch_raster(const RasterArgs& a, bool bwd, hipStream_t s) {
   const int64_t n_tiles = static_cast<int64_t>(a.tiles_x) * a.tiles_y;
   const unsigned gt = static_cast<unsigned>((n_tiles + 255) / 256);
   const unsigned gn = static_cast<unsigned>((a.n + 255) / 256);
   if (!bwd) {
-    hipLaunchKernelGGL(raster_begin, dim3(gt), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(raster_project, dim3(std::max(gt, gn)), dim3(256), 0, s, a);
     if (a.n > 0) {
-      hipLaunchKernelGGL(raster_project, dim3(gn), dim3(256), 0, s, a);
       int pshift = 0;  // 2^pshift tile classes, the fewest that fit the LDS counters
       while ((1 << pshift) < kBinParts && ((n_tiles - 1) >> pshift) + 1 > kBinLdsTiles) ++pshift;
       if (((n_tiles - 1) >> pshift) + 1 <= kBinLdsTiles) {
-        const int64_t chunk = 256 * kBinPrimsPerThread;
+        const int64_t chunk = bin_chunk(a.n);
         const unsigned gc = static_cast<unsigned>((a.n + chunk - 1) / chunk);
-        hipLaunchKernelGGL(raster_bin_lds, dim3(gc << pshift), dim3(256), 0, s, a, pshift);
+        const size_t lds = sizeof(int) * static_cast<size_t>(((n_tiles - 1) >> pshift) + 1);
+        hipLaunchKernelGGL(raster_bin_lds, dim3(gc << pshift), dim3(kBinThreads), lds, s, a, pshift,
+                           static_cast<int>(chunk));
       } else {
         hipLaunchKernelGGL(raster_bin, dim3(gn * kBinParts), dim3(256), 0, s, a);
       }
     }
-    hipLaunchKernelGGL(raster_sort, dim3(static_cast<unsigned>(n_tiles)), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(raster_sort, dim3(static_cast<unsigned>(n_tiles)), dim3(kSortThreads), 0, s, a);
     hipLaunchKernelGGL(raster_sort_network, dim3(static_cast<unsigned>(n_tiles)), dim3(256), 0, s,
                        a);
     hipLaunchKernelGGL(raster_render_fwd, dim3(static_cast<unsigned>(n_tiles)), dim3(256), 0, s,

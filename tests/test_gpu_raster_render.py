@@ -76,3 +76,33 @@ def test_unbounded_opacity_composites_at_the_clamp(value):
     assert torch.equal(res[0][0], res[1][0])
     for x, y in zip(res[0][1:], res[1][1:]):
         assert torch.allclose(x, y, rtol=1e-6, atol=1e-9)
+
+
+@pytest.mark.parametrize("n", [2, 63, 255, 256, 257, 1024, 1025])
+def test_list_lengths_with_equal_depths(n):
+    """One tile that every primitive reaches, at the lengths where the sort
+    and the binning chunks change, with exact depth ties and depths that are
+    equal only in float32 (the camera is turned by 1e-6 rad)."""
+    rng = np.random.default_rng(70 + n)
+    th = 1e-6
+    R = np.array([[np.cos(th), 0.0, np.sin(th)], [0.0, 1.0, 0.0], [-np.sin(th), 0.0, np.cos(th)]])
+    cam = dict(R=R, t=np.zeros(3), fx=20.0, fy=20.0, cx=8.0, cy=8.0, width=16, height=16)
+    x = rng.uniform(-0.5, 0.5, n)
+    x[: n // 2] = rng.choice(x[n // 2:], n // 2)
+    z = np.where(rng.random(n) < 0.3, 4.0, rng.uniform(3.0, 6.0, n))
+    sc = W.SplatScene(means=np.stack([x, rng.uniform(-0.5, 0.5, n), z], -1).astype(np.float32),
+                      scales=np.exp(rng.uniform(np.log(0.3), np.log(0.6), (n, 3))).astype(np.float32),
+                      rots=rng.standard_normal((n, 4)).astype(np.float32),
+                      opac=rng.uniform(0.02, 0.2, n).astype(np.float32),
+                      colors=rng.standard_normal((n, 3)).astype(np.float32),
+                      grad_image=rng.standard_normal((16, 16, 3)).astype(np.float32), cam=cam)
+    d = [torch.from_numpy(np.ascontiguousarray(v)).cuda()
+         for v in (sc.means, sc.scales, sc.rots, sc.opac, sc.colors)]
+    c = P.Camera(R, cam["t"], 20.0, 20.0, 8.0, 8.0, 16, 16)
+    img, ws = P.raster_fwd(*d, c, 2048)
+    out = P.raster_bwd(*d, c, ws, torch.from_numpy(sc.grad_image).cuda(), 2048, geometry=True)
+    ref, scale = RR.render(sc.means, sc.scales, sc.rots, sc.opac, sc.colors, cam,
+                           grad_image=sc.grad_image, geometry=True)
+    compare(img.cpu().numpy(), ref["image"], scale["image"], "image", TOL)
+    for name, v in zip(("colors", "opac", "means", "scales", "rots"), out):
+        compare(v.cpu().numpy(), ref[name], scale[name], f"grad {name}", TOL)
