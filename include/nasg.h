@@ -222,17 +222,18 @@ int sh3_eval_bwd(const float* sh, int64_t n, const nasg_views* views,
 /* ---- uneven multi-scene batches -------------------------------------------
  * Many independent scenes (different N, K and V), each evaluated exactly as
  * nasg_eval_bwd with a non-NULL rgb would (fused forward+backward, gradients
- * summed over that scene's views), in ONE persistent launch: the scenes are
- * cut into tiles of primitives, the tiles are ordered by cost (tile size x K x
- * V, largest first) and a grid of `blocks_per_cu` blocks per compute unit
- * pulls them from a device work queue. Each scene runs the lane mapping the
- * tuning table (nasg_set_tuning, kernel 1, its K and V, float32) holds for
- * it when the batch kernel carries that mapping -- (1, 1), (1, 2), (1, 4),
- * (4, 2) or (4, 4) -- and otherwise the one that nasg_eval_bwd takes on its
- * own: the smallest of these whose view chunk holds its views (V = 1, 2, 3..4,
- * 5..8, more), or (1, 4) for V > 4 where four lanes would leave too many
- * without a lobe (K = 1, and for V <= 8 K = 2, 3, 5, 6). Gradient sums stay per primitive in
- * registers and lanes (the queue counter is the only atomic). Lobe parameters
+ * summed over that scene's views), in ONE persistent launch: the
+ * scenes are cut into tiles of primitives, the tiles are ordered by cost (tile
+ * size x K x V, largest first) and a grid of `blocks_per_cu` blocks per compute
+ * unit pulls them from a device work queue. Each scene runs
+ * the lane mapping the tuning table (nasg_set_tuning, kernel 1, its K and V,
+ * float32) holds for it when the batch kernel carries that mapping -- (1, 1),
+ * (1, 2), (1, 4), (4, 2), (4, 4) or (8, 2) -- and otherwise the one that
+ * nasg_eval_bwd takes on its own: (1, 1), (1, 2), (1, 4) for V = 1, 2, 3..4,
+ * (4, 2) for V = 5..8 and 17..24, (8, 2) for other V where K fills eight lanes
+ * as well as four, else (4, 4); or (1, 4) where four lanes would leave too many
+ * without a lobe (K = 1, and for V <= 8 K = 2, 5). Gradient sums stay per
+ * primitive in registers and lanes (the queue counter is the only atomic). Lobe parameters
  * must be float32 (NASG_F32).
  *
  * Use: nasg_batched_workspace_bytes -> caller allocates device memory ->

@@ -76,16 +76,27 @@ nasg_tuning shape_of(int64_t n, int lanes, int vpl, int bcast = 0) {
 }
 
 // The mapping that fills the chip best when there are primitives enough, also
-// a scene's in the persistent batch: one lane up to four views; beyond, four
-// lanes, except where they would waste more on missing lobes than one lane's
-// repeated passes over the lobes cost (1.27 times for V <= 8, about twice for
-// more). Backward, N = 1.5 M: K = 1, V = 8 355 -> 236, V = 16 572 -> 459;
-// K = 2, V = 8 375 -> 320 (V = 16 stays at four lanes, 570 against 640).
-// Forward: K = 1, V = 8 188 -> 78, V = 16 356 -> 164.
+// a scene's in the persistent batch. Up to four views one lane; beyond, four
+// lanes with two or four views each, or eight with two where that leaves no
+// more lanes without a lobe. What a mapping does per view slot costs, in units
+// of (8, 2): (4, 4) 1.05, (4, 2) 1.25 for V > 8 (its passes over the lobes
+// repeat the loads and sums), so V = 17..24 take three chunks of (4, 2) rather
+// than two of 16 views (K = 8, V = 24, N = 1 M, backward: 1209 against 1286
+// us). One lane in several passes costs 1.4 times four lanes that all have a
+// lobe, so it serves K = 1, 2 and 5 up to eight views (K = 1, N = 1.5 M, V = 8:
+// 355 -> 236; K = 2 375 -> 320; forward K = 1 188 -> 78) and K = 1 beyond
+// (V = 16: 572 -> 459; K = 2 stays, 570 against 640).
 void mapping_at_scale(int k, int v, int* lanes, int* vpl) {
-  const bool one = k == 1 || (v <= 8 && 5 * k < 4 * ((k + 3) / 4 * 4));
-  *lanes = v <= 4 || one ? 1 : 4;
-  *vpl = v <= 1 ? 1 : v <= 2 ? 2 : *lanes == 4 && v <= 8 ? 2 : 4;
+  const int four = (k + 3) / 4 * 4;
+  if (v <= 4 || k == 1 || (v <= 8 && 7 * k < 5 * four)) {
+    *lanes = 1;
+    *vpl = v <= 1 ? 1 : v <= 2 ? 2 : 4;
+    return;
+  }
+  const bool eight = k >= 8 && (k + 7) / 8 * 8 == four;
+  const bool short_chunks = v <= 8 || (v > 16 && v <= 24);
+  *lanes = eight && !short_chunks ? 8 : 4;
+  *vpl = short_chunks || eight ? 2 : 4;
 }
 
 // Few primitives (forward, K = 8, N = 4096: V = 1 8.9 -> 3.5, V = 4 13.6 ->
@@ -97,8 +108,7 @@ void mapping_at_scale(int k, int v, int* lanes, int* vpl) {
 nasg_tuning nasg_shape(bool bwd, bool bf16, int64_t n, int k, int v) {
   int lanes, vpl;
   mapping_at_scale(k, v, &lanes, &vpl);
-  nasg_tuning scale = shape_of(n, lanes, vpl);
-  if (scale.block == 256 && lanes == 4 && vpl == 4 && k >= 8) scale.block = 128;
+  const nasg_tuning scale = shape_of(n, lanes, vpl);
   if (bwd && !bf16) return scale;
   const int kp = std::min(16, pow2_at_least(k));
   auto fits = [n](int p, int64_t most) { return n * p <= most; };
@@ -117,12 +127,7 @@ nasg_tuning nasg_shape(bool bwd, bool bf16, int64_t n, int k, int v) {
     if (k >= 16 && fits(16, kFillLanes / 2)) return shape_of(n, 16, 1);
     return k >= 8 && fits(8, kFillLanes) ? shape_of(n, 8, 1) : scale;
   }
-  if (k >= 16 && fits(16, 2 * kFillLanes)) return shape_of(n, 16, 1);
-  // eight lanes, where they leave no more without a lobe than four, hold half
-  // the view slots each: better in the forward at any size (K = 8, V = 16,
-  // N = 1.5 M: 659 -> 617), in the backward, whose slots are larger, for few
-  return k >= 8 && (k + 7) / 8 * 8 == (k + 3) / 4 * 4 && (!bwd || fits(8, 4 * kFillLanes))
-             ? shape_of(n, 8, 2) : scale;
+  return k >= 16 && fits(16, 2 * kFillLanes) ? shape_of(n, 16, 1) : scale;
 }
 
 // SH-3: every lane of a primitive would load all 48 coefficients, so one lane
@@ -208,8 +213,7 @@ int check_grad_ptrs(const float* grad_rgb, const nasg_grads* g, const float* rgb
 // ---- persistent batches
 // A scene's lane mapping in the persistent batch: the tuning table's choice
 // for its (K, V) when the batch kernel carries that mapping, else the mapping
-// at scale ((1, 1), (1, 2), (1, 4), (4, 2), (4, 4): all carried); plus
-// kBatchVariants for the paper's raw values.
+// at scale (all of those are carried); plus kBatchVariants for the paper's raw values.
 int batch_variant(int32_t k, int32_t v, int32_t param) {
   int lanes, vpl, var = 0;
   mapping_at_scale(k, v, &lanes, &vpl);

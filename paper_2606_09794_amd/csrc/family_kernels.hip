@@ -66,6 +66,7 @@ __device__ __forceinline__ void family_body(const NasgArgs& a, int64_t prim, int
       }
       // normaliser c and d ln c / d(shape value 0)
       const double p0 = sh.x, p1 = sh.y;
+      const double p0s = p0 * kLog2e, p1s = p1 * kLog2e;
       float cn = 1.f, dlc0 = 0.f;
       if constexpr (FAM == kFamSg) {
         const LobeNorm nm = lobe_norm(p0, 0.0, 0.0, 0.0, 1);   // lam / (2 pi (1 - e^{-2 lam}))
@@ -102,12 +103,12 @@ __device__ __forceinline__ void family_body(const NasgArgs& a, int64_t prim, int
           const double hd = 1.0 - dzd;
           float G = 0.f, sx = 0.f, sy = 0.f, sz = 0.f, g0 = 0.f, g1 = 0.f;
           if constexpr (FAM == kFamSg) {
-            // exponent lam (z.d - 1) = -lam h, FP64
-            G = Nn * exp_neg(-p0 * hd);
+            // exponent lam (z.d - 1) = -lam h, FP64 (p0s, p1s: in units of ln 2)
+            G = Nn * exp2_neg(-p0s * hd);
             sz = p0f * G;
             g0 = -static_cast<float>(hd) * G;
           } else if constexpr (FAM == kFamSb) {
-            // (z.d)^beta = e^{beta ln(z.d)} on z.d > 0; ln from the table, with
+            // (z.d)^beta = 2^{beta log2(z.d)} on z.d > 0; log2 from the table, with
             // z.d kept in [1e-300, 1 - 2^-53] (its own value near 1 is exact)
             const bool live = dzd > 0.0;
             const double tc = fmin(fmax(dzd, 1e-300), 0x1.fffffffffffffp-1);
@@ -116,13 +117,13 @@ __device__ __forceinline__ void family_body(const NasgArgs& a, int64_t prim, int
             const LogEntry lt = ltab[log_bucket(lm)];
             // near 1, (z.d - 1) + h is 0 or the cap's own offset when z.d rounds
             // to 1 (both differences exact there)
-            const double lnt = log_finish(lm, le, lt, dzd > 0.5 ? (tc - 1.0) + hd : 0.0);
-            const float e = exp_neg(p0 * lnt);
+            const double l2t = log2_finish(lm, le, lt, dzd > 0.5 ? ((tc - 1.0) + hd) * kLog2e : 0.0);
+            const float e = exp2_neg(p0 * l2t);
             G = live ? Nn * e : 0.f;
             // dG/d(z.d) = beta G / z.d (z.d floored in FP32, so an underflowed G
             // never meets an infinite reciprocal)
             sz = live ? p0f * G * __builtin_amdgcn_rcpf(fmaxf(static_cast<float>(tc), 1e-30f)) : 0.f;
-            g0 = static_cast<float>(lnt) * G;
+            g0 = static_cast<float>(l2t * kLn2) * G;
           } else if constexpr (FAM == kFamSc) {
             // u = 1 + rho^2 - 2 rho z.d = (1 - rho)^2 + 2 rho h, no cancellation
             const double u = fma(om, om, 2.0 * p0 * hd);
@@ -136,7 +137,7 @@ __device__ __forceinline__ void family_body(const NasgArgs& a, int64_t prim, int
           } else if constexpr (FAM == kFamAsg) {
             const double dxd = d[0] * xa[0] + d[1] * xa[1] + d[2] * xa[2];
             const double dyd = d[0] * ya[0] + d[1] * ya[1] + d[2] * ya[2];
-            const float e = exp_neg(-(p0 * dxd * dxd + p1 * dyd * dyd));
+            const float e = exp2_neg(-(p0s * dxd * dxd + p1s * dyd * dyd));
             const bool live = dzd > 0.0;
             const float dx = static_cast<float>(dxd), dy = static_cast<float>(dyd);
             G = live ? Nn * static_cast<float>(dzd) * e : 0.f;

@@ -156,24 +156,31 @@ __device__ inline double sqrt64(double x) { return x * rsqrt64(x); }
 // relatively accurate to ~1e-8. Near kappa = 1, where that derivative grows
 // to 2 lam (1 + tau) ~ 2e6, ln kappa keeps an absolute error ~1e-16.
 
+// The path works in base 2 (log2 kappa, powers of two), so that splitting an
+// exponent into integer and fraction costs a rounding and an exact difference,
+// no product with log2(e) or ln 2; those constants are folded into the
+// per-lobe factors.
+
 constexpr double kLn2 = 0.693147180559945309417232121458176568;
 
-// One bucket of the ln table: 1/c (rounded) and -ln of that rounded value.
+// One bucket of the log2 table: log2(e)/c (rounded, as inv_c log2(e) times a
+// rho = 1 + O(1e-16)) and -log2 of rho/c.
 struct alignas(16) LogEntry {
   double inv_c;
-  double ln_c;
+  double l2c;
 };
 constexpr int kLogBits = 7;
 constexpr int kLogEntries = 1 << kLogBits;
 
-// ln kappa for kappa in (0, 1), from a 128-entry table in LDS. kappa = m 2^e
+// log2 kappa for kappa in (0, 1], from a 128-entry table in LDS. kappa = m 2^e
 // with m in [1/2, 1); the top seven mantissa bits of m select c (the bucket
-// centre; c = 1 for the top bucket); r = m/c - 1 in one rounding, less
-// `dkap`, the known rounding error of kappa itself (kappa as computed minus
-// its exact value; it matters only in the top bucket, where r = kappa - 1);
-// |r| <= 1/256 and ln kappa = e ln2 + ln c + ln(1 + r) with ln(1 + r) summed
-// to r^4 (truncation |r|^5/5 <= 1.8e-13; relative r^4/5 in the top bucket,
-// so ln kappa stays relatively accurate however close kappa is to 1).
+// centre; c = 1 for the top bucket); r = (m/c - 1) log2(e) in one rounding,
+// less `dkap`, log2(e) times the known rounding error of kappa itself (kappa
+// as computed minus its exact value; it matters only in the top bucket, where
+// r = (kappa - 1) log2(e)); |r| <= log2(e)/256 and log2 kappa = e + log2 c +
+// log2(1 + r/log2(e)), the last summed to r^4 (truncation (r/log2(e))^5/5 <=
+// 1.8e-13; relative to the fourth power over 5 in the top bucket, so log2
+// kappa stays relatively accurate however close kappa is to 1).
 __device__ inline int log_bucket(double m) {
   return (__double2hiint(m) >> (20 - kLogBits)) & (kLogEntries - 1);
 }
@@ -188,47 +195,56 @@ __device__ __forceinline__ double vreg_const(double c) {
   return r;
 }
 
-// a * b + c with b a scalar operand (the one the encoding allows besides
-// vector registers), so that no copy of c is made.
+// a * b + c with b or c a scalar operand (the one the encoding allows besides
+// vector registers), so that no copy of a constant is made.
 __device__ __forceinline__ double fma_vsv(double a, double b, double c) {
   double d;
   asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "s"(b), "v"(c));
   return d;
 }
+__device__ __forceinline__ double fma_vvs(double a, double b, double c) {
+  double d;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
+  return d;
+}
 
-__device__ inline double log_finish(double m, int e, const LogEntry& t, double dkap,
-                                    double third = 1.0 / 3.0) {
-  const double r = fma(m, t.inv_c, -1.0) - dkap;
-  double p = fma_vsv(r, -0.25, third);
-  p = fma(p, r, -0.5);
+constexpr double kLog2C3 = kLn2 * kLn2 / 3.0;   // of r^3 in log2(1 + r/log2(e))
+__device__ inline double log2_finish(double m, int e, const LogEntry& t, double dkap,
+                                     double c3 = kLog2C3) {
+  const double r = fma(m, t.inv_c, -kLog2e) - dkap;
+  double p = fma_vsv(r, -0.25 * kLn2 * kLn2 * kLn2, c3);
+  p = fma_vvs(p, r, -0.5 * kLn2);
   const double lp = fma(p, r * r, r);
-  return fma(static_cast<double>(e), kLn2, t.ln_c + lp);
-}
-__device__ inline double log_kappa(double kap, double dkap, const LogEntry* tab) {
-  int e;
-  const double m = frexp(kap, &e);
-  return log_finish(m, e, tab[log_bucket(m)], dkap);
+  return static_cast<double>(e) + (t.l2c + lp);
 }
 
-// e^B and e^B - 1 for B <= 0 on the envelope path: B = n ln2 + r in one FMA
-// (the rounding of ln2 costs |n| 2e-17, negligible wherever e^B matters),
-// e^r - 1 = r q(r) with q the Taylor series of (e^r - 1)/r to r^7/8!
-// (relative truncation r^8/9! <= 6e-10 at |r| = ln2/2, far smaller near
-// B = 0 where 2 lam (e^B - 1) is large). e^B - 1 is formed as e^B - 1, an
-// absolute error ~1e-16. B below -1e6 is clamped (e^B is 0 there).
-__device__ inline void env_exp(double B, double& eb, double& em1,
-                               double inv8f = 1.0 / 40320.0) {
-  B = fmax(B, -1.0e6);
-  const double n = rint(B * kLog2e);
-  const double r = fma(-n, kLn2, B);
-  double q = fma(inv8f, r, 1.0 / 5040.0);   // 1/8! r + 1/7!
-  q = fma(q, r, 1.0 / 720.0);
-  q = fma(q, r, 1.0 / 120.0);
-  q = fma(q, r, 1.0 / 24.0);
-  q = fma(q, r, 1.0 / 6.0);
-  q = fma(q, r, 0.5);
-  q = fma(q, r, 1.0);
-  eb = ldexp(fma(r, q, 1.0), static_cast<int>(n));
+// Nearest int of an integral double, saturated at the int range (the
+// conversion instruction's own behaviour, spelled out so that out-of-range
+// values are defined).
+__device__ __forceinline__ int sat_int(double n) {
+  int r;
+  asm("v_cvt_i32_f64 %0, %1" : "=v"(r) : "v"(n));
+  return r;
+}
+
+// 2^B and 2^B - 1 for B <= 0 on the envelope path: B = n + r exactly, |r| <=
+// 1/2, 2^r - 1 = r q(r) with q the Taylor series of (2^r - 1)/r to r^7
+// (relative truncation (r ln2)^8/9! <= 6e-10 at |r| = 1/2, far smaller near
+// B = 0 where 2 lam (2^B - 1) is large). 2^B - 1 is formed as 2^B - 1, an
+// absolute error ~1e-16. A very negative B gives 0 (n saturates).
+constexpr double kLn2P2 = kLn2 * kLn2, kLn2P4 = kLn2P2 * kLn2P2;
+constexpr double kExp2C8 = kLn2P4 * kLn2P4 / 40320.0;   // ln2^8 / 8!
+__device__ inline void env_exp2(double B, double& eb, double& em1, double c8 = kExp2C8) {
+  const double n = rint(B);
+  const double r = B - n;
+  double q = fma(c8, r, kLn2P4 * kLn2P2 * kLn2 / 5040.0);
+  q = fma(q, r, kLn2P4 * kLn2P2 / 720.0);
+  q = fma(q, r, kLn2P4 * kLn2 / 120.0);
+  q = fma(q, r, kLn2P4 / 24.0);
+  q = fma(q, r, kLn2P2 * kLn2 / 6.0);
+  q = fma(q, r, kLn2P2 / 2.0);
+  q = fma(q, r, kLn2);
+  eb = ldexp(fma(r, q, 1.0), sat_int(n));
   em1 = eb - 1.0;
 }
 
@@ -259,42 +275,32 @@ __device__ inline void exp_em1(double B, double& eb, double& em1) {
   em1 = n == 0.0 ? r * q : eb - 1.0;
 }
 
-// Nearest int of an integral double, saturated at the int range (the
-// conversion instruction's own behaviour, spelled out so that out-of-range
-// values are defined).
-__device__ __forceinline__ int sat_int(double n) {
-  int r;
-  asm("v_cvt_i32_f64 %0, %1" : "=v"(r) : "v"(n));
-  return r;
-}
-
-// e^X as float for X <= 0: y = X log2(e) in FP64 (rounding |y| 1e-16), split
-// into its nearest integer n and |f| <= 1/2, then the hardware base-2
-// exponential of f and an exact power-of-two scale. Very negative X gives
-// 2^f with n saturated far below the FP32 range: 0.
-__device__ inline float exp_neg(double X) {
-  const double y = X * kLog2e;
+// 2^y as float for y <= 0 in FP64: its nearest integer n and the exact rest
+// |f| <= 1/2, then the hardware base-2 exponential of f and an exact
+// power-of-two scale. Very negative y gives 2^f with n saturated far below the
+// FP32 range: 0.
+__device__ inline float exp2_neg(double y) {
   const double n = rint(y);
   const float p = __builtin_amdgcn_exp2f(static_cast<float>(y - n));
   return ldexpf(p, sat_int(n));
 }
 
-// sin(pi x/2) and cos(pi x/2) in FP32 for |x| <= 1/2: Taylor series of sine
-// to y^9 and cosine to y^10 in y = pi x/2, |y| <= pi/4 (truncation below 2e-8
-// relative).
+// sin(pi x/2) and cos(pi x/2) in FP32 for |x| <= 1/2: minimax polynomials in
+// x^2 (own Remez fits for relative error: 3.2e-9 for sine over x, 6.4e-11 for
+// cosine with its constant fixed at 1). Maximum error with FP32 rounding
+// 1.3e-7 and 8.1e-8, against 1.4e-7 and 1.1e-7 of the Taylor series to y^9 and
+// y^10 in y = pi x/2, which take three instructions more.
 __device__ inline void sincos_halfpi(float x, float& s, float& c) {
-  const float y = 1.57079632679489661923f * x;
-  const float z = y * y;
-  float ps = 1.f / 362880.f;
-  ps = fmaf(ps, z, -1.f / 5040.f);
-  ps = fmaf(ps, z, 1.f / 120.f);
-  ps = fmaf(ps, z, -1.f / 6.f);
-  s = fmaf(y * z, ps, y);
-  float pc = -1.f / 3628800.f;
-  pc = fmaf(pc, z, 1.f / 40320.f);
-  pc = fmaf(pc, z, -1.f / 720.f);
-  pc = fmaf(pc, z, 1.f / 24.f);
-  pc = fmaf(pc, z, -0.5f);
+  const float z = x * x;
+  float ps = -0.0046016578911805455f;
+  ps = fmaf(ps, z, 0.07968003277042174f);
+  ps = fmaf(ps, z, -0.645963460233428f);
+  ps = fmaf(ps, z, 1.5707963217083447f);
+  s = x * ps;
+  float pc = 0.0009037665432423369f;
+  pc = fmaf(pc, z, -0.02086016511147022f);
+  pc = fmaf(pc, z, 0.25366922596549085f);
+  pc = fmaf(pc, z, -1.2337005425976675f);
   c = fmaf(z, pc, 1.f);
 }
 

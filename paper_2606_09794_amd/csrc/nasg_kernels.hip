@@ -46,10 +46,6 @@
 #include "nasg_launch.hpp"
 #include "nasg_skeleton.hpp"
 
-#ifndef NASG_BC_WAVES
-#define NASG_BC_WAVES 3
-#endif
-
 namespace nasg {
 
 // The paper's raw lobe values activated (Supplementary C): lam = e^u,
@@ -79,6 +75,24 @@ __device__ __noinline__ Activated activate_raw(float4 sh, float w0, float w1, fl
   return r;
 }
 
+// Waves per SIMD that a lane mapping is compiled for. A view slot takes 19
+// registers. With at most two per lane the kernel fits the 168 registers of
+// three waves, given that the view chunks are no loop where one holds all views
+// (ONE), that c0 and the mean are read again per chunk and that two polynomial
+// constants are not kept in registers. The third wave covers the dependent FP64
+// chains that two leave bare, and fewer spills leave room for it (backward: K =
+// 8, 3 M x 16 on (8, 2) 2069 -> 1892 us, where (4, 4) at two waves takes 2027; K
+// = 16 in bfloat16, 2 M x 8 on (4, 2) 1580 -> 1398; K = 8, 1.5 M x 2 on (1, 2)
+// 274 -> 240). With four views per lane, or the paper's raw values (six more
+// registers of activation derivatives), the spills cost more than the wave
+// brings; four waves of 128 registers spill too (forward K = 8, 1 M x 1: 139 us
+// against 80).
+constexpr int mapping_waves(int lanes, int vpl, bool bc, bool ang) {
+  return bc || (lanes == 1 && vpl == 1) ||
+                 (vpl <= 2 && !(lanes == 2 && vpl == 2) && (!ang || (lanes == 8 && vpl == 1)))
+             ? 3 : 2;
+}
+
 // One primitive-lane-group's work: primitive `prim` (may be >= n for tail
 // lanes, which compute on a real primitive and write nothing), lane j of P.
 // NOCAR: the NASG lobe (Supplementary E): no carrier (k = zeta = 0) and the
@@ -91,7 +105,8 @@ __device__ __noinline__ Activated activate_raw(float4 sh, float w0, float w1, fl
 // the group, so that its bits are those of the one-lane mapping. For few views this spreads a primitive over P lanes (P lobes prepared and
 // loaded at once) instead of one lane walking all of them.
 template <int P, int VPL, bool BWD, bool BF16, bool ANG, bool NOCAR = false, bool BC = false,
-          bool ONCE = false, bool PF = !(P == 1 && VPL == 1)>
+          bool ONE = false, bool ONCE = false,
+          bool PF = (ONE && (!BWD || P == 1 || VPL == 1)) || mapping_waves(P, VPL, false, ANG) == 2>
 __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j,
                                           const LogEntry* ltab) {
   using S = Store<BF16>;
@@ -101,14 +116,19 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
   const int V = a.v;
   const int K = a.k;
   const int rot_addr = group_next_addr<P>();
-  const double k_third = vreg_const(1.0 / 3.0);
-  const double k_inv8f = vreg_const(1.0 / 40320.0);
+  // (two registers each that three waves per SIMD cannot spare)
+  constexpr bool kKeep = mapping_waves(P, VPL, BC, ANG) == 2;
+  const double k_c3 = kKeep ? vreg_const(kLog2C3) : kLog2C3;
+  const double k_c8 = kKeep ? vreg_const(kExp2C8) : kExp2C8;
 
-  const float c0v[3] = {a.c0[3 * i + 0], a.c0[3 * i + 1], a.c0[3 * i + 2]};
   const float* bp = a.dirs != nullptr ? a.dirs : a.means;
-  const double base[3] = {bp[3 * i + 0], bp[3 * i + 1], bp[3 * i + 2]};
 
-  for (int v0 = 0; v0 < V; v0 += BC ? VPL : P * VPL) {
+  constexpr int kChunk = BC ? VPL : P * VPL;
+  for (int v0 = 0; v0 < (ONE ? kChunk : V); v0 += kChunk) {
+    // read again for every view chunk: nine registers that need not live
+    // through the lobes
+    const float c0v[3] = {a.c0[3 * i + 0], a.c0[3 * i + 1], a.c0[3 * i + 2]};
+    const double base[3] = {bp[3 * i + 0], bp[3 * i + 1], bp[3 * i + 2]};
     // gradients of later view chunks accumulate onto the first chunk's
     const bool acc_mode = a.accumulate || v0 > 0;
     ViewSlots<VPL> sl;
@@ -131,8 +151,9 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
       w2_ = S::template load1<ONCE>(a.rgbw, (static_cast<int64_t>(lo_) * 3 + 2) * N + i);
     };
     // PF: the next lobe group's records are loaded while the current group
-    // is evaluated (by default where a lane meets several views per lobe; the
-    // single-view mapping has no registers to spare for them at three waves).
+    // is evaluated, where the 11 registers are there (at two waves, and in the
+    // forward or on one lane with a single chunk: forward K = 8, 1 M x 1 91 ->
+    // 82 us, raw values K = 2, 3 M x 1, both directions 311 -> 287).
     float4 nq, nsh;
     float nw0, nw1, nw2;
     if constexpr (PF) load_rec(0, nq, nsh, nw0, nw1, nw2);
@@ -181,13 +202,13 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
       const float Nn = own ? nm.n : 0.f;
       const float kf = static_cast<float>(kd);
       const float two_lam = static_cast<float>(2.0 * lamd);
-      const double two_lamd = 2.0 * lamd;
-      const double and_ = ad;
-      const float two_an = static_cast<float>(2.0 * ad);
+      const double two_laml = lamd * (2.0 * kLog2e);
+      const double a2 = 2.0 * ad;
+      const float a_ln2 = static_cast<float>(4.0 * kLn2 * ad);
       const float xf0 = static_cast<float>(xa0), xf1 = static_cast<float>(xa1),
                   xf2 = static_cast<float>(xa2);
-      const float zf0 = static_cast<float>(za0), zf1 = static_cast<float>(za1),
-                  zf2 = static_cast<float>(za2);
+      const float zf0 = static_cast<float>(2.0 * za0), zf1 = static_cast<float>(2.0 * za1),
+                  zf2 = static_cast<float>(2.0 * za2);   // 2 z
 
       // gradient sums of the owned lobe
       float acc_w0 = 0.f, acc_w1 = 0.f, acc_w2 = 0.f, acc_G = 0.f, acc_l = 0.f, acc_a = 0.f;
@@ -201,34 +222,35 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
         for (int t = 0; t < VPL; ++t) {
           // Branch-free. A view slot beyond V carries a real direction and a zero
           // upstream gradient, so it adds nothing but its (unwritten) colour; at
-          // d = -z (kappa = 0) G and every gradient are forced to 0 and kappa is
-          // kept away from 0 where it is inverted.
+          // d = -z (kappa = 0) G and every gradient are forced to 0.
           const double dxd = sl.dd[t][0] * xa0 + sl.dd[t][1] * xa1 + sl.dd[t][2] * xa2;
           // q = |d + z|^2 = 2 (1 + d.z) = 4 kappa from the chord: relatively
           // accurate next to the antipode, where 1 + d.z would cancel. Every
           // other quantity derives from q: kappa = q/4 (exact), h = 1 - d.z =
           // 2 - q/2 (exact where q >= 2, Sterbenz), so kappa and h are
-          // consistent and the table ln needs no correction for kappa's own
+          // consistent and the table log needs no correction for kappa's own
           // rounding. Next to the axis h keeps an absolute error ~2e-16;
           // nothing below is sensitive to h's relative error there (G, s_x
           // and a's gradient depend on tau only through tau ln kappa and ln
           // kappa/(1 - (d.z)^2), s_z through tau Q, all smooth in h).
+          // In 1/(h q) = 1/(2 (1 - (d.z)^2)) h and q are kept off zero by less than
+          // their rounding, so that it is finite at the poles: at d = z the
+          // factors it multiplies (d.x, tau) are ~1e-16 of their scale, at
+          // d = -z everything is multiplied by G = 0.
           const double e0 = sl.dd[t][0] + za0;
           const double e1 = sl.dd[t][1] + za1;
           const double e2 = sl.dd[t][2] + za2;
           const double q = fma(e0, e0, fma(e1, e1, e2 * e2));
-          const double hd = fma(q, -0.5, 2.0);
-          const double opd = 0.5 * q;                // 2 kappa
           const bool live = q > 0.0;
-          // kappa = lm 2^(le - 2). The table entry is fetched first, its use
-          // comes after the carrier and 1/(1 - (d.z)^2).
-          int le;
-          const double lm = frexp(q, &le);
+          const double hd = fmax(fma(q, -0.5, 2.0), 0x1p-53);
+          // kappa = lm 2^le. The table entry is fetched first, its use comes
+          // after the carrier and 1/(h q).
+          const int le = __builtin_amdgcn_frexp_exp(q) - 2;
+          const double lm = __builtin_amdgcn_frexp_mant(q);
           const LogEntry lt = ltab[log_bucket(lm)];
           __builtin_amdgcn_sched_barrier(0);   // keep the table read ahead of the carrier work
-          const double dend = hd * opd;              // 1 - (d.z)^2
+          const double dend = hd * fmax(q, 4e-30);   // 2 (1 - (d.z)^2)
           const float dx = static_cast<float>(dxd);
-          const float opf = fmaxf(static_cast<float>(opd), 1e-30f);
           // carrier phase theta/pi = (k d.x + zeta)/pi, reduced to the nearest
           // integer n: theta = pi (n + g), |g| <= 1/2. Even n is a carrier peak,
           // c = cos^2(pi g/2); odd n a zero, c = sin^2(pi g/2); dc/dtheta is
@@ -242,22 +264,20 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
             const double nh = rint(th);
             float sa, ca;
             sincos_halfpi(static_cast<float>(th - nh), sa, ca);
-            peak = (static_cast<int>(nh) & 1) == 0;
+            peak = (sat_int(nh) & 1) == 0;
             const float cpk = peak ? ca : sa;
             car = cpk * cpk;
             scp = sa * ca;
           }
-          // envelope exponent in FP64: X = 2 lam (E kappa - 1) + tau ln kappa
-          const bool pole = !(dend > 0.0);
-          const double rden = pole ? 0.0 : rcp64(dend);
-          const double ud = dxd * dxd * rden;        // tau / a
-          const double taud = and_ * ud;
-          __builtin_amdgcn_sched_barrier(0);
-          const double Ld = log_finish(lm, le - 2, lt, 0.0, k_third);
-          const double Ad = taud * Ld;               // ln E
+          // envelope exponent in FP64, base 2: X log2(e) = 2 lam log2(e) (E kappa
+          // - 1) + tau log2 kappa
+          const double rden = rcp64(dend);           // 1 / (2 (1 - (d.z)^2))
+          const double taud = a2 * (dxd * dxd * rden);
+          const double Ld = log2_finish(lm, le, lt, 0.0, k_c3);
+          const double Ad = taud * Ld;               // log2 E
           double Ekd, em1d;
-          env_exp(Ad + Ld, Ekd, em1d, k_inv8f);      // E kappa and E kappa - 1
-          const float pE = exp_neg(fma(two_lamd, em1d, Ad));
+          env_exp2(Ad + Ld, Ekd, em1d, k_c8);        // E kappa and E kappa - 1
+          const float pE = exp2_neg(fma(two_laml, em1d, Ad));
           const float Npe = live ? Nn * pE : 0.f;
           const float G = Npe * car;
           if constexpr (BC && !BWD) {
@@ -268,11 +288,13 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
             sl.col[t][2] = fmaf(w2, G, sl.col[t][2]);
           }
           if constexpr (BWD) {
-            const float LR = pole ? -0.25f : static_cast<float>(Ld * rden);  // ln kappa/(1-(d.z)^2)
-            // Q = 1/(2 kappa) + 2 d.z ln kappa/(1 - (d.z)^2) = (h + 2 d.z ln kappa)/(1 - (d.z)^2)
-            // in FP64: its two terms (each ~1/2) cancel next to the axis, where
-            // Q -> 3h/8 (0 at d = z, where rden is 0)
-            const float Q = static_cast<float>(fma(q - 2.0, Ld, hd) * rden);   // 2 d.z = q - 2
+            // log2 kappa/(2 (1 - (d.z)^2)); the factor 2 ln2 of ln kappa/(1 -
+            // (d.z)^2) is in a_ln2 and in a's sum
+            const float LR = static_cast<float>(Ld * rden);
+            // Q/2, Q = 1/(2 kappa) + 2 d.z ln kappa/(1 - (d.z)^2) = (h + 2 d.z ln
+            // kappa)/(1 - (d.z)^2) in FP64: its two terms (each ~1/2) cancel next
+            // to the axis, where Q -> 3h/8 (2 d.z = q - 2)
+            const float Qh = static_cast<float>(fma((q - 2.0) * kLn2, Ld, hd) * rden);
             const float tau = static_cast<float>(taud);
             const float em1 = static_cast<float>(em1d);
             const float g0 = sl.gr[t][0], g1 = sl.gr[t][1], g2 = sl.gr[t][2];
@@ -291,17 +313,18 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
             const float gS = gG * Sth;
             acc_k = fmaf(gS, dx, acc_k);
             acc_z += gS;
-            // qT = dL/dG G (2 lam E kappa + 1); uu = qT LR d.x with
-            // LR = ln kappa/(1 - (d.z)^2): a's sum takes uu d.x (ln kappa dtau/da
-            // = LR (d.x)^2), and dL/dG s_x = uu 2a + dL/dG N p E dc/dtheta k
+            // qT = dL/dG G (2 lam E kappa + 1); uu = qT LR d.x with LR as above:
+            // a's sum takes uu d.x (ln kappa dtau/da = 2 ln2 LR (d.x)^2), and
+            // dL/dG s_x = uu 4 a ln2 + dL/dG N p E dc/dtheta k
             const float qT = qG * T2;
             const float uu = qT * LR * dx;
             acc_a = fmaf(uu, dx, acc_a);
-            const float gsx = fmaf(uu, two_an, gS * kf);
-            const float inv2k = __builtin_amdgcn_rcpf(opf);   // 1/(2 kappa)
-            // dL/dG s_z = dL/dG G [(2 lam E kappa + 1) tau Q + lam E],
-            // lam E = 2 lam E kappa / (2 kappa)
-            const float gsz = fmaf(qT * tau, Q, qG * (two_lam * Ek * inv2k));
+            const float gsx = fmaf(uu, a_ln2, gS * kf);
+            const float iq = static_cast<float>(hd * rden);   // 1/q
+            // half of dL/dG s_z = dL/dG G [(2 lam E kappa + 1) tau Q + lam E],
+            // lam E = 2 (2 lam E kappa)/q; the factor 2 is in zf0..2 and where
+            // az is used
+            const float gsz = fmaf(qT * tau, Qh, qG * (two_lam * Ek * iq));
             ax0 = fmaf(gsx, sl.df[t][0], ax0);
             ax1 = fmaf(gsx, sl.df[t][1], ax1);
             ax2 = fmaf(gsx, sl.df[t][2], ax2);
@@ -316,7 +339,6 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
           // soon as it is done, so the transfer overlaps the next view's work
           if constexpr (P > 1 && !BC) {
             slot_pass<P, VPL, BWD>(sl, t, rot_addr);
-            __builtin_amdgcn_sched_barrier(0);
           }
         }
       }
@@ -344,13 +366,13 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
           if (a.g_shape != nullptr) {
             put4<ONCE>(a.g_shape, li,
                        make_float4(fmaf(nm.dl, acc_G, 2.f * acc_l) * dlam_du,
-                                   fmaf(nm.da, acc_G, acc_a) * da_du,
+                                   fmaf(nm.da, acc_G, static_cast<float>(2.0 * kLn2) * acc_a) * da_du,
                                    fmaf(nm.dk, acc_G, acc_k) * dk_du, fmaf(nm.dz, acc_G, acc_z)),
                        acc_mode);
           }
           if (a.g_quat != nullptr) {
-            const float xf[3] = {xf0, xf1, xf2}, zf[3] = {zf0, zf1, zf2};
-            const float gx[3] = {ax0, ax1, ax2}, gz[3] = {az0, az1, az2};
+            const float xf[3] = {xf0, xf1, xf2}, zf[3] = {0.5f * zf0, 0.5f * zf1, 0.5f * zf2};
+            const float gx[3] = {ax0, ax1, ax2}, gz[3] = {2.f * az0, 2.f * az1, 2.f * az2};
             put4<ONCE>(a.g_quat, li, frame_grad<ANG>(f, xf, zf, gx, gz), acc_mode);
           }
           if (a.g_rgbw != nullptr)
@@ -364,22 +386,19 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
   }
 }
 
-template <int P, int VPL, bool BWD, bool BF16, bool ANG, bool NOCAR, bool BC, bool ONCE>
-// One lane and one view per primitive run three waves per SIMD (the few spills
-// land in the once-per-lobe preparation), and so do broadcast views; the other
-// mappings keep two, where the full register budget pays more than a third wave.
-// ONCE (one lane per primitive only): all views fit in one chunk and nothing
-// accumulates onto earlier results, so the lobe records are read and every
-// output is written exactly once, all as streaming data.
+template <int P, int VPL, bool BWD, bool BF16, bool ANG, bool NOCAR, bool BC, bool ONE, bool ONCE>
+// ONE: one chunk holds all views. ONCE (one lane per primitive, one chunk only):
+// and nothing accumulates onto earlier results, so the lobe records are read and
+// every output is written exactly once, all as streaming data.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
-    BC ? NASG_BC_WAVES : (P == 1 && VPL == 1 ? 3 : 2))))
+    mapping_waves(P, VPL, BC, ANG))))
 void nasg_kernel(const NasgArgs a) {
-  static_assert(!ONCE || P == 1, "the streaming flavour has one lane per primitive");
+  static_assert(!ONCE || (P == 1 && ONE), "the streaming flavour: one lane per primitive, one chunk");
   __shared__ LogEntry ltab[kLogEntries];
   load_log_table(ltab);
   const int64_t gt = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  nasg_body<P, VPL, BWD, BF16, ANG, NOCAR, BC, ONCE>(a, gt / P, static_cast<int>(gt & (P - 1)),
-                                                     ltab);
+  nasg_body<P, VPL, BWD, BF16, ANG, NOCAR, BC, ONE, ONCE>(a, gt / P,
+                                                          static_cast<int>(gt & (P - 1)), ltab);
 }
 
 // ------------------------------------------------------- persistent batch
@@ -391,7 +410,7 @@ __device__ __forceinline__ void batch_tile(const NasgArgs& a, int64_t start, int
   for (int m = 0; m < iters; ++m) {
     const int64_t base = start + static_cast<int64_t>(m) * kPrimsPerPass;
     if (base >= a.n) break;  // uniform across the block
-    nasg_body<P, VPL, true, false, ANG, false, false, false, false>(a, base + threadIdx.x / P,
+    nasg_body<P, VPL, true, false, ANG, false, false, false, false, false>(a, base + threadIdx.x / P,
                                         static_cast<int>(threadIdx.x & (P - 1)), ltab);
   }
 }
@@ -418,16 +437,17 @@ __device__ __forceinline__ T load_uniform(const T* p) {
 // Pulls tiles from the queue until it is empty; every block exits when the
 // head passes n_items. A plan whose token does not match is not run.
 // Two waves per SIMD: the inlined lane mappings would otherwise need more
-// registers than that occupancy allows. RAW: the plan has scenes with the
-// paper's raw values, so the five lane mappings are inlined for both
-// parametrisations; without them only the five quaternion mappings are, and
-// an item of a raw-value scene, which such a plan never holds, is skipped.
+// registers than that occupancy allows (a second kernel and queue at three
+// waves for the mappings that fit them alone spills 36 registers here, where
+// the scene's record is in scalar ones, and adds a tail: 32 large scenes 5.7 ->
+// 6.1 ms). RAW: the plan has scenes with the paper's raw values, so the lane
+// mappings are inlined for both parametrisations; without them only the
+// quaternion mappings are, and an item of a raw-value scene, which such a plan
+// never holds, is skipped.
 template <bool RAW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void nasg_batched_kernel(const BatchHeader* hdr,
-                                                           const BatchScene* scenes,
-                                                           const BatchItem* items,
-                                                           uint32_t* counter, uint64_t token) {
+void nasg_batched_kernel(const BatchHeader* hdr, const BatchScene* scenes, const BatchItem* items,
+                         uint32_t* counter, uint64_t token) {
   __shared__ int s_item;
   __shared__ LogEntry ltab[kLogEntries];
   if (hdr->token != token) return;
@@ -447,14 +467,16 @@ void nasg_batched_kernel(const BatchHeader* hdr,
       case 2: batch_tile<1, 4, false>(sc.args, item.start, sc.tile_iters, ltab); break;
       case 3: batch_tile<4, 2, false>(sc.args, item.start, sc.tile_iters, ltab); break;
       case 4: batch_tile<4, 4, false>(sc.args, item.start, sc.tile_iters, ltab); break;
+      case 5: batch_tile<8, 2, false>(sc.args, item.start, sc.tile_iters, ltab); break;
       default:
         if constexpr (RAW) {
           switch (sc.variant) {
-            case 5: batch_tile<1, 1, true>(sc.args, item.start, sc.tile_iters, ltab); break;
-            case 6: batch_tile<1, 2, true>(sc.args, item.start, sc.tile_iters, ltab); break;
-            case 7: batch_tile<1, 4, true>(sc.args, item.start, sc.tile_iters, ltab); break;
-            case 8: batch_tile<4, 2, true>(sc.args, item.start, sc.tile_iters, ltab); break;
-            default: batch_tile<4, 4, true>(sc.args, item.start, sc.tile_iters, ltab); break;
+            case 6: batch_tile<1, 1, true>(sc.args, item.start, sc.tile_iters, ltab); break;
+            case 7: batch_tile<1, 2, true>(sc.args, item.start, sc.tile_iters, ltab); break;
+            case 8: batch_tile<1, 4, true>(sc.args, item.start, sc.tile_iters, ltab); break;
+            case 9: batch_tile<4, 2, true>(sc.args, item.start, sc.tile_iters, ltab); break;
+            case 10: batch_tile<4, 4, true>(sc.args, item.start, sc.tile_iters, ltab); break;
+            default: batch_tile<8, 2, true>(sc.args, item.start, sc.tile_iters, ltab); break;
           }
         }
         break;
@@ -487,15 +509,15 @@ static hipError_t launch_one(const NasgArgs& a, int block, hipStream_t s) {
   // accesses cover whole cache lines, and a launch that reads every record
   // and writes every output once: all views in one chunk and no accumulation
   // onto earlier results (so acc_mode is always false in it).
-  if constexpr (P == 1) {
-    if (!a.accumulate && a.v <= VPL) {
-      hipLaunchKernelGGL((nasg_kernel<P, VPL, BWD, BF16, ANG, NOCAR, BC, true>),
-                         dim3(static_cast<unsigned>(grid)), dim3(block), 0, s, a);
-      return hipGetLastError();
-    }
+  const bool one = a.v <= (BC ? VPL : P * VPL);
+  const dim3 g(static_cast<unsigned>(grid)), b(block);
+  if (one && P == 1 && !a.accumulate) {
+    hipLaunchKernelGGL((nasg_kernel<P, VPL, BWD, BF16, ANG, NOCAR, BC, true, P == 1>), g, b, 0, s, a);
+  } else if (one) {
+    hipLaunchKernelGGL((nasg_kernel<P, VPL, BWD, BF16, ANG, NOCAR, BC, true, false>), g, b, 0, s, a);
+  } else {
+    hipLaunchKernelGGL((nasg_kernel<P, VPL, BWD, BF16, ANG, NOCAR, BC, false, false>), g, b, 0, s, a);
   }
-  hipLaunchKernelGGL((nasg_kernel<P, VPL, BWD, BF16, ANG, NOCAR, BC, false>),
-                     dim3(static_cast<unsigned>(grid)), dim3(block), 0, s, a);
   return hipGetLastError();
 }
 

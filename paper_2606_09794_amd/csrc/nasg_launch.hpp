@@ -102,9 +102,8 @@ static_assert(sizeof(BatchHeader) == 64, "batch header layout");
 
 struct BatchScene {
   NasgArgs args;
-  int32_t variant;     // lane mapping (lanes, views per lane): 0 = (1, 1), 1 = (1, 2),
-                       // 2 = (1, 4), 3 = (4, 2), 4 = (4, 4); 5..9: the same for the
-                       // paper's raw values
+  int32_t variant;     // lane mapping, an index of kBatchLanes; + kBatchVariants for
+                       // the paper's raw values
   int32_t tile_iters;
 };
 
@@ -113,11 +112,11 @@ struct BatchItem {
   int32_t pad;
   int64_t start;       // first primitive of the tile
 };
+static_assert(sizeof(BatchItem) == 16, "the binding counts tiles by their size");
 
-constexpr int kBatchVariants = 5;   // lane mappings per parametrisation
-constexpr int kBatchLanes[2 * kBatchVariants] = {1, 1, 1, 4, 4, 1, 1, 1, 4, 4};
-constexpr int kBatchViewsPerLane[2 * kBatchVariants] = {1, 2, 4, 2, 4, 1, 2, 4, 2, 4};
-
+constexpr int kBatchVariants = 6;   // lane mappings per parametrisation
+constexpr int kBatchLanes[2 * kBatchVariants] = {1, 1, 1, 4, 4, 8, 1, 1, 1, 4, 4, 8};
+constexpr int kBatchViewsPerLane[2 * kBatchVariants] = {1, 2, 4, 2, 4, 2, 1, 2, 4, 2, 4, 2};
 hipError_t launch_batched(const BatchHeader* hdr, const BatchScene* scenes, const BatchItem* items,
                           uint32_t* counter, uint64_t token, int grid, bool raw, hipStream_t s);
 

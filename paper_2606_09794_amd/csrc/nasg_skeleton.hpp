@@ -1,5 +1,5 @@
 // The per-primitive skeleton shared by the NASGabor kernel and the other lobe
-// families: the ln table, the travelling view slots (set-up, transfer,
+// families: the log2 table, the travelling view slots (set-up, transfer,
 // write-out of colours and of the c0 / mean gradients) and the conversion of
 // the frame-axis gradients into the stored frame parameters.
 //
@@ -20,7 +20,7 @@
 
 namespace nasg {
 
-// ------------------------------------------------------------ ln table
+// ----------------------------------------------------------- log2 table
 // ln x for x in [1, 2] at compile time: 2 atanh((x - 1)/(x + 1)) summed until
 // the terms vanish (|s| <= 1/3).
 constexpr double ce_log(double x) {
@@ -38,22 +38,33 @@ struct LogTable {
 };
 
 // Bucket j covers m in [1/2 + j/256, 1/2 + (j + 1)/256); c is its centre, or
-// 1 for the top bucket. ln c is stored as -ln(1/c) of the rounded 1/c, so that
-// ln(m (1/c)) - ln(1/c) is ln m whatever the rounding of 1/c.
+// 1 for the top bucket. With x the rounded log2(e)/c, the kernels form m x -
+// log2(e) = (m x/log2(e) - 1) log2(e), so l2c is -log2(x/log2(e)), formed from
+// 1/c and the rounding of x (first order: x/log2(e) = (1/c)(1 + d), d ~ 1e-16):
+// the sum is log2 m whatever the rounding of x. In the top bucket x is log2(e)
+// itself and l2c is 0.
 constexpr LogTable make_log_table() {
   LogTable t{};
   for (int j = 0; j < kLogEntries; ++j) {
-    const double c = (j == kLogEntries - 1) ? 1.0 : 0.5 + (j + 0.5) / (2.0 * kLogEntries);
-    const double ic = 1.0 / c;
-    t.e[j].inv_c = ic;
-    t.e[j].ln_c = -ce_log(ic);
+    if (j == kLogEntries - 1) {
+      t.e[j].inv_c = kLog2e;
+      t.e[j].l2c = 0.0;
+      continue;
+    }
+    const double c = 0.5 + (j + 0.5) / (2.0 * kLogEntries);
+    t.e[j].inv_c = kLog2e / c;
+    // x c - log2(e) exactly: c has 9 significant bits, x is split at 26
+    const double x = t.e[j].inv_c;
+    const double hi = static_cast<double>(static_cast<float>(x)), lo = x - hi;
+    const double d = ((hi * c - kLog2e) + lo * c) / kLog2e;
+    t.e[j].l2c = (ce_log(2.0 * c) - d) * kLog2e - 1.0;
   }
   return t;
 }
 
 static __constant__ const LogTable kLogTable = make_log_table();
 
-// Copies the ln table into this block's LDS (every thread of the block calls it).
+// Copies the table into this block's LDS (every thread of the block calls it).
 __device__ inline void load_log_table(LogEntry* lds) {
   for (int t = threadIdx.x; t < kLogEntries; t += blockDim.x) lds[t] = kLogTable.e[t];
   __syncthreads();

@@ -23,7 +23,7 @@ def _take(w, m=96):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("n", [1, 4097, 16385, 32769])
 @pytest.mark.parametrize("k,v", [(1, 1), (5, 1), (16, 1), (2, 2), (3, 2), (9, 2), (1, 4), (8, 3), (2, 7),
-                                 (6, 6), (7, 8), (16, 5), (1, 9), (2, 18), (3, 17), (9, 17), (16, 33)])
+                                 (6, 6), (7, 8), (16, 5), (1, 9), (2, 18), (3, 17), (9, 17), (8, 20), (16, 33)])
 def test_nasg_shapes(n, k, v, dtype):
     w = W.draw_workload(n + 64 * k + v, n, k, v, dtype=dtype, with_sh=False)
     d = upload(w)
