@@ -228,9 +228,18 @@ class NasgBatchPlan:
     returned by nasg_grad_buffers) and optionally ``rgb`` [V][N][3]. The plan
     keeps references to every tensor it points at; ``run()`` only launches
     kernels and can be captured into a CUDA/HIP graph. ``tile_iters`` and
-    ``blocks_per_cu`` default to the tuner's cached choice (autotune.tune_batch)."""
+    ``blocks_per_cu`` default to the tuner's cached choice (autotune.tune_batch),
+    ``tile_iters`` halved while the scenes give fewer than ``MIN_TILES`` tiles."""
+
+    # A block pulls a tile at a time and 512 are resident (two per CU): with a
+    # few tiles each, the last ones decide the time. 48 scenes of 1e3 to 1e5
+    # primitives (2 000, 3 900, 7 800, 15 600 tiles of 8, 4, 2, 1 passes): 695,
+    # 611, 573, 591 us; 6 scenes of 3.1e4 in all: 251 us in 36 tiles, 46 in 265;
+    # 32 large scenes take 8 passes (18 800 tiles) as well as 2.
+    MIN_TILES = 6144
 
     def __init__(self, scenes, norm="exact", tile_iters=None, blocks_per_cu=None):
+        adapt = tile_iters is None
         if tile_iters is None or blocks_per_cu is None:
             from .autotune import batch_defaults
             dt, db = batch_defaults()
@@ -253,6 +262,8 @@ class NasgBatchPlan:
                                    sc["rgb"].data_ptr() if sc.get("rgb") is not None else None)
             self._keep.append(sc)
         self._scenes = arr
+        if adapt:
+            tile_iters = self._adapted(arr, tile_iters, blocks_per_cu)
         tun = L.NasgBatchTuning(tile_iters, blocks_per_cu)
         nbytes = L.lib().nasg_batched_workspace_bytes(arr, len(scenes), C.byref(tun))
         if nbytes == 0 and len(scenes) > 0:
@@ -263,6 +274,20 @@ class NasgBatchPlan:
         L.check(L.lib().nasg_batched_plan(arr, len(scenes), _norm_code(norm), C.byref(tun),
                                           C.c_void_p(self.workspace.data_ptr()), self.workspace.numel(),
                                           C.byref(self.batch), _stream()), "nasg_batched_plan")
+
+    @classmethod
+    def _adapted(cls, arr, tile_iters, blocks_per_cu) -> int:
+        """``tile_iters`` halved until there are MIN_TILES tiles (or it is 1)."""
+        def size(scenes, ti):
+            return L.lib().nasg_batched_workspace_bytes(
+                scenes, len(scenes), C.byref(L.NasgBatchTuning(ti, blocks_per_cu)))
+        empty = type(arr).from_buffer_copy(arr)     # the plan's size without its tiles
+        for sc in empty:
+            sc.p.n = 0
+        item = 16                                   # bytes of a tile's record
+        while tile_iters > 1 and size(arr, tile_iters) - size(empty, tile_iters) < cls.MIN_TILES * item:
+            tile_iters //= 2
+        return tile_iters
 
     @property
     def n_items(self) -> int:

@@ -70,3 +70,27 @@ def test_family_shapes(family, k, v):
     torch.cuda.synchronize()
     for name, x in g.items():
         compare(x.cpu().numpy(), ref[name], scale[name], name, TOL)
+
+
+@pytest.mark.parametrize("sizes", [[(300, 8, 1), (5000, 4, 16), (0, 8, 4)], [(40_000, 4, 20)] * 3])
+def test_batch_tiles_adapt(sizes):
+    """A plan without a tile size cuts few scenes into small tiles, with the
+    results of a plan of large tiles bit for bit."""
+    plans = []
+    for ti in (None, 8):
+        scenes = []
+        for s, (n, k, v) in enumerate(sizes):
+            d = upload(W.draw_workload(90 + s, n, k, v, with_sh=False))
+            d["grads"] = {q: t.fill_(float("nan")) for q, t in P.nasg_grad_buffers(k, n, "cuda").items()}
+            d["rgb"] = torch.full((v, n, 3), float("nan"), device="cuda")
+            scenes.append(d)
+        plan = P.NasgBatchPlan(scenes, tile_iters=ti)
+        plan.run()
+        plans.append((plan, scenes))
+    torch.cuda.synchronize()
+    assert plans[0][0].n_items > plans[1][0].n_items
+    for a, b in zip(plans[0][1], plans[1][1]):
+        assert torch.equal(a["rgb"], b["rgb"])
+        for q in a["grads"]:
+            assert torch.equal(a["grads"][q], b["grads"][q])
+            assert torch.isfinite(a["grads"][q]).all()
