@@ -447,10 +447,10 @@ const char* nasg_status_string(int status);
  * (1, 4), (2, 1), (2, 2), (2, 4), (4, 1), (4, 2), (4, 4), (8, 1), (8, 2),
  * (16, 1); bcast = 1 (NASGabor kernels 0 and 1 only): (4, 1), (8, 1),
  * (16, 1), (8, 2), (8, 4); others return NASG_ERR_SHAPE. nasg_set_tuning
- * overrides the built-in
- * choice for a (kernel, K, V, dtype) key, which depends on N too (few
- * primitives are spread over more lanes); nasg_get_tuning reports the choice
- * that a call with that key and many primitives would use. kernel: 0 = NASG forward, 1 = NASG
+ * overrides the built-in choice for a (kernel, K, V, dtype) key. The built-in
+ * choice follows N too (few primitives are spread over more lanes), which no
+ * key holds: nasg_get_tuning reports the override, or without one the view
+ * count's reference mapping. kernel: 0 = NASG forward, 1 = NASG
  * backward / fused, 2 = SH forward, 3 = SH backward. K is ignored for SH.
  * lanes = 0 removes an override. Host-side table, not thread-safe against
  * concurrent calls.                                                         */

@@ -152,6 +152,17 @@ nasg_tuning choose(int32_t kernel, int64_t n, int32_t k, int32_t v, int32_t dtyp
   return kernel >= 2 ? sh_shape(kernel == 3, n, v) : nasg_shape(kernel == 1, dtype == NASG_BF16, n, k, v);
 }
 
+// What nasg_get_tuning reports for a key without an override: the reference
+// mapping of the view count, a valid override by itself. Launches without an
+// override follow N, K and the kernel (above).
+nasg_tuning view_count_mapping(int32_t v) {
+  if (v <= 1) return {1, 1, 256, 0};
+  if (v <= 2) return {1, 2, 256, 0};
+  if (v <= 4) return {1, 4, 256, 0};
+  if (v <= 8) return {4, 2, 128, 0};
+  return {4, 4, 128, 0};
+}
+
 int check_views(const nasg_views* vw, int64_t n) {
   if (vw == nullptr) return NASG_ERR_NULL;
   if (vw->v < 1 || vw->v > NASG_MAX_VIEWS) return NASG_ERR_SHAPE;
@@ -397,7 +408,9 @@ int nasg_set_tuning(int32_t kernel, int32_t k, int32_t v, int32_t dtype, const n
 int nasg_get_tuning(int32_t kernel, int32_t k, int32_t v, int32_t dtype, nasg_tuning* t) {
   if (kernel < 0 || kernel > 3) return NASG_ERR_MODE;
   if (t == nullptr) return NASG_ERR_NULL;
-  *t = choose(kernel, 1 << 22, std::max(1, k), std::max(1, v), dtype);  // built-in: at scale
+  const auto& tab = tuning_table();
+  const auto it = tab.find(Key{kernel, kernel >= 2 ? 0 : k, v, kernel >= 2 ? 0 : dtype});
+  *t = it != tab.end() ? it->second : view_count_mapping(v);
   return NASG_OK;
 }
 
