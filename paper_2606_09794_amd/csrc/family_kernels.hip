@@ -51,11 +51,11 @@ __device__ __forceinline__ void family_body(const NasgArgs& a, int64_t prim, int
       const int lo = own ? lc + j : K - 1;
       const int64_t oi = static_cast<int64_t>(lo) * N + i;
       const int64_t wi = static_cast<int64_t>(lo) * 3 * N + i;
-      const float4 q = S::template load4<false>(a.quat, oi);
-      const float4 sh = S::template load4<false>(a.shape, oi);
-      const float w0 = S::template load1<false>(a.rgbw, wi);
-      const float w1 = S::template load1<false>(a.rgbw, wi + N);
-      const float w2 = S::template load1<false>(a.rgbw, wi + 2 * N);
+      const float4 q = S::wide(S::template raw4<false>(a.quat, oi));
+      const float4 sh = S::wide(S::template raw4<false>(a.shape, oi));
+      const float w0 = S::wide(S::template raw1<false>(a.rgbw, wi));
+      const float w1 = S::wide(S::template raw1<false>(a.rgbw, wi + N));
+      const float w2 = S::wide(S::template raw1<false>(a.rgbw, wi + 2 * N));
       double xa[3], za[3], ya[3] = {0.0, 0.0, 0.0};
       float f[6];
       lobe_frame<false>(q, xa, za, f);

@@ -60,30 +60,38 @@ struct Store;
 
 template <>
 struct Store<false> {
+  using Raw4 = f32x4_nt;
+  using Raw1 = float;
+  __device__ static inline float4 wide(Raw4 v) { return make_float4(v.x, v.y, v.z, v.w); }
+  __device__ static inline float wide(Raw1 v) { return v; }
   template <bool ONCE>
-  __device__ static inline float4 load4(const void* p, int64_t idx) {
-    const f32x4_nt v = load_if<ONCE>(reinterpret_cast<const f32x4_nt*>(p) + idx);
-    return make_float4(v.x, v.y, v.z, v.w);
+  __device__ static inline Raw4 raw4(const void* p, int64_t idx) {
+    return load_if<ONCE>(reinterpret_cast<const Raw4*>(p) + idx);
   }
   template <bool ONCE>
-  __device__ static inline float load1(const void* p, int64_t idx) {
+  __device__ static inline Raw1 raw1(const void* p, int64_t idx) {
     return load_if<ONCE>(reinterpret_cast<const float*>(p) + idx);
   }
 };
 
 template <>
 struct Store<true> {
-  // four bfloat16 values packed little-endian in 8 bytes
-  template <bool ONCE>
-  __device__ static inline float4 load4(const void* p, int64_t idx) {
-    const u32x2_nt u = load_if<ONCE>(reinterpret_cast<const u32x2_nt*>(p) + idx);
+  using Raw4 = u32x2_nt;   // four bfloat16 values packed little-endian in 8 bytes
+  using Raw1 = uint16_t;
+  __device__ static inline float4 wide(Raw4 u) {
     return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u),
                        __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u));
   }
-  template <bool ONCE>
-  __device__ static inline float load1(const void* p, int64_t idx) {
-    const uint16_t u = load_if<ONCE>(reinterpret_cast<const uint16_t*>(p) + idx);
+  __device__ static inline float wide(Raw1 u) {
     return __uint_as_float(static_cast<uint32_t>(u) << 16);
+  }
+  template <bool ONCE>
+  __device__ static inline Raw4 raw4(const void* p, int64_t idx) {
+    return load_if<ONCE>(reinterpret_cast<const Raw4*>(p) + idx);
+  }
+  template <bool ONCE>
+  __device__ static inline Raw1 raw1(const void* p, int64_t idx) {
+    return load_if<ONCE>(reinterpret_cast<const uint16_t*>(p) + idx);
   }
 };
 

@@ -84,11 +84,11 @@ __device__ __noinline__ Activated activate_raw(float4 sh, float w0, float w1, fl
 // 8, 3 M x 16 on (8, 2) 2069 -> 1892 us, where (4, 4) at two waves takes 2027; K
 // = 16 in bfloat16, 2 M x 8 on (4, 2) 1580 -> 1398; K = 8, 1.5 M x 2 on (1, 2)
 // 274 -> 240). With four views per lane, or the paper's raw values (six more
-// registers of activation derivatives), the spills cost more than the wave
-// brings; four waves of 128 registers spill too (forward K = 8, 1 M x 1: 139 us
+// registers of activation derivatives; backward, K = 2, 1 M x 1: 98 us at three
+// waves, 87 at two), the spills cost more than the wave brings; four waves of 128 registers spill too (forward K = 8, 1 M x 1: 139 us
 // against 80).
-constexpr int mapping_waves(int lanes, int vpl, bool bc, bool ang) {
-  return bc || (lanes == 1 && vpl == 1) ||
+constexpr int mapping_waves(int lanes, int vpl, bool bc, bool ang, bool bwd) {
+  return bc || (lanes == 1 && vpl == 1 && !(ang && bwd)) ||
                  (vpl <= 2 && !(lanes == 2 && vpl == 2) && (!ang || (lanes == 8 && vpl == 1)))
              ? 3 : 2;
 }
@@ -106,7 +106,7 @@ constexpr int mapping_waves(int lanes, int vpl, bool bc, bool ang) {
 // loaded at once) instead of one lane walking all of them.
 template <int P, int VPL, bool BWD, bool BF16, bool ANG, bool NOCAR = false, bool BC = false,
           bool ONE = false, bool ONCE = false,
-          bool PF = (ONE && (!BWD || P == 1 || VPL == 1)) || mapping_waves(P, VPL, false, ANG) == 2>
+          bool PF = (ONE && (!BWD || P == 1 || VPL == 1)) || mapping_waves(P, VPL, false, ANG, BWD) == 2>
 __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j,
                                           const LogEntry* ltab) {
   using S = Store<BF16>;
@@ -117,7 +117,7 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
   const int K = a.k;
   const int rot_addr = group_next_addr<P>();
   // (two registers each that three waves per SIMD cannot spare)
-  constexpr bool kKeep = mapping_waves(P, VPL, BC, ANG) == 2;
+  constexpr bool kKeep = mapping_waves(P, VPL, BC, ANG, BWD) == 2;
   const double k_c3 = kKeep ? vreg_const(kLog2C3) : kLog2C3;
   const double k_c8 = kKeep ? vreg_const(kExp2C8) : kExp2C8;
 
@@ -141,31 +141,35 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
     // stay in the lane that owns it; a view's colour and direction gradient
     // travel with its slot. A lane with no lobe left (K not a multiple of P)
     // carries a zero normaliser and adds nothing.
-    auto load_rec = [&](int lc_, float4& q_, float4& sh_, float& w0_, float& w1_, float& w2_) {
+    // Records in their storage type: widened where they are used. Widened
+    // where they are loaded, a bfloat16 record is waited for there, and loading
+    // it ahead covers nothing (K = 8, forward 1 M x 4: 174 -> 122 us, x 1 82 ->
+    // 67; K = 16 backward x 2 341 -> 305).
+    using Raw4 = typename S::Raw4;
+    using Raw1 = typename S::Raw1;
+    auto load_rec = [&](int lc_, Raw4& q_, Raw4& sh_, Raw1& w0_, Raw1& w1_, Raw1& w2_) {
       const int lo_ = lc_ + j < K ? lc_ + j : K - 1;
       const int64_t oi_ = static_cast<int64_t>(lo_) * N + i;
-      q_ = S::template load4<ONCE>(a.quat, oi_);
-      sh_ = S::template load4<ONCE>(a.shape, oi_);
-      w0_ = S::template load1<ONCE>(a.rgbw, (static_cast<int64_t>(lo_) * 3 + 0) * N + i);
-      w1_ = S::template load1<ONCE>(a.rgbw, (static_cast<int64_t>(lo_) * 3 + 1) * N + i);
-      w2_ = S::template load1<ONCE>(a.rgbw, (static_cast<int64_t>(lo_) * 3 + 2) * N + i);
+      q_ = S::template raw4<ONCE>(a.quat, oi_);
+      sh_ = S::template raw4<ONCE>(a.shape, oi_);
+      w0_ = S::template raw1<ONCE>(a.rgbw, (static_cast<int64_t>(lo_) * 3 + 0) * N + i);
+      w1_ = S::template raw1<ONCE>(a.rgbw, (static_cast<int64_t>(lo_) * 3 + 1) * N + i);
+      w2_ = S::template raw1<ONCE>(a.rgbw, (static_cast<int64_t>(lo_) * 3 + 2) * N + i);
     };
     // PF: the next lobe group's records are loaded while the current group
     // is evaluated, where the 11 registers are there (at two waves, and in the
     // forward or on one lane with a single chunk: forward K = 8, 1 M x 1 91 ->
     // 82 us, raw values K = 2, 3 M x 1, both directions 311 -> 287).
-    float4 nq, nsh;
-    float nw0, nw1, nw2;
+    Raw4 nq, nsh;
+    Raw1 nw0, nw1, nw2;
     if constexpr (PF) load_rec(0, nq, nsh, nw0, nw1, nw2);
     for (int lc = 0; lc < K; lc += P) {
       const bool own = lc + j < K;
-      float4 q, sh;
-      float w0, w1, w2;
+      if constexpr (!PF) load_rec(lc, nq, nsh, nw0, nw1, nw2);
+      const float4 q = S::wide(nq), sh = S::wide(nsh);
+      float w0 = S::wide(nw0), w1 = S::wide(nw1), w2 = S::wide(nw2);
       if constexpr (PF) {
-        q = nq; sh = nsh; w0 = nw0; w1 = nw1; w2 = nw2;
         if (lc + P < K) load_rec(lc + P, nq, nsh, nw0, nw1, nw2);
-      } else {
-        load_rec(lc, q, sh, w0, w1, w2);
       }
       double xa[3], za[3], lamd, ad, kd;
       // what the gradient write-out needs besides the sums: the frame's own
@@ -391,7 +395,7 @@ template <int P, int VPL, bool BWD, bool BF16, bool ANG, bool NOCAR, bool BC, bo
 // and nothing accumulates onto earlier results, so the lobe records are read and
 // every output is written exactly once, all as streaming data.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
-    mapping_waves(P, VPL, BC, ANG))))
+    mapping_waves(P, VPL, BC, ANG, BWD))))
 void nasg_kernel(const NasgArgs a) {
   static_assert(!ONCE || (P == 1 && ONE), "the streaming flavour: one lane per primitive, one chunk");
   __shared__ LogEntry ltab[kLogEntries];
