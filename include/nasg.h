@@ -339,6 +339,11 @@ typedef struct nasg_gaussians {
  * aligned. */
 size_t nasg_raster_workspace_bytes(int64_t n, const nasg_camera* cam, int32_t tile_capacity);
 
+/* The camera centre -rot^T t (formed in double) as three floats on the device,
+ * the `cams` of an appearance evaluation for this camera: written by a kernel
+ * on `stream`, so that nothing waits for a copy from the host. */
+int nasg_camera_centre(const nasg_camera* cam, float* centre, void* stream);
+
 /* Forward: image[H][W][3] (float32, every pixel written; transmittance and
  * colour sums are carried in FP64, rho in FP32). Leaves the projection, the
  * depth-sorted tile lists and each pixel's final transmittance in

@@ -87,6 +87,7 @@ EXPORTS = {
                                     C.POINTER(NasgBatch), C.c_void_p]),
     "nasg_batched_run": (C.c_int, [C.POINTER(NasgBatch), C.c_void_p]),
     "nasg_raster_workspace_bytes": (C.c_size_t, [C.c_int64, C.POINTER(NasgCamera), C.c_int32]),
+    "nasg_camera_centre": (C.c_int, [C.POINTER(NasgCamera), C.c_void_p, C.c_void_p]),
     "nasg_raster_fwd": (C.c_int, [C.POINTER(NasgGaussians), C.POINTER(NasgCamera), C.c_int32,
                                   C.c_void_p, C.c_size_t, C.c_void_p, C.c_void_p]),
     "nasg_raster_bwd": (C.c_int, [C.POINTER(NasgGaussians), C.POINTER(NasgCamera), C.c_int32,

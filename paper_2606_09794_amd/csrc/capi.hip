@@ -637,6 +637,19 @@ size_t nasg_raster_workspace_bytes(int64_t n, const nasg_camera* cam, int32_t ti
   return raster_layout(n, cam, tile_capacity, &L) ? L.total : 0;
 }
 
+int nasg_camera_centre(const nasg_camera* cam, float* centre, void* stream) {
+  if (cam == nullptr || centre == nullptr) return NASG_ERR_NULL;
+  if (!aligned(centre, 4)) return NASG_ERR_ALIGN;
+  float o[3];
+  for (int i = 0; i < 3; ++i)
+    o[i] = static_cast<float>(
+        -(cam->rot[i] * cam->t[0] + cam->rot[3 + i] * cam->t[1] + cam->rot[6 + i] * cam->t[2]));
+  return nasg::launch_centre(o[0], o[1], o[2], centre, static_cast<hipStream_t>(stream)) ==
+                 hipSuccess
+             ? NASG_OK
+             : NASG_ERR_LAUNCH;
+}
+
 int nasg_raster_fwd(const nasg_gaussians* g, const nasg_camera* cam, int32_t tile_capacity,
                     void* workspace, size_t ws_bytes, float* image, void* stream) {
   nasg::RasterArgs a{};

@@ -1124,6 +1124,17 @@ void raster_render_bwd(RasterArgs a) {
   }
 }
 
+__global__ void raster_centre(float x, float y, float z, float* dst) {
+  dst[0] = x;
+  dst[1] = y;
+  dst[2] = z;
+}
+
+hipError_t launch_centre(float x, float y, float z, float* dst, hipStream_t s) {
+  hipLaunchKernelGGL(raster_centre, dim3(1), dim3(1), 0, s, x, y, z, dst);
+  return hipGetLastError();
+}
+
 __global__ void raster_copy_flag(const int32_t* src, int32_t* dst) { *dst = *src; }
 
 hipError_t launch_copy_flag(const int32_t* src, int32_t* dst, hipStream_t s) {

@@ -106,3 +106,21 @@ def test_list_lengths_with_equal_depths(n):
     compare(img.cpu().numpy(), ref["image"], scale["image"], "image", TOL)
     for name, v in zip(("colors", "opac", "means", "scales", "rots"), out):
         compare(v.cpu().numpy(), ref[name], scale[name], f"grad {name}", TOL)
+
+
+def test_camera_centre_on_the_device_equals_the_host():
+    """The centre written by a kernel is the float32 of the host's FP64 one; a
+    side stream gets it on that stream. FP64 sums of three products in two
+    orders differ by less than 4 * 2^-53 of the terms, float32 rounds to 2^-24."""
+    rng = np.random.default_rng(5)
+    side = torch.cuda.Stream()
+    for i in range(64):
+        rot, _ = np.linalg.qr(rng.standard_normal((3, 3)))
+        t = rng.standard_normal(3) * 10.0 ** rng.integers(-2, 3)
+        cam = P.Camera(rot, t, 100.0, 100.0, 8.0, 8.0, 16, 16)
+        host = cam.centre("cpu").numpy()
+        with torch.cuda.stream(side if i % 2 else torch.cuda.current_stream()):
+            got = cam.centre("cuda").cpu().numpy()
+        assert got.shape == (1, 3) and got.dtype == np.float32
+        tol = 2.0 ** -23 * np.abs(host) + 2.0 ** -51 * np.abs(t).sum()
+        assert np.all(np.abs(got - host) <= tol), (i, got, host)
