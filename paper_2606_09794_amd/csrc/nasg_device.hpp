@@ -342,50 +342,84 @@ __device__ inline void sincos_turns(double t, double& s, double& c) {
 }
 
 // ------------------------------------------- activations (paper's stored values)
-// e^B and e^B - 1 with the series of (e^r - 1)/r to r^12/13! (truncation
-// ~1e-17): for values that feed the lobe frame or the lobe parameters, whose
-// errors the envelope amplifies by up to lam (1 + a). B is clamped to
-// [-1400, 700] (beyond, e^B is 0 or overflows FP64 either way).
-__device__ inline void exp_full(double B, double& eb, double& em1) {
+// They feed the lobe frame and the lobe parameters, whose errors the envelope
+// amplifies by up to lam (1 + a). Polynomials are Taylor series economised on
+// |r| <= ln2/2.
+
+// e^B, B clamped to [-1400, 700] (beyond, e^B is 0 or overflows FP64 either
+// way): 2^n e^r, (e^r - 1)/r to degree 10 (error 2.5e-17).
+__device__ inline double exp_full(double B) {
   B = fmin(fmax(B, -1400.0), 700.0);
   const double n = rint(B * kLog2e);
   double r = fma(-n, kLn2Hi, B);
   r = fma(-n, kLn2Lo, r);
-  double q = 1.0 / 6227020800.0;       // 1/13!
-  q = fma3(q, r, 1.0 / 479001600.0);
-  q = fma3(q, r, 1.0 / 39916800.0);
-  q = fma3(q, r, 1.0 / 3628800.0);
-  q = fma3(q, r, 1.0 / 362880.0);
-  q = fma3(q, r, 1.0 / 40320.0);
-  q = fma3(q, r, 1.0 / 5040.0);
-  q = fma3(q, r, 1.0 / 720.0);
-  q = fma3(q, r, 1.0 / 120.0);
-  q = fma3(q, r, 1.0 / 24.0);
-  q = fma3(q, r, 1.0 / 6.0);
-  q = fma3(q, r, 0.5);
+  double q = 2.5100376916201744e-08;
+  q = fma_vvs(q, r, 2.761379705043833e-07);
+  q = fma_vvs(q, r, 2.7557268477824867e-06);
+  q = fma_vvs(q, r, 2.4801536406057835e-05);
+  q = fma_vvs(q, r, 0.00019841269863042323);
+  q = fma_vvs(q, r, 0.0013888888905873068);
+  q = fma_vvs(q, r, 0.008333333333330063);
+  q = fma_vvs(q, r, 0.041666666666651364);
+  q = fma_vvs(q, r, 0.16666666666666669);
+  q = fma(q, r, 0.5);
   q = fma(q, r, 1.0);
-  eb = ldexp(fma(r, q, 1.0), static_cast<int>(n));
-  em1 = eb - 1.0;
+  return ldexp(fma(r, q, 1.0), static_cast<int>(n));
 }
 
-// tanh u and sech u (= +sqrt(1 - tanh^2 u)) from one exponential q = e^{-|u|}:
+// e^B = num / den for B <= 0 (clamped to -1400): with c = r coth(r/2), even in
+// r, e^r = (c + r)/(c - r), so that the one division of tanh, sech and the
+// logistic serves the exponential too. c to r^10 (error 6e-18), or for values
+// that are rounded to FP32 to r^6 (1e-11).
+template <bool F32>
+__device__ inline void exp_frac(double B, double& num, double& den) {
+  B = fmax(B, -1400.0);
+  const double n = rint(B * kLog2e);
+  double r = fma(-n, kLn2Hi, B);
+  r = fma(-n, kLn2Lo, r);
+  const double z = r * r;
+  double c;
+  if constexpr (F32) {
+    c = fma_vvs(6.584071454936971e-05, z, -0.0027777644224911266);
+    c = fma_vvs(c, z, 0.16666666657759918);
+  } else {
+    c = fma_vvs(4.143774697636149e-08, z, -1.653406021796854e-06);
+    c = fma_vvs(c, z, 6.613756471747488e-05);
+    c = fma_vvs(c, z, -0.002777777777756467);
+    c = fma_vvs(c, z, 0.1666666666666666);
+  }
+  c = fma(c, z, 2.0);
+  num = ldexp(c + r, static_cast<int>(n));
+  den = c - r;
+}
+
+// tanh u and sech u (= +sqrt(1 - tanh^2 u)) from q = e^{-|u|} = num/den:
 // tanh|u| = (1 - q)(1 + q)/(1 + q^2), sech u = 2 q/(1 + q^2); no overflow.
 __device__ inline void tanh_sech(double u, double& t, double& s) {
-  double q, qm1;
-  exp_full(-fabs(u), q, qm1);
-  const double inv = rcp64(fma(q, q, 1.0));
-  t = copysign(-qm1 * (1.0 + q) * inv, u);
-  s = 2.0 * q * inv;
+  double num, den;
+  exp_frac<false>(-fabs(u), num, den);
+  const double inv = rcp64(fma(num, num, den * den));
+  t = copysign((den - num) * (den + num) * inv, u);
+  s = 2.0 * num * den * inv;
+}
+
+// tanh u and its derivative sech^2 u, for a value rounded to FP32.
+__device__ inline void tanh_f32(double u, float& t, float& dt) {
+  double num, den;
+  exp_frac<true>(-2.0 * fabs(u), num, den);
+  const double inv = rcp64(den + num);
+  t = static_cast<float>(copysign((den - num) * inv, u));
+  dt = static_cast<float>(4.0 * (num * inv) * (den * inv));
 }
 
 // k = 20 (tanh u + 1) = 40/(1 + e^{-2u}) and dk/du = 20 sech^2 u
 // = 80 t/(1 + t)^2 with t = e^{-2|u|} (no overflow, no cancellation).
-__device__ inline void k_activation(double u, double& k, double& dk) {
-  double t, tm1;
-  exp_full(-2.0 * fabs(u), t, tm1);
-  const double inv = rcp64(1.0 + t);
-  k = 40.0 * (u >= 0.0 ? 1.0 : t) * inv;
-  dk = 80.0 * t * inv * inv;
+__device__ inline void k_activation(double u, double& k, float& dk) {
+  double num, den;
+  exp_frac<false>(-2.0 * fabs(u), num, den);
+  const double inv = rcp64(den + num);
+  k = 40.0 * (u >= 0.0 ? den : num) * inv;
+  dk = static_cast<float>(80.0 * (num * inv) * (den * inv));
 }
 
 // ------------------------------------------------------------- normaliser

@@ -50,29 +50,39 @@ namespace nasg {
 
 // The paper's raw lobe values activated (Supplementary C): lam = e^u,
 // a = e^u, k = 20 (tanh u + 1), w = tanh u, with the derivatives of k and w.
-// A called function: once per lobe, and kept out of line its FP64 series do
-// not count against the evaluating kernel's registers.
+// With the frame's three cosines they are nine exponentials a lobe, over a
+// third of the instructions of a lobe with one view. Exponentials that a
+// division follows are carried as a fraction, the weights' polynomials stop at
+// what FP32 keeps, and the forward leaves out the derivatives: 270 -> 190 FP64
+// instructions (K = 8, 1 M x 1: forward 223 -> 202 us, backward 301 -> 287).
+// Inlined where two waves per SIMD leave the registers (backward 287 -> 273, x 2
+// 318 -> 299; forward x 2 246 -> 224); at three waves, and with four views per
+// lane in the backward, it would spill (202 -> 284; 374 -> 395) and is called.
 struct Activated {
   double lam, a, k;
   float dk;
   float w[3], dw[3];
 };
-__device__ __noinline__ Activated activate_raw(float4 sh, float w0, float w1, float w2, bool car) {
+template <bool BWD>
+__device__ __forceinline__ Activated activate(float4 sh, float w0, float w1, float w2, bool car) {
   Activated r;
-  double em1, dkd = 0.0;
-  exp_full(sh.x, r.lam, em1);
-  exp_full(sh.y, r.a, em1);
+  r.lam = exp_full(sh.x);
+  r.a = exp_full(sh.y);
   r.k = 0.0;
-  if (car) k_activation(sh.z, r.k, dkd);
-  r.dk = static_cast<float>(dkd);
+  r.dk = 0.f;
+  if (car) k_activation(sh.z, r.k, r.dk);
   const float w[3] = {w0, w1, w2};
   for (int c = 0; c < 3; ++c) {
-    double t, sc;
-    tanh_sech(w[c], t, sc);
-    r.w[c] = static_cast<float>(t);
-    r.dw[c] = static_cast<float>(sc * sc);
+    tanh_f32(w[c], r.w[c], r.dw[c]);
+    if constexpr (!BWD) r.dw[c] = 0.f;
   }
+  if constexpr (!BWD) r.dk = 0.f;
   return r;
+}
+
+template <bool BWD>
+__device__ __noinline__ Activated activate_call(float4 sh, float w0, float w1, float w2, bool car) {
+  return activate<BWD>(sh, w0, w1, w2, car);
 }
 
 // Waves per SIMD that a lane mapping is compiled for. A view slot takes 19
@@ -179,7 +189,9 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
       float dlam_du = 1.f, da_du = 1.f, dk_du = 1.f, dw0 = 1.f, dw1 = 1.f, dw2 = 1.f;
       lobe_frame<ANG>(q, xa, za, f);
       if constexpr (ANG) {
-        const Activated act = activate_raw(sh, w0, w1, w2, !NOCAR);
+        constexpr bool kInline = kKeep && (!BWD || VPL <= 2);
+        const Activated act = kInline ? activate<BWD>(sh, w0, w1, w2, !NOCAR)
+                                      : activate_call<BWD>(sh, w0, w1, w2, !NOCAR);
         lamd = act.lam;
         ad = act.a;
         kd = act.k;

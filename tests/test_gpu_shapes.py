@@ -94,3 +94,34 @@ def test_batch_tiles_adapt(sizes):
         for q in a["grads"]:
             assert torch.equal(a["grads"][q], b["grads"][q])
             assert torch.isfinite(a["grads"][q]).all()
+
+
+@pytest.mark.parametrize("v", [1, 2, 4, 16])
+def test_raw_activations_over_their_range(v):
+    """The paper's raw values from denormal to saturated, on both sides of the
+    exponential's reduction steps: called and inlined activations (by the views
+    per lane and the direction) against the oracle at the same bar. The colours
+    and the gradients of the weights and c0, whose terms stay in FP32's range: a
+    weight of 1e-30 leaves the others' below it."""
+    n, k = 1500, 8
+    w = W.draw_workload(900 + v, n, k, v, param="angles", with_sh=False)
+    rng = np.random.default_rng(v)
+    step = 0.5 * np.log(2.0)
+    edges = np.array([0.0, 1e-30, 1e-8, 1e-4, 0.5 * step, 0.999 * step, 1.001 * step, 3 * step, 1.0,
+                      5.0, 18.0, 40.0, 380.0, 1e4])
+    pick = lambda size: (rng.choice(edges, size) * rng.choice([-1.0, 1.0], size)).astype(np.float32)  # noqa: E731
+    w.rgbw[:] = pick(w.rgbw.shape)
+    w.shape[..., 2] = pick(w.shape.shape[:-1])
+    w.quat[..., :3] = np.where(rng.random(w.quat[..., :3].shape) < 0.3,
+                               np.clip(pick(w.quat[..., :3].shape), -5.0, 5.0), w.quat[..., :3])
+    d = upload(w)
+    rgb = P.nasg_eval_fwd(d["quat"], d["shape"], d["rgbw"], d["c0"], means=d["means"], cams=d["cams"],
+                          param="angles")
+    fused = torch.empty_like(rgb)
+    g = P.nasg_eval_bwd(d["quat"], d["shape"], d["rgbw"], d["c0"], d["grad_rgb"], means=d["means"],
+                        cams=d["cams"], param="angles", rgb_out=fused)
+    ref, scale = oracle_nasg(w, "exact")
+    compare(rgb.cpu().numpy(), ref["rgb"], scale["rgb"], "rgb", TOL)
+    compare(fused.cpu().numpy(), ref["rgb"], scale["rgb"], "rgb (fused)", TOL)
+    for name in ("rgbw", "c0"):
+        compare(g[name].cpu().numpy(), ref[name], scale[name], name, TOL)
