@@ -71,8 +71,15 @@ int pow2_at_least(int x) {
   return p;
 }
 
+// Threads per block: 64 while a wavefront has a SIMD to itself, 256 where there
+// are many (every block builds the logarithm table); four lanes between with 128
+// (K = 2, V = 16, N = 48 000: 24.0 against 24.6 us; one lane is faster with 256
+// there, whose four wavefronts land on the four SIMDs of a CU: K = 8, V = 4
+// 23.4 against 29.4 at 33 000).
 nasg_tuning shape_of(int64_t n, int lanes, int vpl, int bcast = 0) {
-  return {lanes, vpl, n * lanes <= 32768 ? 64 : 256, bcast};
+  const int64_t all = n * lanes;
+  const int block = all <= 32768 ? 64 : lanes == 4 && bcast == 0 && all <= 524288 ? 128 : 256;
+  return {lanes, vpl, block, bcast};
 }
 
 // The mapping that fills the chip best when there are primitives enough, also
@@ -85,10 +92,16 @@ nasg_tuning shape_of(int64_t n, int lanes, int vpl, int bcast = 0) {
 // us). One lane in several passes costs 1.4 times four lanes that all have a
 // lobe, so it serves K = 1, 2 and 5 up to eight views (K = 1, N = 1.5 M, V = 8:
 // 355 -> 236; K = 2 375 -> 320; forward K = 1 188 -> 78) and K = 1 beyond
-// (V = 16: 572 -> 459; K = 2 stays, 570 against 640).
-void mapping_at_scale(int k, int v, int* lanes, int* vpl) {
+// (V = 16: 572 -> 459; K = 2 stays, 570 against 640), given primitives enough
+// to fill the chip with one lane each: K = 1, V = 16 16.1 against 20.7 us at
+// 20 000, 22 against 20 at 33 000; K = 2, V = 8 22 against 25 at 70 000, 30
+// against 28 at 105 000; with raw values, whose activations a spread primitive
+// shares out, 51 against 57 at 160 000. (N enters here and not only in
+// nasg_shape because the persistent batch follows the same rule.)
+void mapping_at_scale(int64_t n, int k, int v, bool raw, int* lanes, int* vpl) {
   const int four = (k + 3) / 4 * 4;
-  if (v <= 4 || k == 1 || (v <= 8 && 7 * k < 5 * four)) {
+  if (v <= 4 || (k == 1 && (v <= 8 || n > 24576)) ||
+      (v <= 8 && 7 * k < 5 * four && n > (raw ? 196608 : 98304))) {
     *lanes = 1;
     *vpl = v <= 1 ? 1 : v <= 2 ? 2 : 4;
     return;
@@ -105,9 +118,9 @@ void mapping_at_scale(int k, int v, int* lanes, int* vpl) {
 // bit, so only mappings that sum in the order of the mapping at scale serve:
 // for up to four views the forward's broadcast mappings, whose colours are
 // summed in lobe order.
-nasg_tuning nasg_shape(bool bwd, bool bf16, int64_t n, int k, int v) {
+nasg_tuning nasg_shape(bool bwd, bool bf16, int64_t n, int k, int v, bool raw) {
   int lanes, vpl;
-  mapping_at_scale(k, v, &lanes, &vpl);
+  mapping_at_scale(n, k, v, raw, &lanes, &vpl);
   const nasg_tuning scale = shape_of(n, lanes, vpl);
   if (bwd && !bf16) return scale;
   const int kp = std::min(16, pow2_at_least(k));
@@ -130,26 +143,50 @@ nasg_tuning nasg_shape(bool bwd, bool bf16, int64_t n, int k, int v) {
   return k >= 16 && fits(16, 2 * kFillLanes) ? shape_of(n, 16, 1) : scale;
 }
 
-// SH-3: every lane of a primitive would load all 48 coefficients, so one lane
+// SH-3: every lane of a primitive loads all 48 coefficients, so one lane
 // wherever the primitives fill the chip (backward, N = 1.5 M, V = 16: 344 ->
-// 240 us against four lanes; forward 161 -> 110), and more only for few.
+// 240 us against four lanes; forward 161 -> 110), and more only for few. The
+// lines are where the next mapping is faster on either side, over V in {6, 8,
+// 12, 16, 24, 32, 40} and N from 9000 to 520 000: backward, V = 16: four lanes
+// against two 13.3 / 14.0 us at 40 000 and 18.8 / 14.4 at 55 000, two against
+// one 18.3 / 20.1 at 70 000 and 26.7 / 19.8 at 100 000; V = 40: two against one
+// 52 / 55 at 150 000, four against two 42.4 / 44.7 at 100 000 (two leave a last
+// round nearly empty there); forward, V = 32: eight against four 8.7 / 8.9 at
+// 33 000, four against one 12.8 / 15.3 at 70 000 and 19.5 / 15.6 at 100 000.
 nasg_tuning sh_shape(bool bwd, int64_t n, int v) {
-  const int vp = std::min(16, pow2_at_least(v));
   int p = 1;
-  if (!bwd || v > 4) {
-    const int64_t fill = bwd && v < 16 ? kFillLanes / 2 : kFillLanes;
-    while (2 * p <= vp && n * 2 * p <= fill) p *= 2;
-    if (p == 1 && bwd && v >= 16 && n * 2 <= 4 * kFillLanes) p = 2;
+  if (n <= 8192) {
+    p = bwd && v <= 4 ? 1 : 16;
+  } else if (bwd && v > 8) {
+    if (n <= 20480 && v >= 24) p = 8;
+    else if (n <= 49152) p = 4;
+    else if (n <= (v < 16 ? 65536 : 81920)) p = 2;
+    else if (v >= 32 && n <= 114688) p = 4;
+    else if (v >= 24 && n > 114688 && n <= 262144) p = 2;
+  } else if (bwd) {
+    if (v > 4) p = n <= 16384 ? 4 : n <= 45056 ? 2 : 1;
+  } else if (v > 8) {
+    p = n <= (v >= 24 ? 36864 : 20480) ? 8 : n <= (v >= 24 ? 73728 : 45056) ? 4
+        : n <= 73728 ? 2 : 1;
+  } else {
+    p = n <= 16384 ? 8 : n <= 32768 ? 4 : n <= 73728 ? 2 : 1;
   }
+  p = std::min(p, std::min(16, pow2_at_least(v)));
   const int most = p >= 16 ? 1 : p >= 8 ? 2 : 4;
-  return shape_of(n, p, std::min(most, pow2_at_least((v + p - 1) / p)));
+  nasg_tuning t = shape_of(n, p, std::min(most, pow2_at_least((v + p - 1) / p)));
+  // the forward's long launches: V = 16, N = 520 000 39.6 against 44.4 us
+  if (!bwd && p == 1 && n > 393216) t.block = 128;
+  return t;
 }
 
-nasg_tuning choose(int32_t kernel, int64_t n, int32_t k, int32_t v, int32_t dtype) {
+nasg_tuning choose(int32_t kernel, int64_t n, int32_t k, int32_t v, int32_t dtype,
+                   int32_t param = NASG_PARAM_QUAT) {
   const auto& tab = tuning_table();
   auto it = tab.find(Key{kernel, kernel >= 2 ? 0 : k, v, kernel >= 2 ? 0 : dtype});
   if (it != tab.end()) return it->second;
-  return kernel >= 2 ? sh_shape(kernel == 3, n, v) : nasg_shape(kernel == 1, dtype == NASG_BF16, n, k, v);
+  return kernel >= 2 ? sh_shape(kernel == 3, n, v)
+                     : nasg_shape(kernel == 1, dtype == NASG_BF16, n, k, v,
+                                  param == NASG_PARAM_ANGLES);
 }
 
 // What nasg_get_tuning reports for a key without an override: the reference
@@ -225,9 +262,9 @@ int check_grad_ptrs(const float* grad_rgb, const nasg_grads* g, const float* rgb
 // A scene's lane mapping in the persistent batch: the tuning table's choice
 // for its (K, V) when the batch kernel carries that mapping, else the mapping
 // at scale (all of those are carried); plus kBatchVariants for the paper's raw values.
-int batch_variant(int32_t k, int32_t v, int32_t param) {
+int batch_variant(int64_t n, int32_t k, int32_t v, int32_t param) {
   int lanes, vpl, var = 0;
-  mapping_at_scale(k, v, &lanes, &vpl);
+  mapping_at_scale(n, k, v, param == NASG_PARAM_ANGLES, &lanes, &vpl);
   const auto& tab = tuning_table();
   const auto it = tab.find(Key{1, k, v, NASG_F32});   // kernel 1: the NASG backward
   for (int c = 0; c < nasg::kBatchVariants; ++c)
@@ -253,7 +290,7 @@ BatchLayout batch_layout(const nasg_scene* sc, int32_t n, int32_t tile_iters) {
   BatchLayout L{};
   L.items_off = align_up(sizeof(nasg::BatchHeader) + sizeof(nasg::BatchScene) * n, 64);
   for (int32_t s = 0; s < n; ++s) {
-    const int64_t tile = static_cast<int64_t>(tile_iters) * (256 / nasg::kBatchLanes[batch_variant(sc[s].p.k, sc[s].views.v, sc[s].p.param)]);
+    const int64_t tile = static_cast<int64_t>(tile_iters) * (256 / nasg::kBatchLanes[batch_variant(sc[s].p.n, sc[s].p.k, sc[s].views.v, sc[s].p.param)]);
     L.n_items += (sc[s].p.n + tile - 1) / tile;
   }
   L.total = L.items_off + sizeof(nasg::BatchItem) * static_cast<size_t>(L.n_items);
@@ -426,7 +463,7 @@ int nasg_eval_fwd(const nasg_params* p, const nasg_views* views, float* rgb, int
   NasgArgs a = make_args(p, views);
   a.rgb = rgb;
   a.norm = norm;
-  const nasg_tuning t = choose(0, p->n, p->k, views->v, p->dtype);
+  const nasg_tuning t = choose(0, p->n, p->k, views->v, p->dtype, p->param);
   const hipError_t e = nasg::launch_nasg(a, t.lanes, t.views_per_lane, t.bcast != 0, false,
                                          p->dtype == NASG_BF16, t.block,
                                          static_cast<hipStream_t>(stream));
@@ -454,7 +491,7 @@ int nasg_eval_bwd(const nasg_params* p, const nasg_views* views, const float* gr
   a.g_geom = g->geom;
   a.norm = norm;
   a.accumulate = grad_mode == NASG_GRAD_ACCUMULATE;
-  const nasg_tuning t = choose(1, p->n, p->k, views->v, p->dtype);
+  const nasg_tuning t = choose(1, p->n, p->k, views->v, p->dtype, p->param);
   const hipError_t e = nasg::launch_nasg(a, t.lanes, t.views_per_lane, t.bcast != 0, true,
                                          p->dtype == NASG_BF16, t.block,
                                          static_cast<hipStream_t>(stream));
@@ -577,7 +614,7 @@ int nasg_batched_plan(const nasg_scene* scenes, int32_t n_scenes, int32_t norm,
     a.norm = norm;
     a.accumulate = 0;
     bs[s].args = a;
-    bs[s].variant = batch_variant(sc.p.k, sc.views.v, sc.p.param);
+    bs[s].variant = batch_variant(sc.p.n, sc.p.k, sc.views.v, sc.p.param);
     bs[s].tile_iters = tt.tile_iters;
     const int64_t tile = static_cast<int64_t>(tt.tile_iters) * (256 / nasg::kBatchLanes[bs[s].variant]);
     for (int64_t st0 = 0; st0 < sc.p.n; st0 += tile) {

@@ -43,8 +43,8 @@ def test_nasg_shapes(n, k, v, dtype):
         compare(x.cpu().numpy(), ref[name], scale[name], name, TOL)
 
 
-@pytest.mark.parametrize("n", [1, 4097, 16385, 131073])
-@pytest.mark.parametrize("v", [1, 3, 7, 16, 33])
+@pytest.mark.parametrize("n", [1, 4097, 8193, 16385, 36865, 45057, 73729, 131073])
+@pytest.mark.parametrize("v", [1, 3, 7, 13, 16, 33])
 def test_sh_shapes(n, v):
     w = W.draw_workload(n + v, n, 1, v)
     d = upload(w)
@@ -94,6 +94,33 @@ def test_batch_tiles_adapt(sizes):
         for q in a["grads"]:
             assert torch.equal(a["grads"][q], b["grads"][q])
             assert torch.isfinite(a["grads"][q]).all()
+
+
+@pytest.mark.parametrize("n,k,v,param", [(24576, 1, 16, "quat"), (24577, 1, 16, "quat"),
+                                         (98304, 2, 8, "quat"), (98305, 2, 8, "quat"),
+                                         (196608, 2, 7, "angles"), (196609, 2, 7, "angles")])
+def test_batch_follows_the_shape_by_n(n, k, v, param):
+    """On both sides of the lines in N a scene in a batch equals its own launch
+    bit for bit, beside a small scene of the same K and V."""
+    scenes = []
+    for m in (n, 700):
+        w = W.draw_workload(m % 1000 + k, m, k, v, param=param, with_sh=False)
+        d = upload(w)
+        d["param"] = param
+        d["grads"] = {q: t.fill_(float("nan")) for q, t in P.nasg_grad_buffers(k, m, "cuda").items()}
+        d["rgb"] = torch.full((v, m, 3), float("nan"), device="cuda")
+        scenes.append(d)
+    P.NasgBatchPlan(scenes).run()
+    for d in scenes:
+        rgb = torch.empty_like(d["rgb"])
+        g = P.nasg_eval_bwd(d["quat"], d["shape"], d["rgbw"], d["c0"], d["grad_rgb"], means=d["means"],
+                            cams=d["cams"], param=param, rgb_out=rgb)
+        fwd = P.nasg_eval_fwd(d["quat"], d["shape"], d["rgbw"], d["c0"], means=d["means"],
+                              cams=d["cams"], param=param)
+        torch.cuda.synchronize()
+        assert torch.equal(d["rgb"], rgb) and torch.equal(rgb, fwd)
+        for q in g:
+            assert torch.equal(d["grads"][q], g[q]), q
 
 
 @pytest.mark.parametrize("v", [1, 2, 4, 16])
