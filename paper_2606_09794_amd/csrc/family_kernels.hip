@@ -86,10 +86,15 @@ __device__ __forceinline__ void family_body(const NasgArgs& a, int64_t prim, int
       const float sc_a = static_cast<float>(-4.0 * p0 * rcp64(omr2));
       const float xf[3] = {static_cast<float>(xa[0]), static_cast<float>(xa[1]),
                            static_cast<float>(xa[2])};
-      const float yf[3] = {static_cast<float>(ya[0]), static_cast<float>(ya[1]),
-                           static_cast<float>(ya[2])};
       const float zf[3] = {static_cast<float>(za[0]), static_cast<float>(za[1]),
                            static_cast<float>(za[2])};
+
+      // ASG: s_x = -2 mu (x.d) G and s_y alike; the factor -2 mu is in xs and
+      // where ax is used, so that a lobe-view takes one product for each axis
+      const float xs[3] = {static_cast<float>(-2.0 * p0 * xa[0]), static_cast<float>(-2.0 * p0 * xa[1]),
+                           static_cast<float>(-2.0 * p0 * xa[2])};
+      const float ys[3] = {static_cast<float>(-2.0 * p1 * ya[0]), static_cast<float>(-2.0 * p1 * ya[1]),
+                           static_cast<float>(-2.0 * p1 * ya[2])};
 
       float acc_w0 = 0.f, acc_w1 = 0.f, acc_w2 = 0.f, acc_G = 0.f, acc_p0 = 0.f, acc_p1 = 0.f;
       float ax[3] = {0.f, 0.f, 0.f}, ay[3] = {0.f, 0.f, 0.f}, az[3] = {0.f, 0.f, 0.f};
@@ -101,7 +106,7 @@ __device__ __forceinline__ void family_body(const NasgArgs& a, int64_t prim, int
           const double* d = sl.dd[t];
           const double dzd = d[0] * za[0] + d[1] * za[1] + d[2] * za[2];
           const double hd = 1.0 - dzd;
-          float G = 0.f, sx = 0.f, sy = 0.f, sz = 0.f, g0 = 0.f, g1 = 0.f;
+          float G = 0.f, dx = 0.f, dy = 0.f, sz = 0.f, g0 = 0.f;
           if constexpr (FAM == kFamSg) {
             // exponent lam (z.d - 1) = -lam h, FP64 (p0s, p1s: in units of ln 2)
             G = Nn * exp2_neg(-p0s * hd);
@@ -138,14 +143,10 @@ __device__ __forceinline__ void family_body(const NasgArgs& a, int64_t prim, int
             const double dxd = d[0] * xa[0] + d[1] * xa[1] + d[2] * xa[2];
             const double dyd = d[0] * ya[0] + d[1] * ya[1] + d[2] * ya[2];
             const float e = exp2_neg(-(p0s * dxd * dxd + p1s * dyd * dyd));
-            const bool live = dzd > 0.0;
-            const float dx = static_cast<float>(dxd), dy = static_cast<float>(dyd);
-            G = live ? Nn * static_cast<float>(dzd) * e : 0.f;
-            sz = live ? Nn * e : 0.f;
-            sx = -2.f * p0f * dx * G;
-            sy = -2.f * p1f * dy * G;
-            g0 = -dx * dx * G;
-            g1 = -dy * dy * G;
+            dx = static_cast<float>(dxd);
+            dy = static_cast<float>(dyd);
+            sz = dzd > 0.0 ? Nn * e : 0.f;
+            G = sz * static_cast<float>(dzd);
           }
           sl.col[t][0] = fmaf(w0, G, sl.col[t][0]);
           sl.col[t][1] = fmaf(w1, G, sl.col[t][1]);
@@ -156,26 +157,35 @@ __device__ __forceinline__ void family_body(const NasgArgs& a, int64_t prim, int
             acc_w0 = fmaf(r0, G, acc_w0);
             acc_w1 = fmaf(r1, G, acc_w1);
             acc_w2 = fmaf(r2, G, acc_w2);
-            acc_G = fmaf(gG, G, acc_G);
-            acc_p0 = fmaf(gG, g0, acc_p0);
-            acc_p1 = fmaf(gG, g1, acc_p1);
-            const float gsx = gG * sx, gsy = gG * sy, gsz = gG * sz;
+            const float gsz = gG * sz;
+            if constexpr (FAM == kFamAsg) {
+              const float qG = gG * G;
+              const float vx = qG * dx, vy = qG * dy;
+              acc_p0 = fmaf(-vx, dx, acc_p0);
+              acc_p1 = fmaf(-vy, dy, acc_p1);
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-              const float dc = sl.df[t][c];
-              az[c] = fmaf(gsz, dc, az[c]);
-              if constexpr (FAM == kFamAsg) {
-                ax[c] = fmaf(gsx, dc, ax[c]);
-                ay[c] = fmaf(gsy, dc, ay[c]);
-                sl.gdir[t][c] = fmaf(gsx, xf[c], fmaf(gsy, yf[c], fmaf(gsz, zf[c], sl.gdir[t][c])));
-              } else {
+              for (int c = 0; c < 3; ++c) {
+                const float dc = sl.df[t][c];
+                ax[c] = fmaf(vx, dc, ax[c]);
+                ay[c] = fmaf(vy, dc, ay[c]);
+                az[c] = fmaf(gsz, dc, az[c]);
+                sl.gdir[t][c] = fmaf(vx, xs[c], fmaf(vy, ys[c], fmaf(gsz, zf[c], sl.gdir[t][c])));
+              }
+            } else {
+              if constexpr (FAM == kFamSg || FAM == kFamSb) acc_G = fmaf(gG, G, acc_G);
+              acc_p0 = fmaf(gG, g0, acc_p0);
+#pragma unroll
+              for (int c = 0; c < 3; ++c) {
+                az[c] = fmaf(gsz, sl.df[t][c], az[c]);
                 sl.gdir[t][c] = fmaf(gsz, zf[c], sl.gdir[t][c]);
               }
             }
           }
           if constexpr (P > 1) {
             slot_pass<P, VPL, BWD>(sl, t, rot_addr);
-            __builtin_amdgcn_sched_barrier(0);
+            // SG and SC: one view's registers at a time (K = 4, backward, 1 M x
+            // 4, SC: 117 us, 127 without); ASG and SB are faster free (131 -> 121)
+            if constexpr (FAM == kFamSg || FAM == kFamSc) __builtin_amdgcn_sched_barrier(0);
           }
         }
       }
@@ -189,6 +199,12 @@ __device__ __forceinline__ void family_body(const NasgArgs& a, int64_t prim, int
           if (a.g_quat != nullptr) {
             float gx[3] = {ax[0], ax[1], ax[2]}, gz[3] = {az[0], az[1], az[2]};
             if constexpr (FAM == kFamAsg) {
+              const float m0 = -2.f * p0f, m1 = -2.f * p1f;
+#pragma unroll
+              for (int c = 0; c < 3; ++c) {
+                gx[c] *= m0;
+                ay[c] *= m1;
+              }
               // y = z x x: dL/dx += dL/dy x z, dL/dz += x x dL/dy
               gx[0] += ay[1] * zf[2] - ay[2] * zf[1];
               gx[1] += ay[2] * zf[0] - ay[0] * zf[2];
@@ -208,6 +224,10 @@ __device__ __forceinline__ void family_body(const NasgArgs& a, int64_t prim, int
   }
 }
 
+// Bound by the latency of passing the view slots on: 18 ds_bpermute per
+// lobe-view (48 % of the LDS cycles) beside 62 VALU instructions (57 % of the
+// issue slots), ASG, K = 8, 200 003 x 16 backward, at three waves per SIMD. A
+// fourth wave (128 registers) spills 56 bytes: 107 against 99 us.
 template <int P, int VPL, bool BWD, bool BF16, int FAM>
 __global__ __launch_bounds__(256) void family_kernel(const NasgArgs a) {
   __shared__ LogEntry ltab[kLogEntries];
