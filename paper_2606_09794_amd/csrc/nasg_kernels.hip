@@ -95,8 +95,8 @@ __device__ __noinline__ Activated activate_call(float4 sh, float w0, float w1, f
 // = 16 in bfloat16, 2 M x 8 on (4, 2) 1580 -> 1398; K = 8, 1.5 M x 2 on (1, 2)
 // 274 -> 240). With four views per lane, or the paper's raw values (six more
 // registers of activation derivatives; backward, K = 2, 1 M x 1: 98 us at three
-// waves, 87 at two), the spills cost more than the wave brings; four waves of 128 registers spill too (forward K = 8, 1 M x 1: 139 us
-// against 80).
+// waves, 87 at two), the spills cost more than the wave brings; four waves of
+// 128 registers spill too (forward K = 8, 1 M x 1: 139 us against 80).
 constexpr int mapping_waves(int lanes, int vpl, bool bc, bool ang, bool bwd) {
   return bc || (lanes == 1 && vpl == 1 && !(ang && bwd)) ||
                  (vpl <= 2 && !(lanes == 2 && vpl == 2) && (!ang || (lanes == 8 && vpl == 1)))
