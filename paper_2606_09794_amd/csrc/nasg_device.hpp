@@ -293,28 +293,38 @@ __device__ inline float exp2_neg(double y) {
   return ldexpf(p, sat_int(n));
 }
 
-// sin(pi x/2) and cos(pi x/2) in FP32 for |x| <= 1/2: minimax polynomials in
-// x^2 (own Remez fits for relative error: 3.2e-9 for sine over x, 6.4e-11 for
-// cosine with its constant fixed at 1). Maximum error with FP32 rounding
-// 1.3e-7 and 8.1e-8, against 1.4e-7 and 1.1e-7 of the Taylor series to y^9 and
-// y^10 in y = pi x/2, which take three instructions more.
-__device__ inline void sincos_halfpi(float x, float& s, float& c) {
-  const float z = x * x;
-  float ps = -0.0046016578911805455f;
-  ps = fmaf(ps, z, 0.07968003277042174f);
-  ps = fmaf(ps, z, -0.645963460233428f);
-  ps = fmaf(ps, z, 1.5707963217083447f);
-  s = x * ps;
-  float pc = 0.0009037665432423369f;
-  pc = fmaf(pc, z, -0.02086016511147022f);
-  pc = fmaf(pc, z, 0.25366922596549085f);
-  pc = fmaf(pc, z, -1.2337005425976675f);
-  c = fmaf(z, pc, 1.f);
+// Half phase of the carrier in units of pi, reduced to r in [-1/2, 1/2), given as
+// f = r + 1/2: cos(pi r) = pi v (1 + uc) and sin(pi r) = 2 r (1 + us) with v =
+// f (1 - f) (one FP64 rounding, so relatively accurate next to the cosine's zeros
+// at both ends). uc = v + O(v^2) and us = 2 v + O(v^2) are at most 0.28 and 0.58 and
+// vanish at those zeros, so FP32 holds them: own Remez fits with the leading
+// coefficients fixed at 1 and 2, 1.9e-9 and 1.0e-8 relative to cosine and sine,
+// 3e-8 and 6e-8 at most (rms 6e-9 and 1.3e-8) with their FP32 rounding.
+__device__ __forceinline__ float cos_pi_u(float v) {
+  float u = fmaf(v, 0.007639229607417381f, 0.06514647357787971f);
+  u = fmaf(u, v, 0.35506860612312846f);
+  return v * fmaf(u, v, 1.f);
+}
+__device__ __forceinline__ float sin_pi_u(float v) {
+  float u = fmaf(v, 0.03848935620413844f, 0.2604881783097619f);
+  u = fmaf(u, v, 1.0652133403459647f);
+  return v * fmaf(u, v, 2.f);
+}
+
+// (pi/2) tan(pi x) in FP64, x given as x + 1/2.
+__device__ inline double tan_pi(double xh) {
+  const double f = __builtin_amdgcn_fract(xh);
+  const double v = fma(-f, f, f), r = f - 0.5;
+  const float vf = static_cast<float>(v);
+  const double c = fma(v, static_cast<double>(cos_pi_u(vf)), v);
+  return fma(r, static_cast<double>(sin_pi_u(vf)), r) * rcp64(c);
 }
 
 // sin(2 pi t) and cos(2 pi t) in FP64 for any t: t is reduced to the nearest
 // integer and quarter turn, leaving |r| <= pi/4 for the Taylor series
-// (sine to r^13, cosine to r^14; truncation below 1e-14).
+// (sine to r^13, cosine to r^14; truncation below 1e-14). Scalar constants: only
+// lobes with a fast carrier come here, and in vector registers the dozen would be
+// kept through the lobe loops.
 __device__ inline void sincos_turns(double t, double& s, double& c) {
   constexpr double kTwoPi = 6.283185307179586476925286766559005768;
   const double f = t - rint(t);
@@ -322,19 +332,19 @@ __device__ inline void sincos_turns(double t, double& s, double& c) {
   const double r = (f - 0.25 * qd) * kTwoPi;
   const double z = r * r;
   double ps = 1.0 / 6227020800.0;      // 1/13!
-  ps = fma3(ps, z, -1.0 / 39916800.0);
-  ps = fma3(ps, z, 1.0 / 362880.0);
-  ps = fma3(ps, z, -1.0 / 5040.0);
-  ps = fma3(ps, z, 1.0 / 120.0);
-  ps = fma3(ps, z, -1.0 / 6.0);
+  ps = fma_vvs(ps, z, -1.0 / 39916800.0);
+  ps = fma_vvs(ps, z, 1.0 / 362880.0);
+  ps = fma_vvs(ps, z, -1.0 / 5040.0);
+  ps = fma_vvs(ps, z, 1.0 / 120.0);
+  ps = fma_vvs(ps, z, -1.0 / 6.0);
   const double sr = fma(ps * z, r, r);
   double pc = 1.0 / 87178291200.0;     // 1/14!
-  pc = fma3(pc, z, -1.0 / 479001600.0);
-  pc = fma3(pc, z, 1.0 / 3628800.0);
-  pc = fma3(pc, z, -1.0 / 40320.0);
-  pc = fma3(pc, z, 1.0 / 720.0);
-  pc = fma3(pc, z, -1.0 / 24.0);
-  pc = fma3(pc, z, 0.5);
+  pc = fma_vvs(pc, z, -1.0 / 479001600.0);
+  pc = fma_vvs(pc, z, 1.0 / 3628800.0);
+  pc = fma_vvs(pc, z, -1.0 / 40320.0);
+  pc = fma_vvs(pc, z, 1.0 / 720.0);
+  pc = fma_vvs(pc, z, -1.0 / 24.0);
+  pc = fma_vvs(pc, z, 0.5);
   const double cr = fma(-pc, z, 1.0);
   const int q = static_cast<int>(qd) & 3;
   s = (q == 0) ? sr : (q == 1) ? cr : (q == 2) ? -sr : -cr;
@@ -427,7 +437,8 @@ __device__ inline void k_activation(double u, double& k, float& dk) {
 struct LobeNorm {
   float n;        // normaliser value
   float dl, da;   // d ln N / d lambda, d ln N / d a
-  float dk, dz;   // d ln N / d k, d ln N / d zeta (zero for the NASG normaliser)
+  float dk;       // d ln N / d k, and (pi/2) d ln N / d zeta (both zero for the
+  double dz;      // NASG normaliser), the latter in FP64: see lobe_norm_f32
 };
 
 // Psi(Lam, k) = 2 Lam e^{-Lam} S(r) / (1 - e^{-2 Lam}) of the closed-form
@@ -507,7 +518,10 @@ __device__ inline void psi_partials(double L, double k, double iL, double& psi,
 //         B = 1 + cos(zeta) Psi, which FP64 keeps relatively accurate down to
 //         B ~ 1e-9 (zeta within ~5e-5 of pi with Psi -> 1);
 // mode 1: NASG normaliser lambda sqrt(1+a) / (2 pi (1 - e^{-2 lambda})).
+// UNIT: whether n comes times pi^2, the unit of the kernels' carrier.
+template <bool UNIT = false>
 __device__ inline LobeNorm lobe_norm(double lam, double a, double kd, double zd, int mode) {
+  constexpr double unit = UNIT ? kPi * kPi : 1.0;
   double e2l, em1_2l;
   exp_em1<true>(-2.0 * lam, e2l, em1_2l);
   const double dlam = -em1_2l;                    // 1 - e^{-2 lam}, relatively accurate
@@ -520,11 +534,11 @@ __device__ inline LobeNorm lobe_norm(double lam, double a, double kd, double zd,
   const double da_base = 0.5 * ia;
   LobeNorm out;
   if (mode == 1) {
-    out.n = static_cast<float>(lam * sq * idl * (0.5 / kPi));
+    out.n = static_cast<float>(lam * sq * idl * (0.5 / kPi * unit));
     out.dl = static_cast<float>(dl_base);
     out.da = static_cast<float>(da_base);
     out.dk = 0.f;
-    out.dz = 0.f;
+    out.dz = 0.0;
     return out;
   }
   const double L = lam * (1.0 + a);
@@ -535,14 +549,13 @@ __device__ inline LobeNorm lobe_norm(double lam, double a, double kd, double zd,
   const double B = fma(cz, psi, 1.0);
   const double iB = rcp64(B);
   const double czB = cz * iB;
-  out.n = static_cast<float>(lam * sq * idl * iB * (1.0 / kPi));
+  out.n = static_cast<float>(lam * sq * idl * iB * (1.0 / kPi * unit));
   out.dl = static_cast<float>(dl_base - czB * dpsi_dL * (1.0 + a));
   out.da = static_cast<float>(da_base - czB * dpsi_dL * lam);
   out.dk = static_cast<float>(-czB * dpsi_dk);
-  out.dz = static_cast<float>(sz * psi * iB);
+  out.dz = (0.5 * kPi) * (sz * psi * iB);
   return out;
 }
-
 
 // ------------------------------------------------ normaliser, FP32 fast path
 // The same normaliser and log-derivatives in FP32 for lam >= 1/2 and
@@ -550,7 +563,12 @@ __device__ inline LobeNorm lobe_norm(double lam, double a, double kd, double zd,
 // log-uniform draw in [1, 1e3] falls in; smaller lam or Lam take the FP64
 // code above. In that range nothing below cancels by more than a factor of a
 // few, so FP32 keeps N relatively accurate to ~1e-6 and the log-derivatives
-// to ~1e-6 of their size:
+// to ~1e-6 of their size. That is not enough for the one in zeta: where Psi is
+// near 1 (a carrier that hardly turns across the lobe) it cancels the carrier's
+// own d ln c/d zeta = -tan(theta/2), by factors of thirty and more, and so it is
+// formed in FP64 as tan(zeta/2) (1 - rho), rho = (1 - Psi)/B, whose error is that
+// of rho alone (rho >= 1/2, where 1 - rho would cancel: no such cancellation
+// there, and the FP32 form serves). The others:
 // - 1 - e^{-2 lam} >= 0.63 and d/dlam ln(lam / (1 - e^{-2 lam})) >= 0.84;
 // - B = 1 + cos(zeta) Psi is formed as (1 - Psi) + Psi (1 + cos zeta), with
 //   sin zeta, cos zeta and 1 + cos zeta each relatively accurate (the phase
@@ -613,10 +631,11 @@ __device__ inline void sincos_phase(double x, float& s, float& c, float& opc) {
   opc = (q == 2) ? omc : 1.f + c;
 }
 
-// zh = zeta / pi in FP64 (the carrier's own phase offset); lam, a, k as the
-// caller holds them (FP64 for the paper's activated values), rounded to FP32
-// here except where the sine branch needs them exact.
-__device__ inline LobeNorm lobe_norm_f32(double lamd, double ad, double kd, double zh, int mode) {
+// lam, a, k as the caller holds them (FP64 for the paper's activated values),
+// rounded to FP32 here except where the sine branch needs them exact.
+template <bool UNIT>
+__device__ inline LobeNorm lobe_norm_f32(double lamd, double ad, double kd, double zd, int mode) {
+  constexpr double unit = UNIT ? kPi * kPi : 1.0;
   const float lam = static_cast<float>(lamd), a = static_cast<float>(ad), k = static_cast<float>(kd);
   const float e2l = exp_f(-2.f * lam);
   const float idl = __builtin_amdgcn_rcpf(1.f - e2l);
@@ -628,11 +647,11 @@ __device__ inline LobeNorm lobe_norm_f32(double lamd, double ad, double kd, doub
   const float da_base = 0.5f * ia;
   LobeNorm out;
   if (mode == 1) {
-    out.n = lam * sq * idl * static_cast<float>(0.5 / kPi);
+    out.n = lam * sq * idl * static_cast<float>(0.5 / kPi * unit);
     out.dl = dl_base;
     out.da = da_base;
     out.dk = 0.f;
-    out.dz = 0.f;
+    out.dz = 0.0;
     return out;
   }
   const float L = lam * opa;
@@ -699,31 +718,36 @@ __device__ inline LobeNorm lobe_norm_f32(double lamd, double ad, double kd, doub
     dPk = -4.f * L * k * dF * iD;
   }
   float sz, cz, opc;
-  sincos_phase(2.0 * zh, sz, cz, opc);                 // sin, cos and 1 + cos of zeta
+  sincos_phase(zd * (2.0 * kInvPi), sz, cz, opc);      // sin, cos and 1 + cos of zeta
   const float B = fmaf(psi, opc, om);
   const float iB = __builtin_amdgcn_rcpf(B);
   const float czB = cz * iB;
-  out.n = lam * sq * idl * iB * static_cast<float>(1.0 / kPi);
+  out.n = lam * sq * idl * iB * static_cast<float>(1.0 / kPi * unit);
   out.dl = dl_base - czB * dPL * opa;
   out.da = da_base - czB * dPL * lam;
   out.dk = -czB * dPk;
-  out.dz = sz * psi * iB;
+  // d ln N/d zeta = sin(zeta) Psi/B = tan(zeta/2) (1 - (1 - Psi)/B)
+  const float rho = om * iB;
+  out.dz = rho < 0.5f ? tan_pi(fma(zd, kInvTwoPi, 0.5)) * (1.0 - static_cast<double>(rho))
+                      : static_cast<double>(static_cast<float>(0.5 * kPi) * (sz * psi * iB));
   return out;
 }
 
 // The FP64 normaliser as a called function: it runs only for the rare lobes
 // outside the FP32 range, and kept out of line its FP64 temporaries do not
 // count against the calling kernel's register budget.
+template <bool UNIT>
 __device__ __noinline__ LobeNorm lobe_norm_outlined(double lam, double a, double kd, double zd,
                                                     int mode) {
-  return lobe_norm(lam, a, kd, zd, mode);
+  return lobe_norm<UNIT>(lam, a, kd, zd, mode);
 }
 
 // The normaliser by the FP32 path where it applies, by the FP64 one elsewhere.
+template <bool UNIT>
 __device__ inline LobeNorm lobe_norm_any(double lam, double a, double kd, double zd, int mode) {
   const float lf = static_cast<float>(lam), af = static_cast<float>(a);
-  if (lf >= 0.5f && lf * (1.f + af) >= 1.5f) return lobe_norm_f32(lam, a, kd, zd * kInvPi, mode);
-  return lobe_norm_outlined(lam, a, kd, zd, mode);
+  if (lf >= 0.5f && lf * (1.f + af) >= 1.5f) return lobe_norm_f32<UNIT>(lam, a, kd, zd, mode);
+  return lobe_norm_outlined<UNIT>(lam, a, kd, zd, mode);
 }
 
 }  // namespace nasg

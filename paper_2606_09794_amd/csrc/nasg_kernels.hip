@@ -212,11 +212,12 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
       const double xa0 = xa[0], xa1 = xa[1], xa2 = xa[2];
       const double za0 = za[0], za1 = za[1], za2 = za[2];
       const double zd = NOCAR ? 0.0 : static_cast<double>(sh.w);
-      const double kh = kd * kInvPi;
-      const double zh = zd * kInvPi;
-      const LobeNorm nm = lobe_norm_any(lamd, ad, kd, zd, NOCAR ? 1 : a.norm);
+      const double kh = kd * kInvTwoPi;
+      const double zh = fma(zd, kInvTwoPi, 0.5);
+      const LobeNorm nm = lobe_norm_any<!NOCAR>(lamd, ad, kd, zd, NOCAR ? 1 : a.norm);
       const float Nn = own ? nm.n : 0.f;
-      const float kf = static_cast<float>(kd);
+      const float kf = static_cast<float>((-2.0 / kPi) * kd);
+      const float dzf = static_cast<float>(nm.dz);
       const float two_lam = static_cast<float>(2.0 * lamd);
       const double two_laml = lamd * (2.0 * kLog2e);
       const double a2 = 2.0 * ad;
@@ -267,23 +268,31 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
           __builtin_amdgcn_sched_barrier(0);   // keep the table read ahead of the carrier work
           const double dend = hd * fmax(q, 4e-30);   // 2 (1 - (d.z)^2)
           const float dx = static_cast<float>(dxd);
-          // carrier phase theta/pi = (k d.x + zeta)/pi, reduced to the nearest
-          // integer n: theta = pi (n + g), |g| <= 1/2. Even n is a carrier peak,
-          // c = cos^2(pi g/2); odd n a zero, c = sin^2(pi g/2); dc/dtheta is
-          // -sin(pi g/2) cos(pi g/2) at a peak and +sin cos at a zero. The
-          // offset g is exact in FP64, so c and dc/dtheta stay relatively
-          // accurate at the carrier's peaks and zeros alike.
-          float car = 1.f, scp = 0.f;
-          bool peak = true;
+          // carrier c = cos^2(theta/2), theta = k d.x + zeta; its half phase in units
+          // of pi is reduced to an offset r in [-1/2, 1/2), exact in FP64, whose
+          // cosine and sine have the dropped integer's sign in common, so c and
+          // dc/dtheta = -sin cos stay relatively accurate at the carrier's peaks and
+          // zeros alike. car, scp and cz are c, -dc/dtheta and c d ln N/d zeta +
+          // dc/dzeta in units of pi^2, 2 pi and 2 pi; those factors are in Nn, kf and
+          // the write-out. cz's two terms cancel where Psi is near 1 (in FP32 one lobe
+          // next to a zero of its carrier put its rounding into the whole zeta
+          // gradient), so their difference is taken in FP64 up to uc and us, which are
+          // small where it is small: dz v - r.
+          float car = 1.f, scp = 0.f, cz = 0.f;
           if constexpr (!NOCAR) {
-            const double th = fma(dxd, kh, zh);
-            const double nh = rint(th);
-            float sa, ca;
-            sincos_halfpi(static_cast<float>(th - nh), sa, ca);
-            peak = (sat_int(nh) & 1) == 0;
-            const float cpk = peak ? ca : sa;
-            car = cpk * cpk;
-            scp = sa * ca;
+            const double f = __builtin_amdgcn_fract(fma(dxd, kh, zh));   // r + 1/2
+            const double v = fma(-f, f, f);
+            const float vf = static_cast<float>(v);
+            const float uc = cos_pi_u(vf);
+            const float cf = fmaf(vf, uc, vf);
+            car = cf * cf;
+            if constexpr (BWD) {
+              const double r = f - 0.5;
+              const float rf = static_cast<float>(r);
+              const float ru = rf * sin_pi_u(vf);
+              scp = cf * (rf + ru);
+              cz = cf * (static_cast<float>(fma(nm.dz, v, -r)) + fmaf(dzf * vf, uc, -ru));
+            }
           }
           // envelope exponent in FP64, base 2: X log2(e) = 2 lam log2(e) (E kappa
           // - 1) + tau log2 kappa
@@ -325,13 +334,13 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
             // the FP32 difference would carry its absolute error into E kappa
             const float Ek = static_cast<float>(Ekd);
             const float T2 = fmaf(two_lam, Ek, 1.f);   // 2 lam E kappa + 1
-            const float Sth = (peak ? -scp : scp) * Npe;      // N p E dc/dtheta
-            const float gS = gG * Sth;
+            const float gP = gG * Npe;
+            const float gS = gP * scp;                 // dL/dG N p E dc/dtheta, times -pi/2
             acc_k = fmaf(gS, dx, acc_k);
-            acc_z += gS;
+            acc_z = fmaf(gP, cz, acc_z);
             // qT = dL/dG G (2 lam E kappa + 1); uu = qT LR d.x with LR as above:
             // a's sum takes uu d.x (ln kappa dtau/da = 2 ln2 LR (d.x)^2), and
-            // dL/dG s_x = uu 4 a ln2 + dL/dG N p E dc/dtheta k
+            // dL/dG s_x = uu 4 a ln2 + dL/dG N p E dc/dtheta k (kf = -2 k/pi)
             const float qT = qG * T2;
             const float uu = qT * LR * dx;
             acc_a = fmaf(uu, dx, acc_a);
@@ -383,7 +392,8 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
             put4<ONCE>(a.g_shape, li,
                        make_float4(fmaf(nm.dl, acc_G, 2.f * acc_l) * dlam_du,
                                    fmaf(nm.da, acc_G, static_cast<float>(2.0 * kLn2) * acc_a) * da_du,
-                                   fmaf(nm.dk, acc_G, acc_k) * dk_du, fmaf(nm.dz, acc_G, acc_z)),
+                                   fmaf(nm.dk, acc_G, static_cast<float>(-2.0 / kPi) * acc_k) * dk_du,
+                                   static_cast<float>(2.0 / kPi) * acc_z),
                        acc_mode);
           }
           if (a.g_quat != nullptr) {

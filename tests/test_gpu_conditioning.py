@@ -1,0 +1,62 @@
+"""Gradients where two large terms nearly cancel, or where 1 - (d.z)^2 leaves the
+range that a rounding error of d.z allows, against the FP64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2606_09794_amd as P
+import workloads as W
+from gpu_util import compare, dgeo, oracle_nasg, upload
+from oracle import nasg_ref as R
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-5
+
+
+def _run(w, norm="exact"):
+    d = upload(w)
+    rgb = P.nasg_eval_fwd(d["quat"], d["shape"], d["rgbw"], d["c0"], norm=norm, **dgeo(d))
+    fused = torch.empty_like(rgb)
+    g = P.nasg_eval_bwd(d["quat"], d["shape"], d["rgbw"], d["c0"], d["grad_rgb"], norm=norm,
+                        rgb_out=fused, **dgeo(d))
+    torch.cuda.synchronize()
+    return rgb.cpu().numpy(), fused.cpu().numpy(), {k: x.cpu().numpy() for k, x in g.items()}
+
+
+@pytest.mark.parametrize("v", [1, 2, 5, 16])
+def test_zeta_gradient_next_to_the_carrier_zero(v):
+    """EXACT normaliser, zeta next to pi, a slow carrier: d ln N / d zeta and
+    d ln c / d zeta are both about 2/(pi - zeta) with opposite signs. With t =
+    tan(zeta/2), c = cos^2(theta/2), d ln N / d zeta = t (1 - (1 - Psi)/B) is
+    rearranged into two terms that do not cancel,
+        N p E (t c - sin(theta)/2) = -N p E cos(theta/2) sin(k d.x/2)/cos(zeta/2)
+    and -G t (1 - Psi)/B, each held to the parity bar; of the terms before the
+    rearrangement 3e-8 may be left (sine and cosine of the half phase to about 1e-8,
+    entering t c and sin(theta)/2 three times in all; formed in float32 they leave
+    several 1e-7)."""
+    n, k = 3000, 4
+    w = W.draw_workload(50 + v, n, k, v, with_sh=False)
+    rng = np.random.default_rng(v)
+    off = np.exp(rng.uniform(np.log(0.01), np.log(1.0), (k, n))) * rng.choice([-1.0, 1.0], (k, n))
+    w.shape[..., 3] = np.pi * rng.choice([-1.0, 1.0, 3.0], (k, n)) + off
+    w.shape[..., 2] = np.exp(rng.uniform(np.log(1e-3), 0.0, (k, n)))
+    _, _, g = _run(w)
+    ref, scale = oracle_nasg(w, "exact")
+    ax, _, az = R.frame_from_quat(w.quat)
+    dirs, _ = R.view_directions(w.means, w.cams)
+    lam, a, kk, zeta = np.moveaxis(w.shape.astype(np.float64), -1, 0)
+    t = R.lobe_terms(dirs, ax, az, w.shape, R.norm_exact(lam, a, kk, zeta)[0])
+    psi, _, _, om = R.psi(lam * (1.0 + a), kk)
+    tz = np.tan(zeta / 2)
+    B = psi * 2.0 * np.cos(zeta / 2) ** 2 + om
+    weight = np.abs(w.grad_rgb[None] * np.transpose(w.rgbw, (0, 2, 1))[:, None]).sum(-1)   # [K][V][N]
+    first = np.abs(t["p"] * t["E"] * t["Cn"] * np.cos(t["arg"] / 2) * np.sin(kk * t["dx"].swapaxes(0, 1) / 2).swapaxes(0, 1)
+                   / np.cos(zeta / 2)[:, None])
+    second = np.abs(t["G"] * (tz * om / B)[:, None])
+    bar = TOL * (weight * (first + second)).sum(1) + 3e-8 * scale["shape"][..., 3]
+    err = np.abs(g["shape"][..., 3] - ref["shape"][..., 3])
+    worst = float((err / (bar + 1e-30)).max())
+    print(f"zeta error over its bar: {worst:.3g}; norm {np.linalg.norm(err) / np.linalg.norm(ref['shape'][..., 3]):.2g}")
+    assert worst <= 1.0
+    for name in ("quat", "shape", "rgbw", "c0", "geom"):
+        compare(g[name], ref[name], scale[name], name, TOL)
