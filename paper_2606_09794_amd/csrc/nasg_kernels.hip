@@ -249,17 +249,22 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
           // rounding. Next to the axis h keeps an absolute error ~2e-16;
           // nothing below is sensitive to h's relative error there (G, s_x
           // and a's gradient depend on tau only through tau ln kappa and ln
-          // kappa/(1 - (d.z)^2), s_z through tau Q, all smooth in h).
-          // In 1/(h q) = 1/(2 (1 - (d.z)^2)) h and q are kept off zero by less than
-          // their rounding, so that it is finite at the poles: at d = z the
-          // factors it multiplies (d.x, tau) are ~1e-16 of their scale, at
-          // d = -z everything is multiplied by G = 0.
+          // kappa/(1 - (d.z)^2), s_z through tau Q, all smooth in h), given that
+          // both ln kappa and h come from a q below 4: rounded to 4 or above (d
+          // within 2e-8 of z, where d.x is up to that and tau up to a) it would
+          // take ln kappa from the bucket above, 3e-13 instead of -1e-16, and h
+          // would be 0. The largest q below 4 gives ln kappa/(1 - (d.z)^2) = -1/4,
+          // its limit.
+          // In 1/(h q) = 1/(2 (1 - (d.z)^2)) q is kept off zero by less than its
+          // rounding, so that it is finite at d = -z, where everything is
+          // multiplied by G = 0.
           const double e0 = sl.dd[t][0] + za0;
           const double e1 = sl.dd[t][1] + za1;
           const double e2 = sl.dd[t][2] + za2;
-          const double q = fma(e0, e0, fma(e1, e1, e2 * e2));
-          const bool live = q > 0.0;
-          const double hd = fmax(fma(q, -0.5, 2.0), 0x1p-53);
+          const double qr = fma(e0, e0, fma(e1, e1, e2 * e2));
+          const bool live = qr > 0.0;
+          const double q = fmin(qr, 0x1.fffffffffffffp+1);
+          const double hd = fma(q, -0.5, 2.0);
           // kappa = lm 2^le. The table entry is fetched first, its use comes
           // after the carrier and 1/(h q).
           const int le = __builtin_amdgcn_frexp_exp(q) - 2;

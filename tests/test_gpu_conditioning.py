@@ -60,3 +60,50 @@ def test_zeta_gradient_next_to_the_carrier_zero(v):
     assert worst <= 1.0
     for name in ("quat", "shape", "rgbw", "c0", "geom"):
         compare(g[name], ref[name], scale[name], name, TOL)
+
+
+def _check(w, norm="exact"):
+    rgb, fused, g = _run(w, norm)
+    ref, scale = oracle_nasg(w, norm)
+    compare(rgb, ref["rgb"], scale["rgb"], "rgb", TOL)
+    compare(fused, ref["rgb"], scale["rgb"], "rgb (fused)", TOL)
+    for name, x in g.items():
+        compare(x, ref[name], scale[name], name, TOL)
+
+
+@pytest.mark.parametrize("norm", ["exact", "approx"])
+def test_gradients_next_to_the_axis(norm):
+    """Directions 1e-10 to 1e-7 off the lobe axis, where q = |d + z|^2 rounds to 4
+    or above: ln kappa/(1 - (d.z)^2) -> -1/4 there, with d.x up to the offset and
+    tau up to a, so nothing that multiplies it vanishes."""
+    offs = [0.0, 1e-10, 1e-9, 5e-9, 1e-8, 1.4e-8, 2e-8, 3e-8, 6e-8, 1e-7]
+    dirs = [(e * c, e * s, 1.0) for e in offs for c, s in ((1, 0), (1, 1), (0, 1))]
+    lobes = [(lam, a, k) for lam in (0.3, 1.0, 30.0, 1000.0) for a in (0.0, 1.0, 1000.0) for k in (0.0, 8.0)]
+    n = len(dirs) * len(lobes)
+    w = W.draw_workload(3, n, 1, 1, dirs_mode=True, with_sh=False)
+    w.quat[...] = (1.0, 0.0, 0.0, 0.0)
+    w.dirs[...] = np.repeat(np.array(dirs, np.float32), len(lobes), axis=0)
+    w.shape[0, :, :3] = np.tile(np.array(lobes, np.float32), (len(dirs), 1))
+    _check(w, norm)
+
+
+@pytest.mark.parametrize("k,v", [(1, 1), (8, 3), (8, 16)])
+def test_frames_aimed_at_a_camera(k, v):
+    """Float32 frames whose axis is the direction to one of the cameras as nearly
+    as float32 quaternions give it: that view's terms meet the other views' and
+    the other lobes' in one sum."""
+    n = 4000
+    w = W.draw_workload(70 + v, n, k, v, with_sh=False)
+    rng = np.random.default_rng(v)
+    d, _ = R.view_directions(w.means, w.cams)
+    for lobe in range(k):
+        z = d[lobe % v]                                   # [N][3]
+        up = np.cross(z, rng.normal(size=(n, 3)))
+        x = up / np.linalg.norm(up, axis=-1, keepdims=True)
+        y = np.cross(z, x)
+        m = np.stack([x, y, z], -1)                       # columns
+        t = np.trace(m, axis1=1, axis2=2)
+        q = np.stack([1.0 + t, m[:, 2, 1] - m[:, 1, 2], m[:, 0, 2] - m[:, 2, 0],
+                      m[:, 1, 0] - m[:, 0, 1]], -1)
+        w.quat[lobe] = q / np.linalg.norm(q, axis=-1, keepdims=True)
+    _check(w)
