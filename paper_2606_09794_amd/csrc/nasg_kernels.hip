@@ -255,9 +255,11 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
           // take ln kappa from the bucket above, 3e-13 instead of -1e-16, and h
           // would be 0. The largest q below 4 gives ln kappa/(1 - (d.z)^2) = -1/4,
           // its limit.
-          // In 1/(h q) = 1/(2 (1 - (d.z)^2)) q is kept off zero by less than its
-          // rounding, so that it is finite at d = -z, where everything is
-          // multiplied by G = 0.
+          // At d = -z (q = 0) 1/(h q) is not a number, of which the two minima below
+          // take their limits, and everything is multiplied by G = 0. Next to it q
+          // may be any positive number and G keeps its limit N e^{-2 lam} kappa^tau:
+          // tau = 2 a (d.x)^2/(h q) is held to a, its largest value (a rounding of
+          // d.x would take it beyond), and 1/(h q) to 1e35 where it goes into FP32.
           const double e0 = sl.dd[t][0] + za0;
           const double e1 = sl.dd[t][1] + za1;
           const double e2 = sl.dd[t][2] + za2;
@@ -271,7 +273,7 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
           const double lm = __builtin_amdgcn_frexp_mant(q);
           const LogEntry lt = ltab[log_bucket(lm)];
           __builtin_amdgcn_sched_barrier(0);   // keep the table read ahead of the carrier work
-          const double dend = hd * fmax(q, 4e-30);   // 2 (1 - (d.z)^2)
+          const double dend = hd * q;                // 2 (1 - (d.z)^2)
           const float dx = static_cast<float>(dxd);
           // carrier c = cos^2(theta/2), theta = k d.x + zeta; its half phase in units
           // of pi is reduced to an offset r in [-1/2, 1/2), exact in FP64, whose
@@ -302,7 +304,7 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
           // envelope exponent in FP64, base 2: X log2(e) = 2 lam log2(e) (E kappa
           // - 1) + tau log2 kappa
           const double rden = rcp64(dend);           // 1 / (2 (1 - (d.z)^2))
-          const double taud = a2 * (dxd * dxd * rden);
+          const double taud = a2 * fmin(dxd * dxd * rden, 0.5);
           const double Ld = log2_finish(lm, le, lt, 0.0, k_c3);
           const double Ad = taud * Ld;               // log2 E
           double Ekd, em1d;
@@ -320,11 +322,12 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
           if constexpr (BWD) {
             // log2 kappa/(2 (1 - (d.z)^2)); the factor 2 ln2 of ln kappa/(1 -
             // (d.z)^2) is in a_ln2 and in a's sum
-            const float LR = static_cast<float>(Ld * rden);
+            const double rdf = fmin(rden, 1e35);
+            const float LR = static_cast<float>(Ld * rdf);
             // Q/2, Q = 1/(2 kappa) + 2 d.z ln kappa/(1 - (d.z)^2) = (h + 2 d.z ln
             // kappa)/(1 - (d.z)^2) in FP64: its two terms (each ~1/2) cancel next
             // to the axis, where Q -> 3h/8 (2 d.z = q - 2)
-            const float Qh = static_cast<float>(fma((q - 2.0) * kLn2, Ld, hd) * rden);
+            const float Qh = static_cast<float>(fma((q - 2.0) * kLn2, Ld, hd) * rdf);
             const float tau = static_cast<float>(taud);
             const float em1 = static_cast<float>(em1d);
             const float g0 = sl.gr[t][0], g1 = sl.gr[t][1], g2 = sl.gr[t][2];
@@ -350,7 +353,7 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
             const float uu = qT * LR * dx;
             acc_a = fmaf(uu, dx, acc_a);
             const float gsx = fmaf(uu, a_ln2, gS * kf);
-            const float iq = static_cast<float>(hd * rden);   // 1/q
+            const float iq = static_cast<float>(hd * rdf);    // 1/q
             // half of dL/dG s_z = dL/dG G [(2 lam E kappa + 1) tau Q + lam E],
             // lam E = 2 (2 lam E kappa)/q; the factor 2 is in zf0..2 and where
             // az is used

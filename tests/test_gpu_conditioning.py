@@ -107,3 +107,30 @@ def test_frames_aimed_at_a_camera(k, v):
                       m[:, 1, 0] - m[:, 0, 1]], -1)
         w.quat[lobe] = q / np.linalg.norm(q, axis=-1, keepdims=True)
     _check(w)
+
+
+@pytest.mark.parametrize("norm", ["exact", "approx"])
+def test_next_to_the_antipode(norm):
+    """Directions 1e-30 to 1e-6 off -z with an exact frame: G = N e^{-2 lam (1 - E
+    kappa)} kappa^tau, tau = a cos^2(phi), keeps its limit (N e^{-2 lam} along y, 0
+    elsewhere unless a is small) however small kappa = |d + z|^2/4 > 0 is. The
+    gradients, which hold 1/kappa, are compared where those are in FP32's range
+    and are finite everywhere."""
+    offs = [0.0, 1e-30, 1e-20, 1e-18, 1e-17, 1e-16, 1e-15, 1e-14, 1e-12, 1e-9, 1e-6]
+    phis = [(1, 0), (0, 1), (1, 1), (0.01, 1)]
+    dirs = np.array([(e * c, e * s, -1.0) for e in offs for c, s in phis], np.float32)
+    lobes = [(lam, a, k) for lam in (0.05, 0.5, 3.0) for a in (0.0, 1e-3, 0.1, 10.0) for k in (0.0, 3.0)]
+    n = len(dirs) * len(lobes)
+    w = W.draw_workload(4, n, 1, 1, dirs_mode=True, with_sh=False)
+    w.quat[...] = (1.0, 0.0, 0.0, 0.0)
+    w.dirs[...] = np.repeat(dirs, len(lobes), axis=0)
+    w.shape[0, :, :3] = np.tile(np.array(lobes, np.float32), (len(dirs), 1))
+    rgb, fused, g = _run(w, norm)
+    ref, scale = oracle_nasg(w, norm)
+    compare(rgb, ref["rgb"], scale["rgb"], "rgb", TOL)
+    compare(fused, ref["rgb"], scale["rgb"], "rgb (fused)", TOL)
+    far = np.abs(w.dirs[:, :2]).max(-1) > 5e-15
+    for name, x in g.items():
+        assert np.isfinite(x).all(), name
+        at = (np.s_[:, far] if name in ("quat", "shape") else np.s_[:, :, far] if name == "rgbw" else np.s_[far])
+        compare(x[at], ref[name][at], scale[name][at], name, TOL)
