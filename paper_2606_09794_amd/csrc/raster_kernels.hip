@@ -963,8 +963,9 @@ __global__ __launch_bounds__(256) void raster_render_fwd(RasterArgs a) {
 // transmittance, T_i = T_{i+1} / (1 - alpha_i).
 //
 // Only the upstream gradient's product with R enters: P = g . R obeys the same
-// recursion as a scalar per pixel, P_i = g.c_i - (1 - alpha_i) (g.c_i -
-// P_{i+1}), and dL/dalpha_i = T_i (g.c_i - P_{i+1}). All sums are taken in
+// recursion as a scalar per pixel, P_i = P_{i+1} + alpha_i (g.c_i - P_{i+1}) (an
+// instruction more than g.c_i - (1 - alpha_i) (g.c_i - P_{i+1}), which makes a NaN
+// of an infinite colour), and dL/dalpha_i = T_i (g.c_i - P_{i+1}). All sums are taken in
 // units of the opacity (alpha = sigma rho): with s = T rho dL/dalpha / T,
 // the entry's sums are T rho g (colour / sigma), s (dL/dsigma) and the moments
 // s (a dx + b dy), s (b dx + c dy), s dx^2, s dx dy, s dy^2, which the finish
@@ -1046,7 +1047,8 @@ void raster_render_bwd(RasterArgs a) {
         const double rho = static_cast<double>(
             __builtin_amdgcn_exp2f(static_cast<float>(q) * kNegHalfLog2e));
         const double rc = kFast ? rho : fmin(rho, s.rmax);
-        const double om = fma(-s.sigma, rc, 1.0);
+        const double al = s.sigma * rc;
+        const double om = 1.0 - al;
         t[j] *= rcp64(om);  // now T_i = t * pw
         const double w = rc * (kFast ? t[j] : t[j] * pw[j]);
         gc0 = fma(w, g[j][0], gc0);
@@ -1054,7 +1056,7 @@ void raster_render_bwd(RasterArgs a) {
         gc2 = fma(w, g[j][2], gc2);
         const double gc = fma(g[j][0], s.c0, fma(g[j][1], s.c1, g[j][2] * s.c2));
         const double d = gc - P[j];
-        P[j] = fma(-om, d, gc);
+        P[j] = fma(al, d, P[j]);
         const double sm = kFast || rho < s.rmax ? d * w : 0.0;
         q0 += sm;
         if constexpr (GEOM) {

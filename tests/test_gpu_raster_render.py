@@ -124,3 +124,28 @@ def test_camera_centre_on_the_device_equals_the_host():
         assert got.shape == (1, 3) and got.dtype == np.float32
         tol = 2.0 ** -23 * np.abs(host) + 2.0 ** -51 * np.abs(t).sum()
         assert np.all(np.abs(got - host) <= tol), (i, got, host)
+
+
+@pytest.mark.parametrize("canvas", [(16, 16), (896, 896)], ids=["few-tiles", "many-tiles"])
+def test_infinite_colour_behind(canvas):
+    """An infinite colour (an overflow of the appearance): the entry in front of it
+    gets an infinite opacity gradient of the sign that c - R has, R the colour seen
+    behind it, its own the other sign, and those behind it what they get beside a
+    finite colour, bit for bit. (From the next entry on R itself is inf - inf.)"""
+    cam = P.Camera(np.eye(3), np.zeros(3), 20.0, 20.0, canvas[0] / 2, canvas[1] / 2, *canvas)
+    n = 5
+    means = torch.tensor([[0.0, 0.0, 3.0 + i] for i in range(n)], device="cuda")
+    scales = torch.full((n, 3), 0.4, device="cuda")
+    rots = torch.tensor([[1.0, 0.0, 0.0, 0.0]] * n, device="cuda")
+    opac = torch.tensor([0.2, 0.3, 0.4, 0.5, 0.6], device="cuda")
+    g = torch.ones((canvas[1], canvas[0], 3), device="cuda")
+    grads = []
+    for c in (float("inf"), 1.0):
+        col = torch.full((n, 3), 0.5, device="cuda")
+        col[2, 1] = c
+        img, ws = P.raster_fwd(means, scales, rots, opac, col, cam, 64)
+        grads.append([x.cpu() for x in P.raster_bwd(means, scales, rots, opac, col, cam, ws, g, 64)])
+    go = grads[0][1]
+    assert go[1] == -float("inf") and go[2] == float("inf"), go
+    assert torch.equal(go[3:], grads[1][1][3:])
+    assert torch.equal(grads[0][0], grads[1][0])      # the colours' gradients do not hold colours
