@@ -457,9 +457,10 @@ const char* nasg_status_string(int status);
  * overrides the built-in choice for a (kernel, K, V, dtype) key. The built-in
  * choice follows N too (few primitives are spread over more lanes), which no
  * key holds: nasg_get_tuning reports the override, or without one the view
- * count's reference mapping. kernel: 0 = NASG forward, 1 = NASG
- * backward / fused, 2 = SH forward, 3 = SH backward. K is ignored for SH.
- * lanes = 0 removes an override. Host-side table, not thread-safe against
+ * count's reference mapping with bcast = NASG_TUNING_BUILT_IN. kernel: 0 = NASG
+ * forward, 1 = NASG backward / fused, 2 = SH forward, 3 = SH backward. K is
+ * ignored for SH. lanes = 0 or bcast = NASG_TUNING_BUILT_IN removes an override,
+ * so that setting what nasg_get_tuning reported restores a key. Host-side table, not thread-safe against
  * concurrent calls.                                                         */
 typedef struct nasg_tuning {
   int32_t lanes;
@@ -467,8 +468,10 @@ typedef struct nasg_tuning {
   int32_t block;       /* threads per block: 64, 128 or 256 (the kernels are
                           compiled for at most 256; other values return
                           NASG_ERR_SHAPE)                                     */
-  int32_t bcast;       /* 0: travelling views, 1: broadcast views (above)     */
+  int32_t bcast;       /* 0: travelling views, 1: broadcast views (above),
+                          NASG_TUNING_BUILT_IN: no override                   */
 } nasg_tuning;
+enum { NASG_TUNING_BUILT_IN = -1 };
 
 int nasg_set_tuning(int32_t kernel, int32_t k, int32_t v, int32_t dtype,
                     const nasg_tuning* t);

@@ -14,6 +14,7 @@ LIB_PATH = os.path.join(_PKG, "libnasg.so")
 NASG_OK = 0
 NASG_F32, NASG_BF16 = 0, 1
 NORM_EXACT, NORM_APPROX = 0, 1
+TUNING_BUILT_IN = -1
 GRAD_OVERWRITE, GRAD_ACCUMULATE = 0, 1
 PARAM_QUAT, PARAM_ANGLES = 0, 1
 FAMILIES = {"nasgabor": 0, "nasg": 1, "sg": 2, "sb": 3, "sc": 4, "asg": 5}

@@ -307,7 +307,8 @@ def set_tuning(kernel: int, k: int, v: int, dtype: int, lanes: int, views_per_la
 
 def get_tuning(kernel: int, k: int, v: int, dtype: int):
     """(lanes, views_per_lane, block, bcast) set for this key, or the view count's
-    reference mapping when none is (the built-in choice follows N too)."""
+    reference mapping with bcast -1 when none is (the built-in choice follows N
+    too). set_tuning() of either restores the key."""
     t = L.NasgTuning()
     L.check(L.lib().nasg_get_tuning(kernel, k, v, dtype, C.byref(t)), "nasg_get_tuning")
     return (t.lanes, t.views_per_lane, t.block, t.bcast)

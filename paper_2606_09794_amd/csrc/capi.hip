@@ -179,9 +179,9 @@ nasg_tuning sh_shape(bool bwd, int64_t n, int v) {
   return t;
 }
 
-// What nasg_get_tuning reports for a key without an override: the reference
-// mapping of the view count, a valid override by itself. Launches without an
-// override follow N, K and the kernel.
+// What nasg_get_tuning reports for a key without an override, marked as such: the
+// reference mapping of the view count, a valid override but for the mark. Launches
+// without an override follow N, K and the kernel.
 nasg_tuning view_count_mapping(int32_t v) {
   if (v <= 1) return {1, 1, 256, 0};
   if (v <= 2) return {1, 2, 256, 0};
@@ -439,7 +439,7 @@ int nasg_set_tuning(int32_t kernel, int32_t k, int32_t v, int32_t dtype, const n
   if (kernel < 0 || kernel > 3) return NASG_ERR_MODE;
   if (t == nullptr) return NASG_ERR_NULL;
   const Key key{kernel, kernel >= 2 ? 0 : k, v, kernel >= 2 ? 0 : dtype};
-  if (t->lanes == 0) {
+  if (t->lanes == 0 || t->bcast == NASG_TUNING_BUILT_IN) {
     tuning_table().erase(key);
     return NASG_OK;
   }
@@ -456,6 +456,7 @@ int nasg_get_tuning(int32_t kernel, int32_t k, int32_t v, int32_t dtype, nasg_tu
   const auto& tab = tuning_table();
   const auto it = tab.find(Key{kernel, kernel >= 2 ? 0 : k, v, kernel >= 2 ? 0 : dtype});
   *t = it != tab.end() ? it->second : view_count_mapping(v);
+  if (it == tab.end()) t->bcast = NASG_TUNING_BUILT_IN;
   return NASG_OK;
 }
 

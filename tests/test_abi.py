@@ -123,6 +123,31 @@ def test_status_strings_and_tuning(lib):
     assert lib.nasg_set_tuning(9, 8, 16, 0, C.byref(t)) == -5
 
 
+def test_tuning_round_trip(lib):
+    """Setting what nasg_get_tuning reported restores a key, one without an override
+    too: launches of it follow N again and not the view count's mapping."""
+    def get(kernel, k, v, dtype):
+        t = L.NasgTuning()
+        assert lib.nasg_get_tuning(kernel, k, v, dtype, C.byref(t)) == 0
+        return t
+
+    for kernel, k, v, dtype in ((0, 8, 1, 0), (1, 8, 9, 0), (1, 8, 16, 1), (2, 0, 6, 0), (3, 0, 40, 0)):
+        before = get(kernel, k, v, dtype)
+        assert before.bcast == L.TUNING_BUILT_IN
+        assert lib.nasg_set_tuning(kernel, k, v, dtype, C.byref(before)) == 0
+        assert get(kernel, k, v, dtype).bcast == L.TUNING_BUILT_IN
+        assert lib.nasg_set_tuning(kernel, k, v, dtype, C.byref(L.NasgTuning(2, 2, 64, 0))) == 0
+        kept = get(kernel, k, v, dtype)
+        assert (kept.lanes, kept.views_per_lane, kept.block, kept.bcast) == (2, 2, 64, 0)
+        assert lib.nasg_set_tuning(kernel, k, v, dtype, C.byref(kept)) == 0
+        assert get(kernel, k, v, dtype).bcast == 0
+        assert lib.nasg_set_tuning(kernel, k, v, dtype, C.byref(before)) == 0
+        after = get(kernel, k, v, dtype)
+        assert (after.lanes, after.views_per_lane, after.block, after.bcast) == (
+            before.lanes, before.views_per_lane, before.block, L.TUNING_BUILT_IN)
+    assert lib.nasg_set_tuning(1, 8, 16, 0, C.byref(L.NasgTuning(4, 4, 128, 2))) == -2
+
+
 def test_batched_rejects(lib):
     sc = (L.NasgScene * 1)()
     sc[0] = L.NasgScene(params(), views(), FAKE, L.NasgGrads(FAKE, FAKE, FAKE, FAKE, FAKE), None)
