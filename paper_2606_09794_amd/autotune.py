@@ -4,7 +4,12 @@ For a key (kernel, K, V, storage dtype) it times every compiled
 (lanes per primitive, views per lane) mapping and block size on synthetic
 device inputs of the requested size, installs the fastest in the library's
 tuning table (``nasg_set_tuning``) and records it in a JSON cache, which
-``load_cache`` replays at start-up.
+``load_cache`` replays at start-up. An entry holds for every N and both
+parametrisations of its key, where the built-in choice follows them (K = 8, one
+view, 8192 primitives, forward: 7.6 us against 8.6 on the mapping that is best
+for a million; K = 16, eight views, bfloat16 7.5 against 19.1). The committed
+cache has none: at the sizes they were tuned for (1 M and 3 M) each of 56 took as
+long as the built-in choice, within the runs' 3 %, or longer (up to 7 %).
 
     python -m paper_2606_09794_amd.autotune --k 8 --v 16 --n 3000000
 """

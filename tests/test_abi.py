@@ -148,6 +148,28 @@ def test_tuning_round_trip(lib):
     assert lib.nasg_set_tuning(1, 8, 16, 0, C.byref(L.NasgTuning(4, 4, 128, 2))) == -2
 
 
+def test_committed_tuning_leaves_the_choice_by_n(lib):
+    """Loading the committed cache leaves every key its built-in choice, which
+    follows N and the parametrisation: an entry would pin the mapping that is best
+    for a million primitives on small calls too."""
+    from paper_2606_09794_amd import autotune
+    t = L.NasgTuning()
+    try:
+        autotune.load_cache()
+        for kernel in range(4):
+            for k in (1, 2, 4, 8, 16):
+                for v in (1, 2, 4, 8, 16, 32):
+                    for dtype in (0, 1):
+                        assert lib.nasg_get_tuning(kernel, k, v, dtype, C.byref(t)) == 0
+                        assert t.bcast == L.TUNING_BUILT_IN, (kernel, k, v, dtype)
+    finally:
+        for kernel in range(4):
+            for k in (4, 8, 16):
+                for v in (1, 4, 8, 16):
+                    for dtype in (0, 1):
+                        lib.nasg_set_tuning(kernel, k, v, dtype, C.byref(L.NasgTuning(0, 0, 0)))
+
+
 def test_batched_rejects(lib):
     sc = (L.NasgScene * 1)()
     sc[0] = L.NasgScene(params(), views(), FAKE, L.NasgGrads(FAKE, FAKE, FAKE, FAKE, FAKE), None)
