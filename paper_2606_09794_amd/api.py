@@ -385,20 +385,25 @@ class Camera:
 
     def centre(self, device) -> torch.Tensor:
         """Camera centre o = -rot^T t as a [1][3] float32 device tensor (the
-        view input of the appearance evaluation). On the current GPU a kernel
-        writes it from its arguments: a copy from the host would wait there for
-        everything queued on the stream (35 us of a small training step)."""
-        dev = torch.device(device)
-        if (dev.type == "cuda" and torch.cuda.is_initialized()
-                and dev.index in (None, torch._C._cuda_getDevice())
-                and not torch.cuda.is_current_stream_capturing()):
-            out = torch.empty((1, 3), dtype=torch.float32, device=dev)
-            L.check(L.lib().nasg_camera_centre(C.byref(self.struct()), out.data_ptr(), _stream()),
-                    "nasg_camera_centre")
-            return out
+        view input of the appearance evaluation). A copy from the host that is
+        waited for, so that any stream may use it."""
         r = torch.tensor(self.rot, dtype=torch.float64).reshape(3, 3)
         o = -(r.T @ torch.tensor(self.t, dtype=torch.float64))
         return o.to(torch.float32).reshape(1, 3).to(device)
+
+
+def _view_centre(cam: Camera, device: torch.device) -> torch.Tensor:
+    """``cam.centre(device)`` for use on the current stream alone. On the current
+    GPU a kernel writes it from its arguments: the copy from the host waits
+    there for everything queued on the stream (35 us of a small training step)."""
+    if (type(cam).centre is Camera.centre and device.type == "cuda"
+            and device.index == torch.cuda.current_device()
+            and not torch.cuda.is_current_stream_capturing()):
+        out = torch.empty((1, 3), dtype=torch.float32, device=device)
+        L.check(L.lib().nasg_camera_centre(C.byref(cam.struct()), out.data_ptr(), _stream()),
+                "nasg_camera_centre")
+        return out
+    return cam.centre(device)
 
 
 def _gaussians(means, scales, rots, opac, colors) -> L.NasgGaussians:
@@ -492,7 +497,7 @@ def render_view(quat, shape, rgbw, c0, means, scales, rots, opac, cam: Camera, *
     into the image (Section 3.1). Differentiable in the lobe parameters, c0,
     the opacities, and the means (through the view direction and the
     projection), scales and rotations (through the projection)."""
-    rgb = NasgEval.apply(quat, shape, rgbw, c0, means, cam.centre(means.device), None, norm,
+    rgb = NasgEval.apply(quat, shape, rgbw, c0, means, _view_centre(cam, means.device), None, norm,
                          param)
     # (a reshape, whose backward is one too; rgb[0]'s fills and copies a tensor)
     return Rasterize.apply(means, scales, rots, opac, rgb.reshape(rgb.shape[1:]), cam,

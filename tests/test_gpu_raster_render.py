@@ -149,3 +149,38 @@ def test_infinite_colour_behind(canvas):
     assert go[1] == -float("inf") and go[2] == float("inf"), go
     assert torch.equal(go[3:], grads[1][1][3:])
     assert torch.equal(grads[0][0], grads[1][0])      # the colours' gradients do not hold colours
+
+
+def test_camera_centre_is_there_for_every_stream():
+    """The centre of a camera made on a busy stream is read by another one at once,
+    without an event between them."""
+    busy = torch.randn((8192, 8192), device="cuda")
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for i in range(4):
+        cam = P.Camera(np.eye(3), [1.0 + i, -2.0, 3.0], 100.0, 100.0, 8.0, 8.0, 16, 16)
+        for _ in range(8):
+            busy = (busy @ busy) * 1e-4
+        c = cam.centre("cuda")
+        with torch.cuda.stream(side):
+            got = c.clone()
+        side.synchronize()
+        assert torch.equal(got.cpu(), torch.tensor([[-1.0 - i, 2.0, -3.0]])), i
+    torch.cuda.synchronize()
+
+
+def test_view_of_a_camera_with_its_own_centre():
+    """A camera class that says its centre differently is asked for it."""
+    class Shifted(P.Camera):
+        def centre(self, device):
+            return super().centre(device) + 0.5
+
+    sc = W.draw_splat_scene(64, 200, 48, 32)
+    w = W.draw_workload(64, 200, 2, 1, with_sh=False)
+    lob = [torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in (w.quat, w.shape, w.rgbw, w.c0)]
+    d = [torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in (sc.means, sc.scales, sc.rots, sc.opac)]
+    args = (sc.cam["R"], sc.cam["t"], sc.cam["fx"], sc.cam["fy"], sc.cam["cx"], sc.cam["cy"], 48, 32)
+    cam = Shifted(*args)
+    got = P.render_view(*lob, *d, cam, tile_capacity=512)
+    rgb = P.nasg_eval_fwd(*lob, means=d[0], cams=P.Camera(*args).centre("cuda") + 0.5)
+    assert torch.equal(got, P.raster_fwd(*d, rgb[0].contiguous(), cam, 512)[0])
