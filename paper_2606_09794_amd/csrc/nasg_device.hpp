@@ -379,25 +379,17 @@ __device__ inline double exp_full(double B) {
 
 // e^B = num / den for B <= 0 (clamped to -1400): with c = r coth(r/2), even in
 // r, e^r = (c + r)/(c - r), so that the one division of tanh, sech and the
-// logistic serves the exponential too. c to r^10 (error 6e-18), or for values
-// that are rounded to FP32 to r^6 (1e-11).
-template <bool F32>
+// logistic serves the exponential too. c to r^10 (error 6e-18).
 __device__ inline void exp_frac(double B, double& num, double& den) {
   B = fmax(B, -1400.0);
   const double n = rint(B * kLog2e);
   double r = fma(-n, kLn2Hi, B);
   r = fma(-n, kLn2Lo, r);
   const double z = r * r;
-  double c;
-  if constexpr (F32) {
-    c = fma_vvs(6.584071454936971e-05, z, -0.0027777644224911266);
-    c = fma_vvs(c, z, 0.16666666657759918);
-  } else {
-    c = fma_vvs(4.143774697636149e-08, z, -1.653406021796854e-06);
-    c = fma_vvs(c, z, 6.613756471747488e-05);
-    c = fma_vvs(c, z, -0.002777777777756467);
-    c = fma_vvs(c, z, 0.1666666666666666);
-  }
+  double c = fma_vvs(4.143774697636149e-08, z, -1.653406021796854e-06);
+  c = fma_vvs(c, z, 6.613756471747488e-05);
+  c = fma_vvs(c, z, -0.002777777777756467);
+  c = fma_vvs(c, z, 0.1666666666666666);
   c = fma(c, z, 2.0);
   num = ldexp(c + r, static_cast<int>(n));
   den = c - r;
@@ -407,7 +399,7 @@ __device__ inline void exp_frac(double B, double& num, double& den) {
 // tanh|u| = (1 - q)(1 + q)/(1 + q^2), sech u = 2 q/(1 + q^2); no overflow.
 __device__ inline void tanh_sech(double u, double& t, double& s) {
   double num, den;
-  exp_frac<false>(-fabs(u), num, den);
+  exp_frac(-fabs(u), num, den);
   const double inv = rcp64(fma(num, num, den * den));
   t = copysign((den - num) * (den + num) * inv, u);
   s = 2.0 * num * den * inv;
@@ -416,7 +408,7 @@ __device__ inline void tanh_sech(double u, double& t, double& s) {
 // tanh u and its derivative sech^2 u, for a value rounded to FP32.
 __device__ inline void tanh_f32(double u, float& t, float& dt) {
   double num, den;
-  exp_frac<true>(-2.0 * fabs(u), num, den);
+  exp_frac(-2.0 * fabs(u), num, den);
   const double inv = rcp64(den + num);
   t = static_cast<float>(copysign((den - num) * inv, u));
   dt = static_cast<float>(4.0 * (num * inv) * (den * inv));
@@ -426,7 +418,7 @@ __device__ inline void tanh_f32(double u, float& t, float& dt) {
 // = 80 t/(1 + t)^2 with t = e^{-2|u|} (no overflow, no cancellation).
 __device__ inline void k_activation(double u, double& k, float& dk) {
   double num, den;
-  exp_frac<false>(-2.0 * fabs(u), num, den);
+  exp_frac(-2.0 * fabs(u), num, den);
   const double inv = rcp64(den + num);
   k = 40.0 * (u >= 0.0 ? den : num) * inv;
   dk = static_cast<float>(80.0 * (num * inv) * (den * inv));

@@ -152,3 +152,24 @@ def test_raw_activations_over_their_range(v):
     compare(fused.cpu().numpy(), ref["rgb"], scale["rgb"], "rgb (fused)", TOL)
     for name in ("rgbw", "c0"):
         compare(g[name].cpu().numpy(), ref[name], scale[name], name, TOL)
+
+
+def test_raw_weights_are_rounded_once():
+    """A raw weight's tanh is formed in FP64 and rounded to float32 once: of a million
+    colours w G, G known from a saturated weight, the FP64 tanh rounded explains all
+    but those whose tanh lies within 2e-14 (its FP64 error at |u| >= 0.01) of the
+    middle between two float32 values: an expected 0.3 at most, 4 allowed."""
+    n = 1 << 20
+    w = W.draw_workload(77, n, 1, 1, param="angles", dirs_mode=True, with_sh=False)
+    rng = np.random.default_rng(77)
+    w.rgbw[:] = np.exp(rng.uniform(np.log(0.01), np.log(8.0), w.rgbw.shape)) * rng.choice([-1.0, 1.0], w.rgbw.shape)
+    w.shape[..., :2] = 0.0             # lam = a = 1: no G near float32's smallest
+    w.c0[:] = 0.0
+    d = upload(w)
+    one = torch.full_like(d["rgbw"], 30.0)
+    G = P.nasg_eval_fwd(d["quat"], d["shape"], one, d["c0"], dirs=d["dirs"], param="angles")
+    got = P.nasg_eval_fwd(d["quat"], d["shape"], d["rgbw"], d["c0"], dirs=d["dirs"], param="angles")
+    want = torch.tanh(d["rgbw"][0].double()).float().T * G[0]
+    off = int((got[0] != want).sum())
+    print(f"{off} of {3 * n} colours differ")
+    assert off <= 4
