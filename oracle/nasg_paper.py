@@ -16,7 +16,9 @@ Supplementary C gives each lobe nine stored values, all pre-activation
   and y = z cross x completes R = [x y z]. (The supplement names the in-plane
   angle tau in the construction and psi in the derivatives; it is one angle,
   called psi here because tau is the anisotropy exponent of the lobe.)
-* bandwidths lam = exp(u), a = exp(u); frequency k = 20 (tanh(u) + 1);
+* bandwidths lam = exp(u), a = exp(u); frequency k = 20 (tanh(u) + 1),
+  evaluated as 40/(1 + e^{-2u}) (1 + tanh(u) of a tanh near -1 would lose the
+  digits of k);
 * colour weights w = tanh(u).
 
 A fourth value in the shape slot is the carrier phase zeta, passed through
@@ -47,8 +49,9 @@ def activate(frame_raw, shape_raw, rgbw_raw):
     f = np.asarray(frame_raw, np.float64)
     sr = np.asarray(shape_raw, np.float64)
     cos = np.tanh(f[..., :3])
-    shape = np.stack([np.exp(sr[..., 0]), np.exp(sr[..., 1]),
-                      20.0 * (np.tanh(sr[..., 2]) + 1.0), sr[..., 3]], -1)
+    with np.errstate(over="ignore"):
+        k = 40.0 / (1.0 + np.exp(-2.0 * sr[..., 2]))
+    shape = np.stack([np.exp(sr[..., 0]), np.exp(sr[..., 1]), k, sr[..., 3]], -1)
     w = np.tanh(np.asarray(rgbw_raw, np.float64))
     return cos, shape, w
 

@@ -179,3 +179,15 @@ def test_frame_gradient_finite_at_saturated_cosines():
     out, scale = Pp.forward_backward(wl.quat, wl.shape, wl.rgbw, wl.c0, wl.grad_rgb,
                                      R.NORM_EXACT, means=wl.means, cams=wl.cams)
     assert np.all(np.isfinite(out["quat"])) and np.all(np.isfinite(scale["quat"]))
+
+
+@pytest.mark.parametrize("u", [-300.0, -30.0, -18.0, -5.0, -0.1, 0.0, 0.3, 4.0, 30.0])
+def test_frequency_activation_keeps_its_digits(u):
+    """k = 20 (tanh u + 1) against 50 digits, also where tanh u is next to -1."""
+    import mpmath as mp
+    with mp.workdps(50):
+        want = 20 * (mp.tanh(mp.mpf(u)) + 1) if u > -100 else 40 * mp.e ** (2 * mp.mpf(u))
+        raw = np.zeros((1, 1, 4))
+        raw[..., 2] = u
+        got = Pp.activate(np.zeros((1, 1, 4)), raw, np.zeros((1, 3, 1)))[1][0, 0, 2]
+        assert abs(mp.mpf(float(got)) - want) <= mp.mpf(2) ** -50 * want
