@@ -293,13 +293,17 @@ __device__ inline float exp2_neg(double y) {
   return ldexpf(p, sat_int(n));
 }
 
-// Half phase of the carrier in units of pi, reduced to r in [-1/2, 1/2), given as
-// f = r + 1/2: cos(pi r) = pi v (1 + uc) and sin(pi r) = 2 r (1 + us) with v =
-// f (1 - f) (one FP64 rounding, so relatively accurate next to the cosine's zeros
-// at both ends). uc = v + O(v^2) and us = 2 v + O(v^2) are at most 0.28 and 0.58 and
-// vanish at those zeros, so FP32 holds them: own Remez fits with the leading
+// Half phase of the carrier in units of pi, reduced to r in [-1/2, 1/2] (exact):
+// cos(pi r) = pi v (1 + uc) and sin(pi r) = 2 r (1 + us) with v = 1/4 - r^2 formed
+// as b (1 - b), b = 1/2 - |r|, so that both are relatively accurate next to their
+// zeros. uc = v + O(v^2) and us = 2 v + O(v^2) are at most 0.28 and 0.58 and vanish
+// at the cosine's zeros, so FP32 holds them: own Remez fits with the leading
 // coefficients fixed at 1 and 2, 1.9e-9 and 1.0e-8 relative to cosine and sine,
 // 3e-8 and 6e-8 at most (rms 6e-9 and 1.3e-8) with their FP32 rounding.
+__device__ __forceinline__ double quarter_less_sq(double r) {
+  const double b = 0.5 - fabs(r);
+  return fma(-b, b, b);
+}
 __device__ __forceinline__ float cos_pi_u(float v) {
   float u = fmaf(v, 0.007639229607417381f, 0.06514647357787971f);
   u = fmaf(u, v, 0.35506860612312846f);
@@ -311,10 +315,10 @@ __device__ __forceinline__ float sin_pi_u(float v) {
   return v * fmaf(u, v, 2.f);
 }
 
-// (pi/2) tan(pi x) in FP64, x given as x + 1/2.
-__device__ inline double tan_pi(double xh) {
-  const double f = __builtin_amdgcn_fract(xh);
-  const double v = fma(-f, f, f), r = f - 0.5;
+// (pi/2) tan(pi x) in FP64.
+__device__ inline double tan_pi(double x) {
+  const double r = x - rint(x);
+  const double v = quarter_less_sq(r);
   const float vf = static_cast<float>(v);
   const double c = fma(v, static_cast<double>(cos_pi_u(vf)), v);
   return fma(r, static_cast<double>(sin_pi_u(vf)), r) * rcp64(c);
@@ -720,7 +724,7 @@ __device__ inline LobeNorm lobe_norm_f32(double lamd, double ad, double kd, doub
   out.dk = -czB * dPk;
   // d ln N/d zeta = sin(zeta) Psi/B = tan(zeta/2) (1 - (1 - Psi)/B)
   const float rho = om * iB;
-  out.dz = rho < 0.5f ? tan_pi(fma(zd, kInvTwoPi, 0.5)) * (1.0 - static_cast<double>(rho))
+  out.dz = rho < 0.5f ? tan_pi(zd * kInvTwoPi) * (1.0 - static_cast<double>(rho))
                       : static_cast<double>(static_cast<float>(0.5 * kPi) * (sz * psi * iB));
   return out;
 }

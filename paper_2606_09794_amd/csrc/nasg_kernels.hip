@@ -213,7 +213,7 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
       const double za0 = za[0], za1 = za[1], za2 = za[2];
       const double zd = NOCAR ? 0.0 : static_cast<double>(sh.w);
       const double kh = kd * kInvTwoPi;
-      const double zh = fma(zd, kInvTwoPi, 0.5);
+      const double zh = zd * kInvTwoPi;
       const LobeNorm nm = lobe_norm_any<!NOCAR>(lamd, ad, kd, zd, NOCAR ? 1 : a.norm);
       const float Nn = own ? nm.n : 0.f;
       const float kf = static_cast<float>((-2.0 / kPi) * kd);
@@ -276,7 +276,7 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
           const double dend = hd * q;                // 2 (1 - (d.z)^2)
           const float dx = static_cast<float>(dxd);
           // carrier c = cos^2(theta/2), theta = k d.x + zeta; its half phase in units
-          // of pi is reduced to an offset r in [-1/2, 1/2), exact in FP64, whose
+          // of pi is reduced to an offset r in [-1/2, 1/2], exact in FP64, whose
           // cosine and sine have the dropped integer's sign in common, so c and
           // dc/dtheta = -sin cos stay relatively accurate at the carrier's peaks and
           // zeros alike. car, scp and cz are c, -dc/dtheta and c d ln N/d zeta +
@@ -287,14 +287,14 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
           // small where it is small: dz v - r.
           float car = 1.f, scp = 0.f, cz = 0.f;
           if constexpr (!NOCAR) {
-            const double f = __builtin_amdgcn_fract(fma(dxd, kh, zh));   // r + 1/2
-            const double v = fma(-f, f, f);
+            const double th = fma(dxd, kh, zh);
+            const double r = th - rint(th);
+            const double v = quarter_less_sq(r);
             const float vf = static_cast<float>(v);
             const float uc = cos_pi_u(vf);
             const float cf = fmaf(vf, uc, vf);
             car = cf * cf;
             if constexpr (BWD) {
-              const double r = f - 0.5;
               const float rf = static_cast<float>(r);
               const float ru = rf * sin_pi_u(vf);
               scp = cf * (rf + ru);

@@ -173,3 +173,47 @@ def test_raw_weights_are_rounded_once():
     off = int((got[0] != want).sum())
     print(f"{off} of {3 * n} colours differ")
     assert off <= 4
+
+
+@pytest.mark.parametrize("v", [1, 2, 4, 16])
+def test_raw_gradients_at_the_reduction_steps(v):
+    """The gradients that the activations' exponentials feed (shape and quat among
+    them), with the raw bandwidths, frequency and frame on both sides of the
+    exponentials' reduction steps and at saturation, and ordinary weights."""
+    n, k = 1500, 8
+    w = W.draw_workload(950 + v, n, k, v, param="angles", with_sh=False)
+    rng = np.random.default_rng(v)
+    step = 0.5 * np.log(2.0)
+    edges = np.array([0.0, 1e-8, 1e-4, 0.5 * step, 0.999 * step, 1.001 * step, 2.999 * step, 3.001 * step, 1.0, 5.0])
+    pick = lambda size, more=(): (rng.choice(np.append(edges, more), size)  # noqa: E731
+                                  * rng.choice([-1.0, 1.0], size)).astype(np.float32)
+    w.shape[..., :2] = np.where(rng.random(w.shape[..., :2].shape) < 0.5, pick(w.shape[..., :2].shape), w.shape[..., :2])
+    w.shape[..., 2] = pick(w.shape.shape[:-1], (18.0, 380.0))
+    w.quat[..., :3] = np.where(rng.random(w.quat[..., :3].shape) < 0.3, pick(w.quat[..., :3].shape, (18.0,)),
+                               w.quat[..., :3])
+    d = upload(w)
+    fused = torch.empty((v, n, 3), device="cuda")
+    g = P.nasg_eval_bwd(d["quat"], d["shape"], d["rgbw"], d["c0"], d["grad_rgb"], means=d["means"],
+                        cams=d["cams"], param="angles", rgb_out=fused)
+    ref, scale = oracle_nasg(w, "exact")
+    compare(fused.cpu().numpy(), ref["rgb"], scale["rgb"], "rgb", TOL)
+    for name, x in g.items():
+        compare(x.cpu().numpy(), ref[name], scale[name], name, TOL)
+
+
+@pytest.mark.parametrize("lanes,vpl", [(4, 1), (8, 1), (16, 1), (8, 2), (8, 4)])
+@pytest.mark.parametrize("k", [1, 3, 8, 13])
+def test_broadcast_forward_has_the_one_lane_bits(k, lanes, vpl):
+    """Each broadcast mapping's colours equal those of one lane per primitive with
+    the same views per lane bit for bit, also with lanes left without a lobe."""
+    n, v = 700, vpl + 1
+    d = upload(W.draw_workload(31 * k + lanes, n, k, v, with_sh=False))
+    got = []
+    try:
+        for m in ((lanes, vpl, 256, 1), (1, vpl, 256, 0)):
+            P.set_tuning(0, k, v, 0, *m)
+            got.append(P.nasg_eval_fwd(d["quat"], d["shape"], d["rgbw"], d["c0"], means=d["means"], cams=d["cams"]))
+    finally:
+        P.set_tuning(0, k, v, 0, 0, 0)
+    torch.cuda.synchronize()
+    assert torch.equal(*got)
