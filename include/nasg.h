@@ -146,8 +146,8 @@ typedef enum nasg_param { NASG_PARAM_QUAT = 0, NASG_PARAM_ANGLES = 1 } nasg_para
  *              y = z x x, no normaliser (the table gives none).
  * SG, SB, SC and ASG take NASG_PARAM_QUAT only; `norm` is validated but used
  * by NASGabor only. The families other than NASGabor use a fixed lane
- * mapping by view and lobe count (tuning entries set the block size only) and are not
- * accepted by the persistent batch (NASG_ERR_MODE).                          */
+ * mapping by view and lobe count (tuning entries set the block size only) and
+ * are not accepted by the persistent batch (NASG_ERR_MODE).                  */
 typedef enum nasg_family {
   NASG_FAMILY_NASGABOR = 0,
   NASG_FAMILY_NASG = 1,
@@ -222,20 +222,20 @@ int sh3_eval_bwd(const float* sh, int64_t n, const nasg_views* views,
 /* ---- uneven multi-scene batches -------------------------------------------
  * Many independent scenes (different N, K and V), each evaluated exactly as
  * nasg_eval_bwd with a non-NULL rgb would (fused forward+backward, gradients
- * summed over that scene's views), in ONE persistent launch: the
- * scenes are cut into tiles of primitives, the tiles are ordered by cost (tile
- * size x K x V, largest first) and a grid of `blocks_per_cu` blocks per compute
- * unit pulls them from a device work queue. Each scene runs
- * the lane mapping the tuning table (nasg_set_tuning, kernel 1, its K and V,
- * float32) holds for it when the batch kernel carries that mapping -- (1, 1),
- * (1, 2), (1, 4), (4, 2), (4, 4) or (8, 2) -- and otherwise the one that
- * nasg_eval_bwd takes on its own: (1, 1), (1, 2), (1, 4) for V = 1, 2, 3..4,
- * (4, 2) for V = 5..8 and 17..24, (8, 2) for other V where K fills eight lanes
- * as well as four, else (4, 4); or (1, 4) where four lanes would leave too many
- * without a lobe and the scene's primitives fill the chip with one lane each (K =
- * 1, above V = 8 from N = 24577; V <= 8 with K = 2 and 5 from N = 98305, raw values
- * 196609). Gradient sums stay per primitive in registers and lanes (the queue
- * counter is the only atomic). Lobe parameters
+ * summed over that scene's views), in ONE persistent launch: the scenes are
+ * cut into tiles of primitives, the tiles are ordered by cost (tile size x K x
+ * V, largest first) and a grid of `blocks_per_cu` blocks per compute unit
+ * pulls them from a device work queue. Each scene runs the lane mapping the
+ * tuning table (nasg_set_tuning, kernel 1, its K and V, float32) holds for it
+ * when the batch kernel carries that mapping -- (1, 1), (1, 2), (1, 4), (4, 2),
+ * (4, 4) or (8, 2) -- and otherwise the one that nasg_eval_bwd takes on its
+ * own: (1, 1), (1, 2), (1, 4) for V = 1, 2, 3..4, (4, 2) for V = 5..8 and
+ * 17..24, (8, 2) for other V where K fills eight lanes as well as four, else
+ * (4, 4); or (1, 4) where four lanes would leave too many without a lobe and
+ * the scene's primitives fill the chip with one lane each (K = 1, above V = 8
+ * from N = 24577; V <= 8 with K = 2 and 5 from N = 98305, raw values 196609).
+ * Gradient sums stay per primitive in registers and lanes (the queue counter
+ * is the only atomic). Lobe parameters
  * must be float32 (NASG_F32).
  *
  * Use: nasg_batched_workspace_bytes -> caller allocates device memory ->
@@ -446,11 +446,12 @@ const char* nasg_status_string(int status);
  * bcast = 0 the views travel: each lane holds `views_per_lane` views of a
  * chunk of lanes * views_per_lane and passes them round the group, so every
  * lobe meets every view. With bcast = 1 every lane holds the same
- * `views_per_lane` views (a chunk of that many) and the per-view colour and
- * direction-gradient sums are reduced over the group afterwards: for few
- * views, it spreads a primitive's lobes over the lanes. V larger than a chunk
- * is processed in chunks, accumulated in place, so any accepted mapping
- * serves any V. Accepted (lanes, views_per_lane): bcast = 0: (1, 1), (1, 2),
+ * `views_per_lane` views (a chunk of that many): for few views, it spreads a
+ * primitive's lobes over the lanes. The backward reduces the per-view colour and
+ * direction-gradient sums over the group afterwards; the forward adds every
+ * lobe's colour in lobe order in each lane, so its colours have the bits of (1,
+ * views_per_lane). V larger than a chunk is processed in chunks, accumulated in
+ * place, so any accepted mapping serves any V. Accepted (lanes, views_per_lane): bcast = 0: (1, 1), (1, 2),
  * (1, 4), (2, 1), (2, 2), (2, 4), (4, 1), (4, 2), (4, 4), (8, 1), (8, 2),
  * (16, 1); bcast = 1 (NASGabor kernels 0 and 1 only): (4, 1), (8, 1),
  * (16, 1), (8, 2), (8, 4); others return NASG_ERR_SHAPE. nasg_set_tuning

@@ -298,7 +298,8 @@ BatchLayout batch_layout(const nasg_scene* sc, int32_t n, int32_t tile_iters) {
   BatchLayout L{};
   L.items_off = align_up(sizeof(nasg::BatchHeader) + sizeof(nasg::BatchScene) * n, 64);
   for (int32_t s = 0; s < n; ++s) {
-    const int64_t tile = static_cast<int64_t>(tile_iters) * (256 / nasg::kBatchLanes[batch_variant(sc[s].p.n, sc[s].p.k, sc[s].views.v, sc[s].p.param)]);
+    const int var = batch_variant(sc[s].p.n, sc[s].p.k, sc[s].views.v, sc[s].p.param);
+    const int64_t tile = static_cast<int64_t>(tile_iters) * (256 / nasg::kBatchLanes[var]);
     L.n_items += (sc[s].p.n + tile - 1) / tile;
   }
   L.total = L.items_off + sizeof(nasg::BatchItem) * static_cast<size_t>(L.n_items);

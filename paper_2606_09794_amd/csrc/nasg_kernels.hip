@@ -52,9 +52,9 @@ namespace nasg {
 // a = e^u, k = 20 (tanh u + 1), w = tanh u, with the derivatives of k and w.
 // With the frame's three cosines they are nine exponentials a lobe, over a
 // third of the instructions of a lobe with one view. Exponentials that a
-// division follows are carried as a fraction, the weights' polynomials stop at
-// what FP32 keeps, and the forward leaves out the derivatives: 270 -> 190 FP64
-// instructions (K = 8, 1 M x 1: forward 223 -> 202 us, backward 301 -> 287).
+// division follows are carried as a fraction and the forward leaves out the
+// derivatives: 270 -> 196 FP64 instructions (K = 8, 1 M x 1: forward 223 -> 202
+// us, backward 301 -> 287).
 // Inlined where two waves per SIMD leave the registers (backward 287 -> 273, x 2
 // 318 -> 299; forward x 2 246 -> 224); at three waves, and with four views per
 // lane in the backward, it would spill (202 -> 284; 374 -> 395) and is called.
@@ -112,8 +112,9 @@ constexpr int mapping_waves(int lanes, int vpl, bool bc, bool ang, bool bwd) {
 // against all of them with no slot transfer, and the per-view colour and
 // direction-gradient partials are summed over the lane group at the end (DPP);
 // the forward instead adds each lobe's colour in lobe order, in every lane of
-// the group, so that its bits are those of the one-lane mapping. For few views this spreads a primitive over P lanes (P lobes prepared and
-// loaded at once) instead of one lane walking all of them.
+// the group, so that its bits are those of the one-lane mapping. For few views
+// this spreads a primitive over P lanes (P lobes prepared and loaded at once)
+// instead of one lane walking all of them.
 template <int P, int VPL, bool BWD, bool BF16, bool ANG, bool NOCAR = false, bool BC = false,
           bool ONE = false, bool ONCE = false,
           bool PF = (ONE && (!BWD || P == 1 || VPL == 1)) || mapping_waves(P, VPL, false, ANG, BWD) == 2>

@@ -1153,9 +1153,10 @@ static void launch_bwd(const RasterArgs& a, int64_t n_tiles, hipStream_t s) {
 // Primitives per LDS-counting block: 1024 threads hide the latency of the
 // record loads and LDS atomics that a block of 256 left bare (3 M primitives
 // at 1920 x 1080: 366 -> 259 us, with four per thread; eight 278, two blocks
-// per CU are then all that fit); fewer primitives take smaller chunks, so that
-// at least 128 blocks share them (500 k at 1280 x 720: 171 -> 36 us, with one
-// per thread 45, whose blocks send more device atomics; 12 k: 48 -> 5 us).
+// per CU are then all that fit); fewer primitives take smaller chunks, of at least
+// 1024: 128 blocks or more for each tile class from 131 072 primitives on, n/1024
+// of them below (500 k at 1280 x 720: 171 -> 36 us, with one per thread 45, whose
+// blocks send more device atomics; 12 k, 13 blocks: 48 -> 5 us).
 static int64_t bin_chunk(int64_t n) {
   return kBinThreads * std::min<int64_t>(4, std::max<int64_t>(1, n / (kBinThreads * 128)));
 }
