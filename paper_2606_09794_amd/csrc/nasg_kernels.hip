@@ -293,9 +293,10 @@ __device__ __forceinline__ void nasg_body(const NasgArgs& a, int64_t prim, int j
             const double v = quarter_less_sq(r);
             const float vf = static_cast<float>(v);
             const float uc = cos_pi_u(vf);
-            const float cf = fmaf(vf, uc, vf);
-            car = cf * cf;
+            const double cr = fma(v, static_cast<double>(uc), v);
+            car = static_cast<float>(cr * cr);
             if constexpr (BWD) {
+              const float cf = fmaf(vf, uc, vf);
               const float rf = static_cast<float>(r);
               const float ru = rf * sin_pi_u(vf);
               scp = cf * (rf + ru);
