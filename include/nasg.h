@@ -146,7 +146,7 @@ typedef enum nasg_param { NASG_PARAM_QUAT = 0, NASG_PARAM_ANGLES = 1 } nasg_para
  *              y = z x x, no normaliser (the table gives none).
  * SG, SB, SC and ASG take NASG_PARAM_QUAT only; `norm` is validated but used
  * by NASGabor only. The families other than NASGabor use a fixed lane
- * mapping by view and lobe count (tuning entries set the block size only) and
+ * mapping by N, view and lobe count (tuning entries set the block size only) and
  * are not accepted by the persistent batch (NASG_ERR_MODE).                  */
 typedef enum nasg_family {
   NASG_FAMILY_NASGABOR = 0,

@@ -253,7 +253,7 @@ static hipError_t launch_f(const NasgArgs& a, bool bwd, bool bf16, int block, hi
 template <int FAM>
 static hipError_t launch_fam(const NasgArgs& a, bool bwd, bool bf16, int block, hipStream_t s) {
   int lanes, vpl;
-  family_mapping(a.k, a.v, lanes, vpl);
+  family_mapping(a.n, a.k, a.v, lanes, vpl);
   switch (lanes) {
     case 1: return launch_f<1, 1, FAM>(a, bwd, bf16, block, s);
     case 2: return launch_f<2, 2, FAM>(a, bwd, bf16, block, s);

@@ -574,9 +574,9 @@ static hipError_t launch_pv(const NasgArgs& a, bool bwd, bool bf16, int block, h
 hipError_t launch_nasg(const NasgArgs& a, int lanes, int vpl, bool bcast, bool bwd, bool bf16,
                        int block, hipStream_t s) {
   if (a.family == kFamNasg) {
-    // NASG lobes: the compiled family mappings, chosen by view count
+    // NASG lobes: the compiled family mappings
     int fl, fv;
-    family_mapping(a.k, a.v, fl, fv);
+    family_mapping(a.n, a.k, a.v, fl, fv);
     switch (fl) {
       case 1: return launch_pv<1, 1, true>(a, bwd, bf16, block, s);
       case 2: return launch_pv<2, 2, true>(a, bwd, bf16, block, s);

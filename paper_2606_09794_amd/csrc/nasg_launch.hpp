@@ -41,12 +41,18 @@ constexpr int kFamSb = 3;
 constexpr int kFamSc = 4;
 constexpr int kFamAsg = 5;
 
-// The lane mappings compiled for the families other than NASGabor, by view
-// count: (1, 1) for V = 1, (2, 2) up to 4, (4, 2) up to 8, (8, 2) above, but
-// no more lanes than the lobes round up to (lanes beyond them do nothing).
-inline void family_mapping(int k, int v, int& lanes, int& vpl) {
+// The lane mappings compiled for the families other than NASGabor: by view count
+// (1, 1) for V = 1, (2, 2) up to 4, (4, 2) up to 8, (8, 2) above; given primitives
+// enough to fill the chip without them, lanes beyond the lobes are left out, down to
+// two (a lane alone holds one view: K = 1, 200 000 x 16, backward 0.67 of eight
+// lanes' time, two lanes 0.56). Few primitives need the lanes: backward, x 16, times
+// of fewer lanes over eight lanes', mean of ASG, SG and NASG: four, K <= 4, 1.19 at
+// 4096, 0.98 at 8192, 0.84 at 24 576; two, K <= 2, 1.27 at 8192, 1.02 at 24 576 (four
+// 0.84), 0.68 at 49 152; x 8, two over four lanes, 1.10 at 32 768, 0.97 at 49 152.
+inline void family_mapping(int64_t n, int k, int v, int& lanes, int& vpl) {
   lanes = v <= 1 ? 1 : v <= 4 ? 2 : v <= 8 ? 4 : 8;
-  while (lanes > 1 && lanes / 2 >= k) lanes /= 2;
+  if (lanes == 8 && k <= 4 && n > 8192) lanes = 4;
+  if (lanes >= 4 && k <= 2 && n > 40960) lanes = 2;
   vpl = lanes == 1 ? 1 : 2;
 }
 

@@ -217,3 +217,59 @@ def test_broadcast_forward_has_the_one_lane_bits(k, lanes, vpl):
         P.set_tuning(0, k, v, 0, 0, 0)
     torch.cuda.synchronize()
     assert torch.equal(*got)
+
+
+def _graph_us(fn):
+    """Device time of one call: the fastest of several replays of four."""
+    s, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        fn()
+        s.synchronize()
+        with torch.cuda.graph(g, stream=s):
+            for _ in range(4):
+                fn()
+    a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    best = float("inf")
+    for _ in range(20):
+        a.record()
+        g.replay()
+        b.record()
+        b.synchronize()
+        best = min(best, 250.0 * a.elapsed_time(b))
+    return best
+
+
+@pytest.mark.parametrize("family", ["nasg", "sg", "asg"])
+@pytest.mark.parametrize("k,v", [(1, 7), (1, 16), (2, 16), (1, 24)])
+def test_few_lobes_take_no_longer_than_eight(family, k, v):
+    """Few primitives need the lanes however few lobes they have: a backward of
+    one or two lobes (two to three and a half times that of eight, where its lanes
+    followed the lobes at any N) against that of eight, with a third for noise."""
+    us = []
+    for lobes in (k, 8):
+        w = W.draw_workload(5, 4096, lobes, v, family=family, with_sh=False)
+        d = upload(w)
+        grads = P.nasg_grad_buffers(lobes, 4096, "cuda")
+        us.append(_graph_us(lambda: P.nasg_eval_bwd(
+            d["quat"], d["shape"], d["rgbw"], d["c0"], d["grad_rgb"], means=d["means"], cams=d["cams"],
+            family=family, grads=grads)))
+    assert us[0] <= 1.33 * us[1], us
+
+
+@pytest.mark.parametrize("family", ["nasg", "asg"])
+@pytest.mark.parametrize("n,k,v", [(8192, 4, 9), (8193, 4, 9), (8193, 5, 9), (40960, 2, 5), (40961, 2, 5),
+                                   (40961, 1, 17), (40961, 3, 16)])
+def test_family_shapes(family, n, k, v):
+    w = W.draw_workload(n + k, n, k, v, family=family, with_sh=False)
+    d = upload(w)
+    idx, sub = _take(w)
+    ref, scale = oracle_nasg(sub, "exact")
+    kw = dict(means=d["means"], cams=d["cams"], family=family)
+    rgb = P.nasg_eval_fwd(d["quat"], d["shape"], d["rgbw"], d["c0"], **kw)
+    g = P.nasg_eval_bwd(d["quat"], d["shape"], d["rgbw"], d["c0"], d["grad_rgb"], **kw)
+    torch.cuda.synchronize()
+    t = torch.from_numpy(idx).cuda()
+    for name, x in (("rgb", rgb[:, t]), ("quat", g["quat"][:, t]), ("shape", g["shape"][:, t]),
+                    ("rgbw", g["rgbw"][:, :, t]), ("c0", g["c0"][t]), ("geom", g["geom"][t])):
+        compare(x.cpu().numpy(), ref[name], scale[name], name, TOL)
