@@ -90,18 +90,20 @@ nasg_tuning shape_of(int64_t n, int lanes, int vpl, int bcast = 0) {
 // repeat the loads and sums), so V = 17..24 take three chunks of (4, 2) rather
 // than two of 16 views (K = 8, V = 24, N = 1 M, backward: 1209 against 1286
 // us). One lane in several passes costs 1.4 times four lanes that all have a
-// lobe, so it serves K = 1, 2 and 5 up to eight views (K = 1, N = 1.5 M, V = 8:
-// 355 -> 236; K = 2 375 -> 320; forward K = 1 188 -> 78) and K = 1 beyond
-// (V = 16: 572 -> 459; K = 2 stays, 570 against 640), given primitives enough
-// to fill the chip with one lane each: K = 1, V = 16 16.1 against 20.7 us at
-// 20 000, 22 against 20 at 33 000; K = 2, V = 8 22 against 25 at 70 000, 30
-// against 28 at 105 000; with raw values, whose activations a spread primitive
-// shares out, 51 against 57 at 160 000. (N enters here and not only in
+// lobe, so it serves K = 1 and, up to eight views, K = 2 (N = 1.5 M, V = 8: K = 1
+// 355 -> 236 us, K = 2 375 -> 320, forward K = 1 188 -> 78; K = 1, V = 16 572 ->
+// 459, K = 2 stays, 570 against 640; K = 5, V = 8 stays, its forward 0.85 of four
+// lanes' time, its backward 1.15), given primitives enough to fill the chip with
+// one lane each. Its time over four lanes' in the backward: K = 1, V = 8 1.34 at
+// 4096, 1.06 at 32 768, 0.89 at 49 152; V = 16 1.66, 1.22, 0.90; with raw values,
+// whose activations a spread primitive shares out, 2.00, 1.45, 1.07, 0.90 at
+// 65 536; K = 2, V = 8 22 us against 25 at 70 000, 30 against 28 at 105 000, with
+// raw values 51 against 57 at 160 000. (N enters here and not only in
 // nasg_shape because the persistent batch follows the same rule.)
 void mapping_at_scale(int64_t n, int k, int v, bool raw, int* lanes, int* vpl) {
   const int four = (k + 3) / 4 * 4;
-  if (v <= 4 || (k == 1 && (v <= 8 || n > 24576)) ||
-      (v <= 8 && 7 * k < 5 * four && n > (raw ? 196608 : 98304))) {
+  if (v <= 4 || (k == 1 && n > (raw ? 57344 : 40960)) ||
+      (k == 2 && v <= 8 && n > (raw ? 196608 : 98304))) {
     *lanes = 1;
     *vpl = v <= 1 ? 1 : v <= 2 ? 2 : 4;
     return;
@@ -132,10 +134,6 @@ nasg_tuning nasg_shape(bool bwd, bool bf16, int64_t n, int k, int v, bool raw) {
   }
   if (v <= 4) return k >= 3 && fits(8, kFillLanes) ? shape_of(n, 8, vpl, 1) : scale;
   if (!bf16) return scale;
-  if (lanes == 1) {
-    if (fits(4, kFillLanes / 2)) return shape_of(n, 4, v <= 8 ? 2 : 4);
-    return fits(2, kFillLanes) && k > 1 ? shape_of(n, 2, bwd ? 2 : 4) : scale;
-  }
   if (v <= 8) {
     if (k >= 16 && fits(16, kFillLanes / 2)) return shape_of(n, 16, 1);
     return k >= 8 && fits(8, kFillLanes) ? shape_of(n, 8, 1) : scale;

@@ -273,3 +273,33 @@ def test_family_shapes(family, n, k, v):
     for name, x in (("rgb", rgb[:, t]), ("quat", g["quat"][:, t]), ("shape", g["shape"][:, t]),
                     ("rgbw", g["rgbw"][:, :, t]), ("c0", g["c0"][t]), ("geom", g["geom"][t])):
         compare(x.cpu().numpy(), ref[name], scale[name], name, TOL)
+
+
+@pytest.mark.parametrize("n,v,param", [(4096, 7, "quat"), (4096, 8, "angles"), (30000, 16, "quat"),
+                                       (30000, 16, "angles")])
+def test_one_lobe_keeps_four_lanes_for_few_primitives(n, v, param):
+    """The built-in choice against four lanes per primitive, which take 0.5 to
+    0.8 of one lane's time here; a ninth for noise."""
+    w = W.draw_workload(6, n, 1, v, param=param, with_sh=False)
+    d = upload(w)
+    grads = P.nasg_grad_buffers(1, n, "cuda")
+
+    def us():
+        return _graph_us(lambda: P.nasg_eval_bwd(
+            d["quat"], d["shape"], d["rgbw"], d["c0"], d["grad_rgb"], means=d["means"], cams=d["cams"],
+            param=param, grads=grads))
+
+    built_in = us()
+    try:
+        P.set_tuning(1, 1, v, 0, 4, 2 if v <= 8 else 4, 64 if 4 * n <= 32768 else 128)
+        four = us()
+    finally:
+        P.set_tuning(1, 1, v, 0, 0, 0)
+    assert built_in <= 1.11 * four, (built_in, four)
+
+
+@pytest.mark.parametrize("n,k,v,param", [(40960, 1, 7, "quat"), (40961, 1, 7, "quat"), (40961, 1, 16, "quat"),
+                                         (57344, 1, 16, "angles"), (57345, 1, 16, "angles"),
+                                         (98305, 5, 8, "quat")])
+def test_batch_follows_the_one_lobe_lines(n, k, v, param):
+    test_batch_follows_the_shape_by_n(n, k, v, param)
