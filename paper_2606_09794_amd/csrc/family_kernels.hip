@@ -56,6 +56,10 @@ __device__ __forceinline__ void family_body(const NasgArgs& a, int64_t prim, int
       const float w0 = S::wide(S::template raw1<false>(a.rgbw, wi));
       const float w1 = S::wide(S::template raw1<false>(a.rgbw, wi + N));
       const float w2 = S::wide(S::template raw1<false>(a.rgbw, wi + 2 * N));
+      // keeps the weights' loads ahead of the frame, where the scheduler moves them
+      // behind it (K = 16, 30 000 x 1, backward: 20.9 us, 16.3 ahead); the other
+      // kernels load ahead by themselves and lose by a fence (5 to 20 % at x 1)
+      if constexpr (FAM == kFamSg && P == 1 && BWD) __builtin_amdgcn_sched_barrier(0);
       double xa[3], za[3], ya[3] = {0.0, 0.0, 0.0};
       float f[6];
       lobe_frame<false>(q, xa, za, f);
@@ -183,9 +187,12 @@ __device__ __forceinline__ void family_body(const NasgArgs& a, int64_t prim, int
           }
           if constexpr (P > 1) {
             slot_pass<P, VPL, BWD>(sl, t, rot_addr);
-            // SG and SC: one view's registers at a time (K = 4, backward, 1 M x
-            // 4, SC: 117 us, 127 without); ASG and SB are faster free (131 -> 121)
-            if constexpr (FAM == kFamSg || FAM == kFamSc) __builtin_amdgcn_sched_barrier(0);
+            // one view's registers at a time (K = 4, backward, 1 M x 4, SC: 117 us,
+            // 127 without; forward, K = 8, 120 000 x 8, ASG: 17.5, 18.8 without); faster
+            // free: the backward of ASG and SB (131 -> 121), the forward on two lanes
+            // (K = 8, 600 000 x 3, SG: 43.9 -> 42.9; not SC's)
+            if constexpr (FAM == kFamSc || (BWD ? FAM == kFamSg : P >= 4))
+              __builtin_amdgcn_sched_barrier(0);
           }
         }
       }
@@ -253,7 +260,7 @@ static hipError_t launch_f(const NasgArgs& a, bool bwd, bool bf16, int block, hi
 template <int FAM>
 static hipError_t launch_fam(const NasgArgs& a, bool bwd, bool bf16, int block, hipStream_t s) {
   int lanes, vpl;
-  family_mapping(a.n, a.k, a.v, lanes, vpl);
+  family_mapping(bwd, a.n, a.k, a.v, lanes, vpl);
   switch (lanes) {
     case 1: return launch_f<1, 1, FAM>(a, bwd, bf16, block, s);
     case 2: return launch_f<2, 2, FAM>(a, bwd, bf16, block, s);

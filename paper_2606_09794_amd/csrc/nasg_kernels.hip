@@ -576,7 +576,7 @@ hipError_t launch_nasg(const NasgArgs& a, int lanes, int vpl, bool bcast, bool b
   if (a.family == kFamNasg) {
     // NASG lobes: the compiled family mappings
     int fl, fv;
-    family_mapping(a.n, a.k, a.v, fl, fv);
+    family_mapping(bwd, a.n, a.k, a.v, fl, fv);
     switch (fl) {
       case 1: return launch_pv<1, 1, true>(a, bwd, bf16, block, s);
       case 2: return launch_pv<2, 2, true>(a, bwd, bf16, block, s);

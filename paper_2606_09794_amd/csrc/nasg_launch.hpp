@@ -43,16 +43,19 @@ constexpr int kFamAsg = 5;
 
 // The lane mappings compiled for the families other than NASGabor: by view count
 // (1, 1) for V = 1, (2, 2) up to 4, (4, 2) up to 8, (8, 2) above; given primitives
-// enough to fill the chip without them, lanes beyond the lobes are left out, down to
-// two (a lane alone holds one view: K = 1, 200 000 x 16, backward 0.67 of eight
-// lanes' time, two lanes 0.56). Few primitives need the lanes: backward, x 16, times
+// enough to fill the chip without them, lanes beyond the lobes are left out, in the
+// backward down to two (a lane alone holds one view: K = 1, 200 000 x 16 0.67 of
+// eight lanes' time, two lanes 0.56; forward 0.46 both, 600 000 x 33 88 against
+// 103 us, x 3 14.4 against 17). Few primitives need the lanes: backward, x 16, times
 // of fewer lanes over eight lanes', mean of ASG, SG and NASG: four, K <= 4, 1.19 at
 // 4096, 0.98 at 8192, 0.84 at 24 576; two, K <= 2, 1.27 at 8192, 1.02 at 24 576 (four
-// 0.84), 0.68 at 49 152; x 8, two over four lanes, 1.10 at 32 768, 0.97 at 49 152.
-inline void family_mapping(int64_t n, int k, int v, int& lanes, int& vpl) {
+// 0.84), 0.68 at 49 152; x 8, two over four lanes, 1.10 at 32 768, 0.97 at 49 152;
+// forward, x 4, one over two, 1.13 at 98 304, 0.97 at 196 608.
+inline void family_mapping(bool bwd, int64_t n, int k, int v, int& lanes, int& vpl) {
   lanes = v <= 1 ? 1 : v <= 4 ? 2 : v <= 8 ? 4 : 8;
   if (lanes == 8 && k <= 4 && n > 8192) lanes = 4;
   if (lanes >= 4 && k <= 2 && n > 40960) lanes = 2;
+  if (!bwd && k == 1 && n > 131072) lanes = 1;
   vpl = lanes == 1 ? 1 : 2;
 }
 
