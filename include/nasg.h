@@ -232,8 +232,9 @@ int sh3_eval_bwd(const float* sh, int64_t n, const nasg_views* views,
  * own: (1, 1), (1, 2), (1, 4) for V = 1, 2, 3..4, (4, 2) for V = 5..8 and
  * 17..24, (8, 2) for other V where K fills eight lanes as well as four, else
  * (4, 4); or (1, 4) where four lanes would leave too many without a lobe and
- * the scene's primitives fill the chip with one lane each (K = 1 from N = 40961,
- * raw values 57345; K = 2 and V <= 8 from N = 98305, raw values 196609).
+ * the scene's primitives fill the chip with one lane each (K = 1 from N = 16385
+ * for V <= 8, 40961 above, raw values 57345; K = 2 and V <= 8 from N = 98305, raw
+ * values 196609).
  * Gradient sums stay per primitive in registers and lanes (the queue counter
  * is the only atomic). Lobe parameters
  * must be float32 (NASG_F32).

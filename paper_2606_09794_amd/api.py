@@ -238,14 +238,19 @@ class NasgBatchPlan:
     keeps references to every tensor it points at; ``run()`` only launches
     kernels and can be captured into a CUDA/HIP graph. ``tile_iters`` and
     ``blocks_per_cu`` default to the tuner's cached choice (autotune.tune_batch),
-    ``tile_iters`` halved while the scenes give fewer than ``MIN_TILES`` tiles."""
+    ``tile_iters`` halved while the scenes give fewer than ``MIN_TILES`` tiles of
+    at least twice ``MIN_TILE_WORK`` lobe-views on average."""
 
     # A block pulls a tile at a time and 512 are resident (two per CU): with a
     # few tiles each, the last ones decide the time. 48 scenes of 1e3 to 1e5
     # primitives (2 000, 3 900, 7 800, 15 600 tiles of 8, 4, 2, 1 passes): 695,
     # 611, 573, 591 us; 6 scenes of 3.1e4 in all: 251 us in 36 tiles, 46 in 265;
     # 32 large scenes take 8 passes (18 800 tiles) as well as 2.
+    # Pulling and setting up a tile costs about as much as 100 lobe-views of its
+    # primitives: 64 scenes of 8000, K = 1, V = 1 (512, 1024, 2048 tiles) 35, 37, 44
+    # us, K = 1, V = 7 (2048, 4032, 8000) 145, 140, 154.
     MIN_TILES = 6144
+    MIN_TILE_WORK = 512
 
     def __init__(self, scenes, norm="exact", tile_iters=None, blocks_per_cu=None):
         adapt = tile_iters is None
@@ -286,7 +291,8 @@ class NasgBatchPlan:
 
     @classmethod
     def _adapted(cls, arr, tile_iters, blocks_per_cu) -> int:
-        """``tile_iters`` halved until there are MIN_TILES tiles (or it is 1)."""
+        """``tile_iters`` halved until there are MIN_TILES tiles, or halves of them
+        would hold less than MIN_TILE_WORK (or it is 1)."""
         def size(scenes, ti):
             return L.lib().nasg_batched_workspace_bytes(
                 scenes, len(scenes), C.byref(L.NasgBatchTuning(ti, blocks_per_cu)))
@@ -294,7 +300,11 @@ class NasgBatchPlan:
         for sc in empty:
             sc.p.n = 0
         item = 16                                   # bytes of a tile's record
-        while tile_iters > 1 and size(arr, tile_iters) - size(empty, tile_iters) < cls.MIN_TILES * item:
+        work = sum(sc.p.n * sc.p.k * sc.views.v for sc in arr)
+        while tile_iters > 1:
+            tiles = (size(arr, tile_iters) - size(empty, tile_iters)) // item
+            if tiles >= cls.MIN_TILES or work < 2 * tiles * cls.MIN_TILE_WORK:
+                break
             tile_iters //= 2
         return tile_iters
 

@@ -95,14 +95,16 @@ nasg_tuning shape_of(int64_t n, int lanes, int vpl, int bcast = 0) {
 // 459, K = 2 stays, 570 against 640; K = 5, V = 8 stays, its forward 0.85 of four
 // lanes' time, its backward 1.15), given primitives enough to fill the chip with
 // one lane each. Its time over four lanes' in the backward: K = 1, V = 8 1.34 at
-// 4096, 1.06 at 32 768, 0.89 at 49 152; V = 16 1.66, 1.22, 0.90; with raw values,
-// whose activations a spread primitive shares out, 2.00, 1.45, 1.07, 0.90 at
-// 65 536; K = 2, V = 8 22 us against 25 at 70 000, 30 against 28 at 105 000, with
-// raw values 51 against 57 at 160 000. (N enters here and not only in
-// nasg_shape because the persistent batch follows the same rule.)
+// 4096, 1.07 at 16 384, 1.06 at 32 768, 0.89 at 49 152; V = 16 1.66, 1.22, 1.22, 0.90;
+// with raw values, whose activations a spread primitive shares out, 2.00, 1.47, 1.45,
+// 1.07, and 0.90 at 65 536; K = 2, V = 8 22 us against 25 at 70 000, 30 against 28 at
+// 105 000, with raw values 51 against 57 at 160 000. (N enters here and not only in
+// nasg_shape because the persistent batch follows the same rule: there the other
+// scenes fill the chip, which is why the line of K = 1, V <= 8 lies at its first
+// near tie: 16 scenes of 20 000, V = 7, 55 us on one lane, 109 on four.)
 void mapping_at_scale(int64_t n, int k, int v, bool raw, int* lanes, int* vpl) {
   const int four = (k + 3) / 4 * 4;
-  if (v <= 4 || (k == 1 && n > (raw ? 57344 : 40960)) ||
+  if (v <= 4 || (k == 1 && n > (raw ? 57344 : v <= 8 ? 16384 : 40960)) ||
       (k == 2 && v <= 8 && n > (raw ? 196608 : 98304))) {
     *lanes = 1;
     *vpl = v <= 1 ? 1 : v <= 2 ? 2 : 4;

@@ -300,7 +300,7 @@ def test_one_lobe_keeps_four_lanes_for_few_primitives(n, v, param):
     assert built_in <= 1.11 * four, (built_in, four)
 
 
-@pytest.mark.parametrize("n,k,v,param", [(40960, 1, 7, "quat"), (40961, 1, 7, "quat"), (40961, 1, 16, "quat"),
+@pytest.mark.parametrize("n,k,v,param", [(16384, 1, 7, "quat"), (16385, 1, 7, "quat"), (40961, 1, 16, "quat"),
                                          (57344, 1, 16, "angles"), (57345, 1, 16, "angles"),
                                          (98305, 5, 8, "quat")])
 def test_batch_follows_the_one_lobe_lines(n, k, v, param):
@@ -314,3 +314,16 @@ def test_one_view_of_sg_waits_for_its_records_once():
     us = _device_us(*[_bwd_graph(W.draw_workload(7, 30000, 16, 1, family=family, with_sh=False))
                       for family in ("sg", "asg")])
     assert us[0] <= 0.94 * us[1], us
+
+
+def test_batch_keeps_cheap_tiles_whole():
+    """A plan's own tile size does not cut one-view, one-lobe scenes into tiles
+    that cost less than their turn in the queue."""
+    scenes = []
+    for _ in range(16):
+        d = upload(W.draw_workload(9, 8000, 1, 1, with_sh=False))
+        d["grads"] = P.nasg_grad_buffers(1, 8000, "cuda")
+        scenes.append(d)
+    whole = P.NasgBatchPlan(scenes, tile_iters=8).n_items
+    n_items = P.NasgBatchPlan(scenes).n_items
+    assert whole < n_items and 16 * 8000 >= 384 * n_items
