@@ -174,8 +174,11 @@ nasg_tuning sh_shape(bool bwd, int64_t n, int v) {
   p = std::min(p, std::min(16, pow2_at_least(v)));
   const int most = p >= 16 ? 1 : p >= 8 ? 2 : 4;
   nasg_tuning t = shape_of(n, p, std::min(most, pow2_at_least((v + p - 1) / p)));
-  // the forward's long launches: V = 16, N = 520 000 39.6 against 44.4 us
-  if (!bwd && p == 1 && n > 393216) t.block = 128;
+  // long launches: forward, V = 16, N = 520 000 39.6 against 44.4 us; backward, V = 1,
+  // N = 2^19 41.3 against 47.7, 2^20 83 against 99 (coefficient rows a power of two
+  // apart; 1 M 78.4 against 78.7, 3 M 228 against 232); from four views on 2^21 loses
+  // what 2^19 gains (188 against 182, 48 against 54)
+  if (p == 1 && n > 393216 && (!bwd || v <= 2)) t.block = 128;
   return t;
 }
 

@@ -327,3 +327,9 @@ def test_batch_keeps_cheap_tiles_whole():
     whole = P.NasgBatchPlan(scenes, tile_iters=8).n_items
     n_items = P.NasgBatchPlan(scenes).n_items
     assert whole < n_items and 16 * 8000 >= 384 * n_items
+
+
+@pytest.mark.parametrize("n", [393216, 393217])
+@pytest.mark.parametrize("v", [1, 2])
+def test_sh_block_line(n, v):
+    test_sh_shapes(n, v)
