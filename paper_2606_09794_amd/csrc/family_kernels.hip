@@ -57,9 +57,11 @@ __device__ __forceinline__ void family_body(const NasgArgs& a, int64_t prim, int
       const float w1 = S::wide(S::template raw1<false>(a.rgbw, wi + N));
       const float w2 = S::wide(S::template raw1<false>(a.rgbw, wi + 2 * N));
       // keeps the weights' loads ahead of the frame, where the scheduler moves them
-      // behind it (K = 16, 30 000 x 1, backward: 20.9 us, 16.3 ahead); the other
-      // kernels load ahead by themselves and lose by a fence (5 to 20 % at x 1)
-      if constexpr (FAM == kFamSg && P == 1 && BWD) __builtin_amdgcn_sched_barrier(0);
+      // behind it (SG, K = 16, 30 000 x 1, backward: 20.9 us, 16.3 ahead; ASG in bfloat16,
+      // K = 16, 20 000 x 2, forward: 11.0, 9.5); the other kernels load ahead by
+      // themselves and lose by a fence (5 to 20 % at x 1)
+      if constexpr (BWD ? FAM == kFamSg && P == 1 : BF16 && FAM == kFamAsg && P > 1)
+        __builtin_amdgcn_sched_barrier(0);
       double xa[3], za[3], ya[3] = {0.0, 0.0, 0.0};
       float f[6];
       lobe_frame<false>(q, xa, za, f);
@@ -190,8 +192,8 @@ __device__ __forceinline__ void family_body(const NasgArgs& a, int64_t prim, int
             // one view's registers at a time (K = 4, backward, 1 M x 4, SC: 117 us,
             // 127 without; forward, K = 8, 120 000 x 8, ASG: 17.5, 18.8 without); faster
             // free: the backward of ASG and SB (131 -> 121), the forward on two lanes
-            // (K = 8, 600 000 x 3, SG: 43.9 -> 42.9; not SC's)
-            if constexpr (FAM == kFamSc || (BWD ? FAM == kFamSg : P >= 4))
+            // (K = 8, 600 000 x 3, SG: 43.9 -> 42.9; not SC's, nor ASG's in bfloat16)
+            if constexpr (FAM == kFamSc || (BWD ? FAM == kFamSg : P >= 4 || (BF16 && FAM == kFamAsg)))
               __builtin_amdgcn_sched_barrier(0);
           }
         }
