@@ -18,12 +18,12 @@
 // |d + z|^2 = 4 kappa (relatively accurate next to the antipode, where
 // 1 + d.z would cancel), h = 1 - d.z and 1 - (d.z)^2 are FP64 (the lobes reach
 // lambda (1 + a) ~ 1e6, where FP32 rounding of d.z alone moves G by ~1e-4);
-// the carrier phase is reduced in FP64 to its offset from the nearest peak or
-// zero, which keeps the carrier and its derivative relatively accurate at its
-// peaks and zeros; the envelope exponent ln(p E) is formed in
-// FP64 (exp turns its absolute error into a relative error of G) and only
-// its final exponential, the carrier's sine/cosine and all gradient factors
-// and accumulations are FP32. The normaliser and its log-derivatives are
+// the carrier's half phase is reduced in FP64 to an exact offset, of which the
+// carrier and the zeta gradient's two cancelling terms are formed in FP64 up to
+// FP32 corrections, relatively accurate at the carrier's peaks and zeros; the
+// envelope exponent ln(p E) is formed in FP64 (exp turns its absolute error into
+// a relative error of G) and only its final exponential, the other gradient
+// factors and all accumulations are FP32. The normaliser and its log-derivatives are
 // formed once per lobe: in FP32 where lam >= 1/2 and lam (1 + a) >= 3/2
 // (with the cancellation-prone pieces in FP64), in FP64 elsewhere.
 //
@@ -93,7 +93,7 @@ __device__ __noinline__ Activated activate_call(float4 sh, float w0, float w1, f
 // chains that two leave bare, and fewer spills leave room for it (backward: K =
 // 8, 3 M x 16 on (8, 2) 2069 -> 1892 us, where (4, 4) at two waves takes 2027; K
 // = 16 in bfloat16, 2 M x 8 on (4, 2) 1580 -> 1398; K = 8, 1.5 M x 2 on (1, 2)
-// 274 -> 240). With four views per lane, or the paper's raw values (six more
+// 274 -> 240; the FP64 terms of the zeta gradient have since added 5 %). With four views per lane, or the paper's raw values (six more
 // registers of activation derivatives; backward, K = 2, 1 M x 1: 98 us at three
 // waves, 87 at two), the spills cost more than the wave brings; four waves of
 // 128 registers spill too (forward K = 8, 1 M x 1: 139 us against 80).
